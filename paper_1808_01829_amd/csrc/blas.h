@@ -23,8 +23,33 @@ struct UpdateArgs {
   const double2* wst;         // FP64 window state [2][ns][2][BMS_MAX_WIN][n][n] (drain)
   int win;                    // window length of the shifts s >= 1 (1: every iteration)
   SolverFlags* flags;         // read; the matrix-core update also sets upd_done, upd_stop
+  int* upd_log;               // [max_iter] traffic and work of each iteration's update
+  int max_iter;
   int xidx[BMS_MAX_SHIFTS];
 };
+
+// The update of one iteration, for the timing statistics: block vectors moved, and
+// the n x n right products of the applied windows above bit 16 (the Q step's two are
+// added by the host). 3 block vectors for the Q step, 4 for each shift applied (P and X
+// read and written) and, once, the ring buffers of the longest window applied that are
+// not in registers (Q_{k0+1} .. Q_{k-1}). Called by the first wave of one block, a lane
+// per shift.
+__device__ __forceinline__ void log_update(const SolverFlags* fl, int* upd_log, int max_iter,
+                                           int ns) {
+  static_assert(BMS_MAX_SHIFTS <= 64, "a lane per shift");
+  const int lane = threadIdx.x & 63, iter = fl->iter, slot = iter & 1;
+  const int j = lane < ns ? fl->win_j[slot][lane] : 0;
+  const bool on = j > 0 && (fl->win_flush[slot][lane] || fl->stop);
+  int units = on ? 4 : 0, prods = on ? 2 * j : 0, qx = on && j > 2 ? j - 2 : 0;
+  for (int off = 1; off < 64; off <<= 1) {
+    units += __shfl_xor(units, off);
+    prods += __shfl_xor(prods, off);
+    const int o = __shfl_xor(qx, off);
+    qx = o > qx ? o : qx;
+  }
+  if (lane == 0 && iter >= 1 && iter <= max_iter)
+    upd_log[iter - 1] = (3 + units + qx) | (prods << 16);
+}
 
 // run_if: the kernel does nothing unless *run_if is non-zero (NULL: always runs)
 template <typename T>
@@ -84,7 +109,7 @@ struct SmallState {
   double2* alpha;   // [n*n]     alpha_k
   double2* rhoinv;  // [n*n]     rho_k^-1
   double2* delta;   // [n*n]     delta_k (unshifted residual coefficients)
-  double2* beta_s;  // [ns][n*n] beta^(s)
+  double2* beta_s;  // [ns][n*n] beta^(s); for n <= 16: 1 - beta^(s)
   double2* alpha_s; // [ns][n*n] alpha^(s)
   double* norm0;    // [n]       |b_i|
   double2* G4;      // [4][n*n]  P^H W, Q^H W, W^H W, Q^H Q of the iteration
@@ -92,7 +117,6 @@ struct SmallState {
   double2* tmp;     // [n*n]     scratch
   double* rel_last; // smallest max relative true residual of sigma_0 at a reliable update
   int* counter;     // grid-completion counter of the rho kernel
-  int* upd_log;    // [max_iter] block vectors the update of each iteration moves
   // Window state of the deferred shift update, [2][ns][2][BMS_MAX_WIN][n*n]:
   // per slot and shift the X family (Cx, Ex_0, Ex_1, ...) and the P family
   // (Cp, Ep_0, ...) of the open window started at iteration k0, such that after
@@ -127,6 +151,14 @@ hipError_t launch_small_iter(hipStream_t st, const SmallParams& p, SmallState s,
 template <typename T>
 hipError_t launch_small_rho_explicit(hipStream_t st, const SmallParams& p, SmallState s,
                                      SolverFlags* fl, cplx<T>* Mp, cplx<T>* Wm);
+// the same two for n <= 16 (smallwave.hip)
+__host__ __device__ constexpr bool small_wave_supported(int n) { return n <= 16; }
+template <typename T>
+hipError_t launch_small_iter_w(hipStream_t st, const SmallParams& p, SmallState s, SolverFlags* fl,
+                               cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm);
+template <typename T>
+hipError_t launch_small_rho_explicit_w(hipStream_t st, const SmallParams& p, SmallState s,
+                                       SolverFlags* fl, cplx<T>* Mp, cplx<T>* Wm);
 // variant 0: vector kernel; 1, 2 and the default: matrix cores, every wave
 // streaming its own rows with 4 or 8 steps in flight; 3, 4, 5: matrix cores,
 // rows staged through LDS with 1, 2 or 4 chunks in flight (n = 8, 16; other n

@@ -189,6 +189,7 @@ __global__ __launch_bounds__(BMS_WG) void k_update(UpdateArgs<T, TX> a) {
   using CX = cplx<TX>;
   const SolverFlags* fl = a.flags;
   if (fl->halted) return;
+  if (blockIdx.x == 0 && threadIdx.x < 64) log_update(fl, a.upd_log, a.max_iter, a.ns);
   constexpr int NCH = UPDATE_NCH;
   __shared__ double2 ws[BMS_WG];
   __shared__ double2 vs[BMS_WG];
@@ -1204,6 +1205,7 @@ __global__ __launch_bounds__(BMS_WG) void k_update_n(UpdateArgs<T, TX> a) {
   using CX = cplx<TX>;
   const SolverFlags* fl = a.flags;
   if (fl->halted) return;
+  if (blockIdx.x == 0 && threadIdx.x < 64) log_update(fl, a.upd_log, a.max_iter, a.ns);
   constexpr int C = BMS_WG / N;
   const int t = threadIdx.x;
   const int lr = t / N, j = t % N;

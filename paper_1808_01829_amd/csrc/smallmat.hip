@@ -8,7 +8,8 @@
 // (Sec. III, the paragraph after eq. convergence_bound_shifts). alpha_{k-1}^-1
 // is the previous Gram G_{k-1}, kept instead of inverting alpha again.
 //
-// One work-group of 256 threads per shift; matrices live in LDS (n <= 32).
+// One work-group of 256 threads per shift; matrices live in LDS (n <= 32). The two
+// kernels of the iteration take n > 16 here; for n <= 16 they are in smallwave.hip.
 #include "blas.h"
 
 #define NMAX BMS_MAX_RHS
@@ -261,7 +262,9 @@ __global__ __launch_bounds__(BMS_WG) void k_small_init(SmallParams p, SmallState
     int i = e / n, j = e - (e / n) * n;
     s.Gb[n * n + e] = make_double2(i == j ? 1.0 : 0.0, 0);
     for (int q = 0; q < p.ns; ++q) {
-      s.beta_s[(size_t)q * n * n + e] = make_double2(i == j ? 1.0 : 0.0, 0);
+      // beta_0 = 1; the kernels for n <= 16 keep 1 - beta
+      s.beta_s[(size_t)q * n * n + e] =
+          make_double2(i == j && !small_wave_supported(n) ? 1.0 : 0.0, 0);
       s.alpha_s[(size_t)q * n * n + e] = make_double2(i == j ? 1.0 : 0.0, 0);
     }
   }
@@ -352,11 +355,7 @@ __global__ __launch_bounds__(BMS_WG) void k_small_reliable(SmallParams p, SmallS
 
 // Completion of one iteration's small step: count this block's arrival and
 // whether its shift met tol; the last block to arrive stops the solve when
-// all did, logs the update's traffic and work and advances the iteration
-// counter. The
-// update moves 3 block vectors for the Q step, 4 for each shift it applies
-// (P and X read and written) and, once, the ring buffers of the longest
-// window applied that are not in registers (Q_{k0+1} .. Q_{k-1}).
+// all did and advances the iteration counter.
 __device__ void finish_shift(const SmallParams& p, const SmallState& s, SolverFlags* fl,
                              int done) {
   if (threadIdx.x == 0) {
@@ -365,20 +364,6 @@ __device__ void finish_shift(const SmallParams& p, const SmallState& s, SolverFl
     if ((v & 0xffff) == p.ns) {
       __threadfence();
       if ((v >> 16) == p.ns || fl->error) fl->stop = 1;
-      const int ws = (fl->iter + 1) & 1;
-      int units = 3, qx = 0, prods = 0;
-      for (int i = 0; i < p.ns; ++i) {
-        const int j = fl->win_j[ws][i];
-        if (j > 0 && (fl->win_flush[ws][i] || fl->stop)) {
-          units += 4;
-          prods += 2 * j;
-          qx = j - 2 > qx ? j - 2 : qx;
-        }
-      }
-      units += qx;
-      // block vectors moved, and the n x n right products of the applied
-      // windows above bit 16 (the Q step's two are added by the host)
-      if (s.upd_log && fl->iter < p.max_iter) s.upd_log[fl->iter] = units | (prods << 16);
       fl->need_explicit = 0;
       fl->iter = fl->iter + 1;
       atomicExch(s.counter, 0);
@@ -670,6 +655,7 @@ hipError_t launch_small_reliable(hipStream_t st, const SmallParams& p, SmallStat
 template <typename T>
 hipError_t launch_small_iter(hipStream_t st, const SmallParams& p, SmallState s, SolverFlags* fl,
                              cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm) {
+  if (small_wave_supported(p.n)) return launch_small_iter_w<T>(st, p, s, fl, Mx, Mp, Wm);
   k_small_iter<T><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm);
   return hipGetLastError();
 }
@@ -677,6 +663,7 @@ hipError_t launch_small_iter(hipStream_t st, const SmallParams& p, SmallState s,
 template <typename T>
 hipError_t launch_small_rho_explicit(hipStream_t st, const SmallParams& p, SmallState s,
                                      SolverFlags* fl, cplx<T>* Mp, cplx<T>* Wm) {
+  if (small_wave_supported(p.n)) return launch_small_rho_explicit_w<T>(st, p, s, fl, Mp, Wm);
   k_small_rho_explicit<T><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mp, Wm);
   return hipGetLastError();
 }

@@ -45,6 +45,8 @@ struct Work {
   void *W1, *W, *Q, *P, *X, *Mx, *Mp, *Wm;
   SmallState sm;
   SolverFlags* flags;
+  int* upd_log;  // [max_iter], see log_update
+  int max_iter;
   double2* partials;
   double2* Rinv;
   double2* Gtmp;
@@ -135,7 +137,8 @@ int alloc_work(bms_ctx* c, int n, int ns, int max_iter, int win, Work& w) {
   w.sm.counter = (int*)((char*)fp + sizeof(SolverFlags));
   void* lp;
   if ((rc = scratch_buf(c, S_LOG, (size_t)max_iter * sizeof(int) + 64, &lp))) return rc;
-  w.sm.upd_log = (int*)lp;
+  w.upd_log = (int*)lp;
+  w.max_iter = max_iter;
   return BMS_OK;
 }
 
@@ -162,6 +165,8 @@ UpdateArgs<T, T> update_args(const Work& w) {
   ua.wst = w.sm.wst;
   ua.win = w.win;
   ua.flags = w.flags;
+  ua.upd_log = w.upd_log;
+  ua.max_iter = w.max_iter;
   for (int s = 0; s < BMS_MAX_SHIFTS; ++s) ua.xidx[s] = s < w.ns ? s : 0;
   return ua;
 }
@@ -270,7 +275,7 @@ std::string chunk_key(const bms_ctx* c, const Work& w, const SmallParams& sp, do
   struct {
     const void* p[16];
     double mass;
-    int K, n, ns, nb, hop_v, gram_v, upd_v, prec, nlinks;
+    int K, n, ns, nb, hop_v, gram_v, upd_v, prec, nlinks, max_iter;
     HopCfg hop_cfg[2];
     SmallParams sp;
     SmallState sm;
@@ -279,7 +284,7 @@ std::string chunk_key(const bms_ctx* c, const Work& w, const SmallParams& sp, do
   const bool two = c->links_two_rows && c->nlinks == 8;
   const void* ptrs[16] = {w.W1, w.W, w.Q, w.P, w.X, w.Mx, w.Mp, w.flags, w.partials, w.sm.counter,
                           two ? c->links64r.p : c->links64.p, two ? c->links32r.p : c->links32.p,
-                          w.Wm, w.sm.wst, two ? c->lsign.p : nullptr, nullptr};
+                          w.Wm, w.sm.wst, two ? c->lsign.p : nullptr, w.upd_log};
   for (int i = 0; i < 16; ++i) k.p[i] = ptrs[i];
   k.mass = mass;
   k.K = K;
@@ -291,6 +296,7 @@ std::string chunk_key(const bms_ctx* c, const Work& w, const SmallParams& sp, do
   k.upd_v = c->update_variant;
   k.prec = (int)sizeof(T);
   k.nlinks = c->nlinks;
+  k.max_iter = w.max_iter;
   k.hop_cfg[0] = c->hop_cfg[0];
   k.hop_cfg[1] = c->hop_cfg[1];
   k.sp = sp;
@@ -444,7 +450,7 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
   if (w.win > 1) HIP_TRY(c, launch_update_drain<T>(c->stream, update_args<T>(w)));
   if (c->timing && hf.iter > 0) {
     std::vector<int> units(hf.iter);
-    HIP_TRY(c, hipMemcpyAsync(units.data(), w.sm.upd_log, hf.iter * sizeof(int),
+    HIP_TRY(c, hipMemcpyAsync(units.data(), w.upd_log, hf.iter * sizeof(int),
                               hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     double S = (double)w.blk * sizeof(cplx<T>);

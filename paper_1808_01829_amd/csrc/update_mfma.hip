@@ -286,6 +286,7 @@ void k_update_mfma(UpdateArgs<F, F> a) {
     fl->upd_done = iter;
     fl->upd_stop = stop;
   }
+  if (blockIdx.x == 0 && tid < 64) log_update(fl, a.upd_log, a.max_iter, a.ns);
   const int lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, c = lane & 15;
   const int rows = a.rows, ns = a.ns, win = a.win;
