@@ -377,8 +377,8 @@ int bms_rhmc_trajectory(bms_ctx* ctx, const bms_rhmc_params* p, void* U, void* P
  * accumulators; bms_timing_read returns them (host pointers, any may be NULL).
  * bms_timing_flops returns the matrix-core work of the same launches for
  * BMS_KERNEL_UPDATE (the real products of the Q step and of the applied
- * windows, 2 flops per multiply-add: per complex product 3 rows n^2 for
- * n = 16, rows (2n)^2 for n = 8), split into FP64 and FP32 arithmetic; 0 for
+ * windows, 2 flops per multiply-add: per complex product 3 rows 16^2 for
+ * n = 13 .. 16, 3 rows 12 16 for n = 9 .. 12, rows (2n)^2 for n = 8), split into FP64 and FP32 arithmetic; 0 for
  * the other classes and for the vector kernels.
  * bms_timing_floor returns in *seconds the least time the recorded launches
  * of a class need at the given peaks (bytes/s, FP64 and FP32 flops/s, each
@@ -404,7 +404,8 @@ int bms_timing_enable(bms_ctx* ctx, int enable);
  * than the smallest are updated once per window of iterations (4 in FP64,
  * 8 in FP32: X^(s) and P^(s) of the whole window from the window's start and
  * the Q blocks it spans, 4 block vectors per shift per window instead of per
- * iteration; Algorithm 1's updates composed over the window);
+ * iteration; Algorithm 1's updates composed over the window; the other n up
+ * to 16 always run such a windowed kernel);
  * 6 = the same kernel updating every shift every iteration, one tile per
  * wave; 0..3 = the vector kernels
  * (0 = four row chunks per work-group with both coefficient columns in

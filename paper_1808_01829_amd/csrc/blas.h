@@ -15,6 +15,7 @@ struct UpdateArgs {
   const cplx<T>* W;           // [rows][n]  (A + s0) P^(0)
   const double2* alpha;       // n x n FP64
   const double2* rhoinv;      // n x n FP64
+  const double2* arho;        // n x n FP64: -alpha rho^-1 (n <= 16)
   cplx<T>* P;                 // [ns][rows][n] search directions, sorted shift order
   cplx<TX>* X;                // solutions; shift s at X + xidx[s]*rows*n
   const cplx<T>* Mx;          // [ns][n][n]
@@ -61,9 +62,11 @@ hipError_t launch_update(hipStream_t st, const UpdateArgs<T, TX>& a);
 // variant 0: both coefficient columns in registers; 1: one at a time
 template <typename T, typename TX>
 hipError_t launch_update_fast(hipStream_t st, const UpdateArgs<T, TX>& a, int variant);
-// update on the matrix cores (update_mfma.hip), for n = 8 and 16, with one or
-// two 16-row tiles per wave; F = double or float (the Q step is FP64 in both)
-bool update_mfma_supported(int n);
+// windowed update (update_mfma.hip), F = double or float (the Q step is FP64 in both): on the
+// matrix cores for n = 8 .. 16 (n = 8 and 16 with one or two 16-row tiles per wave), on the
+// vector units for n < 8
+bool update_mfma_supported(int n);  // n = 8, 16: the widths with a choice of kernels
+bool update_windowed(int n);        // n <= 16
 // The shifts s >= 1 are updated in windows of SmallParams::win iterations
 // (the small step gathers each window's coefficients, see SmallState::wst);
 // after the last iteration launch_update_drain applies every window still
@@ -108,6 +111,7 @@ struct SmallState {
   double2* rhob;    // [2][n*n]  rho_k
   double2* alpha;   // [n*n]     alpha_k
   double2* rhoinv;  // [n*n]     rho_k^-1
+  double2* arho;    // [n*n]     -alpha_k rho_k^-1 (n <= 16)
   double2* delta;   // [n*n]     delta_k (unshifted residual coefficients)
   double2* beta_s;  // [ns][n*n] beta^(s); for n <= 16: 1 - beta^(s)
   double2* alpha_s; // [ns][n*n] alpha^(s)

@@ -1222,166 +1222,132 @@ __global__ __launch_bounds__(BMS_WG) void k_update_n(UpdateArgs<T, TX> a) {
     off[ch] = (size_t)(rbase + ch * C) * N + t;
   }
   C_ qn[NCH];
-  if constexpr (N == 1) {
-    // no row mixing: every product is a scalar multiplication
-    double2 al = a.alpha[0], ri = a.rhoinv[0];
+  // rows padded to N + 1 entries: the rows a wave reads sit in different banks
+  constexpr int RS = N + 1;
+  constexpr int CS = C * RS;
+  __shared__ double2 buf[NCH * CS];
+  __shared__ C_ ps[NCH * CS];
+  const int lw = lr * RS + j;  // this thread's LDS slot inside a chunk
+  double2 mcol[N];
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      if (!act[ch]) continue;
-      double2 v = csub(to_d(a.Q[off[ch]]), cmul(to_d(a.W[off[ch]]), al));
-      qn[ch] = from_d<C_>(cmul(v, ri));
-      a.Q[off[ch]] = qn[ch];
-    }
-    for (int s = 0; s < ns; ++s) {
-      if (!fl->active[s]) continue;
-      C_* P = a.P + (size_t)s * rows;
-      CX* X = a.X + (size_t)a.xidx[s] * rows;
-      C_ mx = a.Mx[s], mp = a.Mp[s];
-      C_ p[NCH];
-      CX x[NCH];
+  for (int ch = 0; ch < NCH; ++ch)
+    if (act[ch]) buf[ch * CS + lw] = to_d(a.W[off[ch]]);
 #pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) {
-        if (!act[ch]) continue;
-        p[ch] = P[off[ch]];
-        x[ch] = X[off[ch]];
-      }
+  for (int k = 0; k < N; ++k) mcol[k] = a.alpha[k * N + j];
+  __syncthreads();
+  double2 v[NCH];
 #pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) {
-        if (!act[ch]) continue;
-        C_ dx = cmul(p[ch], mx);
-        X[off[ch]] = cmk<CX>(x[ch].x + (TX)dx.x, x[ch].y + (TX)dx.y);
-        P[off[ch]] = cfma(p[ch], mp, qn[ch]);
-      }
-    }
-    return;
-  } else {
-    // rows padded to N + 1 entries: the rows a wave reads sit in different banks
-    constexpr int RS = N + 1;
-    constexpr int CS = C * RS;
-    __shared__ double2 buf[NCH * CS];
-    __shared__ C_ ps[NCH * CS];
-    const int lw = lr * RS + j;  // this thread's LDS slot inside a chunk
-    double2 mcol[N];
+  for (int ch = 0; ch < NCH; ++ch) {
+    if (!act[ch]) continue;
+    double2 wa = make_double2(0, 0);
+    const double2* wr = buf + ch * CS + lr * RS;
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch)
-      if (act[ch]) buf[ch * CS + lw] = to_d(a.W[off[ch]]);
+    for (int k = 0; k < N; ++k) wa = cfma(wr[k], mcol[k], wa);
+    v[ch] = csub(to_d(a.Q[off[ch]]), wa);
+  }
+  __syncthreads();
 #pragma unroll
-    for (int k = 0; k < N; ++k) mcol[k] = a.alpha[k * N + j];
-    __syncthreads();
-    double2 v[NCH];
+  for (int ch = 0; ch < NCH; ++ch)
+    if (act[ch]) buf[ch * CS + lw] = v[ch];
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      if (!act[ch]) continue;
-      double2 wa = make_double2(0, 0);
-      const double2* wr = buf + ch * CS + lr * RS;
+  for (int k = 0; k < N; ++k) mcol[k] = a.rhoinv[k * N + j];
+  __syncthreads();
 #pragma unroll
-      for (int k = 0; k < N; ++k) wa = cfma(wr[k], mcol[k], wa);
-      v[ch] = csub(to_d(a.Q[off[ch]]), wa);
-    }
-    __syncthreads();
+  for (int ch = 0; ch < NCH; ++ch) {
+    if (!act[ch]) continue;
+    double2 q = make_double2(0, 0);
+    const double2* vr = buf + ch * CS + lr * RS;
+#pragma unroll
+    for (int k = 0; k < N; ++k) q = cfma(vr[k], mcol[k], q);
+    qn[ch] = from_d<C_>(q);
+    a.Q[off[ch]] = qn[ch];
+  }
+  // shifts, with the next active shift's rows prefetched
+  C_ pn[NCH];
+  CX xn[NCH], xv[NCH];
+  int s = next_active(fl, -1, ns);
+  if (s < ns) {
+    const C_* P = a.P + (size_t)s * rows * N;
+    const CX* X = a.X + (size_t)a.xidx[s] * rows * N;
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch)
-      if (act[ch]) buf[ch * CS + lw] = v[ch];
+      if (act[ch]) {
+        pn[ch] = P[off[ch]];
+        xn[ch] = X[off[ch]];
+      }
+  }
+  while (s < ns) {
+    const int s2 = next_active(fl, s, ns);
+    C_* P = a.P + (size_t)s * rows * N;
+    CX* X = a.X + (size_t)a.xidx[s] * rows * N;
+    const C_* Mx = a.Mx + (size_t)s * N * N;
+    const C_* Mp = a.Mp + (size_t)s * N * N;
 #pragma unroll
-    for (int k = 0; k < N; ++k) mcol[k] = a.rhoinv[k * N + j];
+    for (int ch = 0; ch < NCH; ++ch)
+      if (act[ch]) {
+        ps[ch * CS + lw] = pn[ch];
+        xv[ch] = xn[ch];
+      }
     __syncthreads();
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      if (!act[ch]) continue;
-      double2 q = make_double2(0, 0);
-      const double2* vr = buf + ch * CS + lr * RS;
-#pragma unroll
-      for (int k = 0; k < N; ++k) q = cfma(vr[k], mcol[k], q);
-      qn[ch] = from_d<C_>(q);
-      a.Q[off[ch]] = qn[ch];
-    }
-    // shifts, with the next active shift's rows prefetched
-    C_ pn[NCH];
-    CX xn[NCH], xv[NCH];
-    int s = next_active(fl, -1, ns);
-    if (s < ns) {
-      const C_* P = a.P + (size_t)s * rows * N;
-      const CX* X = a.X + (size_t)a.xidx[s] * rows * N;
+    if (s2 < ns) {
+      const C_* P2 = a.P + (size_t)s2 * rows * N;
+      const CX* X2 = a.X + (size_t)a.xidx[s2] * rows * N;
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch)
         if (act[ch]) {
-          pn[ch] = P[off[ch]];
-          xn[ch] = X[off[ch]];
+          pn[ch] = P2[off[ch]];
+          xn[ch] = X2[off[ch]];
         }
     }
-    while (s < ns) {
-      const int s2 = next_active(fl, s, ns);
-      C_* P = a.P + (size_t)s * rows * N;
-      CX* X = a.X + (size_t)a.xidx[s] * rows * N;
-      const C_* Mx = a.Mx + (size_t)s * N * N;
-      const C_* Mp = a.Mp + (size_t)s * N * N;
+    if constexpr (SPLIT) {
+      C_ m[N];
 #pragma unroll
-      for (int ch = 0; ch < NCH; ++ch)
-        if (act[ch]) {
-          ps[ch * CS + lw] = pn[ch];
-          xv[ch] = xn[ch];
-        }
-      __syncthreads();
-      if (s2 < ns) {
-        const C_* P2 = a.P + (size_t)s2 * rows * N;
-        const CX* X2 = a.X + (size_t)a.xidx[s2] * rows * N;
+      for (int k = 0; k < N; ++k) m[k] = Mx[k * N + j];
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch)
-          if (act[ch]) {
-            pn[ch] = P2[off[ch]];
-            xn[ch] = X2[off[ch]];
-          }
+      for (int ch = 0; ch < NCH; ++ch) {
+        if (!act[ch]) continue;
+        const C_* pr = ps + ch * CS + lr * RS;
+        C_ dx = czero<C_>();
+#pragma unroll
+        for (int k = 0; k < N; ++k) dx = cfma(pr[k], m[k], dx);
+        X[off[ch]] = cmk<CX>(xv[ch].x + (TX)dx.x, xv[ch].y + (TX)dx.y);
       }
-      if constexpr (SPLIT) {
-        C_ m[N];
 #pragma unroll
-        for (int k = 0; k < N; ++k) m[k] = Mx[k * N + j];
+      for (int k = 0; k < N; ++k) m[k] = Mp[k * N + j];
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-          if (!act[ch]) continue;
-          const C_* pr = ps + ch * CS + lr * RS;
-          C_ dx = czero<C_>();
+      for (int ch = 0; ch < NCH; ++ch) {
+        if (!act[ch]) continue;
+        const C_* pr = ps + ch * CS + lr * RS;
+        C_ np = qn[ch];
 #pragma unroll
-          for (int k = 0; k < N; ++k) dx = cfma(pr[k], m[k], dx);
-          X[off[ch]] = cmk<CX>(xv[ch].x + (TX)dx.x, xv[ch].y + (TX)dx.y);
-        }
+        for (int k = 0; k < N; ++k) np = cfma(pr[k], m[k], np);
+        P[off[ch]] = np;
+      }
+    } else {
+      C_ mx[N], mp[N];
 #pragma unroll
-        for (int k = 0; k < N; ++k) m[k] = Mp[k * N + j];
+      for (int k = 0; k < N; ++k) {
+        mx[k] = Mx[k * N + j];
+        mp[k] = Mp[k * N + j];
+      }
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-          if (!act[ch]) continue;
-          const C_* pr = ps + ch * CS + lr * RS;
-          C_ np = qn[ch];
-#pragma unroll
-          for (int k = 0; k < N; ++k) np = cfma(pr[k], m[k], np);
-          P[off[ch]] = np;
-        }
-      } else {
-        C_ mx[N], mp[N];
+      for (int ch = 0; ch < NCH; ++ch) {
+        if (!act[ch]) continue;
+        const C_* pr = ps + ch * CS + lr * RS;
+        C_ dx = czero<C_>();
+        C_ np = qn[ch];
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-          mx[k] = Mx[k * N + j];
-          mp[k] = Mp[k * N + j];
+          C_ pk = pr[k];
+          dx = cfma(pk, mx[k], dx);
+          np = cfma(pk, mp[k], np);
         }
-#pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-          if (!act[ch]) continue;
-          const C_* pr = ps + ch * CS + lr * RS;
-          C_ dx = czero<C_>();
-          C_ np = qn[ch];
-#pragma unroll
-          for (int k = 0; k < N; ++k) {
-            C_ pk = pr[k];
-            dx = cfma(pk, mx[k], dx);
-            np = cfma(pk, mp[k], np);
-          }
-          X[off[ch]] = cmk<CX>(xv[ch].x + (TX)dx.x, xv[ch].y + (TX)dx.y);
-          P[off[ch]] = np;
-        }
+        X[off[ch]] = cmk<CX>(xv[ch].x + (TX)dx.x, xv[ch].y + (TX)dx.y);
+        P[off[ch]] = np;
       }
-      __syncthreads();
-      s = s2;
     }
+    __syncthreads();
+    s = s2;
   }
 }
 
@@ -1398,9 +1364,6 @@ template <typename T, typename TX>
 hipError_t launch_update_fast(hipStream_t st, const UpdateArgs<T, TX>& a, int variant) {
   // variant: 0 = NCH 4 both columns, 1 = NCH 2 split, 2 = NCH 4 split, 3 = NCH 2 both
   switch (a.n) {
-    case 1: return launch_update_n<T, TX, 1, 4, 0>(st, a);
-    case 2: return launch_update_n<T, TX, 2, 4, 0>(st, a);
-    case 4: return launch_update_n<T, TX, 4, 4, 0>(st, a);
     case 8:
       switch (variant) {
         case 1: return launch_update_n<T, TX, 8, 2, 1>(st, a);

@@ -236,7 +236,8 @@ __device__ __forceinline__ int wm_cholesky(WM<NE> a, int n, int g, int c, double
 
 // ---- the iteration ------------------------------------------------------------
 
-// What the four waves exchange once rho_k is known.
+// What the four waves exchange once rho_k is known: rho, alpha^(s), for a shift beta^(s)^H,
+// for sigma_0 alpha (in bh) and rho^-H (in t).
 struct SmallLds {
   double2 rho[WLDS], mx[WLDS], bh[WLDS], t[WLDS];
   int st1, st2, st3;
@@ -321,6 +322,18 @@ __device__ __forceinline__ void rho_part_w(const SmallParams& p, const SmallStat
     wm_store(tp + (size_t)j0 * nn, n, n, g, c, mp);
     if (q == 0) wm_store(s.rhob + (size_t)cur * nn, n, n, g, c, wm_load<NE>(l.rho, WP, n, g, c));
   } else if (wave == 3) {
+    if (q == 0) {
+      // rho^-1 and -alpha rho^-1 for the update's Q step
+      const WM<NE> ri = wm_loadh<NE>(l.t, WP, n, g, c);
+      WM<NE> ar = wm_mulh(wm_loadh<NE>(l.bh, WP, n, g, c), ri);
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        ar.re[e] = -ar.re[e];
+        ar.im[e] = -ar.im[e];
+      }
+      wm_store(s.rhoinv, n, n, g, c, ri);
+      wm_store(s.arho, n, n, g, c, ar);
+    }
     wm_store(nx + (size_t)j0 * nn, n, n, g, c, mx);
     wm_store(tx + (size_t)j0 * nn, n, n, g, c, mx);
   }
@@ -348,17 +361,14 @@ __device__ __forceinline__ double lds_trace(const double2* m, int n) {
   return t;
 }
 
-// R and R^-1 of this wave to where the others and the update find them
+// rho_k (for sigma_0 also rho_k^-H and alpha_k) to where the other waves find them
 template <int NE>
-__device__ __forceinline__ void put_rho(SmallLds& l, const SmallState& s, int n, int g, int c,
-                                        int q, const WM<NE>& r, const WM<NE>& rih) {
+__device__ __forceinline__ void put_rho(SmallLds& l, int n, int g, int c, int q, const WM<NE>& r,
+                                        const WM<NE>& rih, const WM<NE>& alpha) {
   wm_store(l.rho, WP, n, g, c, r);
   if (q > 0) return;
-#pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    const int row = 4 * e + g;
-    if (row < n && c < n) s.rhoinv[c * n + row] = make_double2(rih.re[e], -rih.im[e]);
-  }
+  wm_store(l.t, WP, n, g, c, rih);
+  wm_store(l.bh, WP, n, g, c, alpha);
 }
 
 // One iteration's n x n work after G4 = [P^H W, Q^H W, W^H W, Q^H Q] (the steps and
@@ -444,7 +454,7 @@ __global__ __launch_bounds__(BMS_WG) void k_small_iter_w(SmallParams p, SmallSta
       int st2 = BMS_EBREAKDOWN;
       if (!cancel) {
         st2 = wm_cholesky(E, n, g, c, p.breakdown_tol, tv, R, rih);
-        if (st2 == 0 && st1 == 0) put_rho(l, s, n, g, c, q, R, rih);
+        if (st2 == 0 && st1 == 0) put_rho(l, n, g, c, q, R, rih, A);
       }
       if (lane == 0) {
         l.st1 = st1;
@@ -520,7 +530,7 @@ __global__ __launch_bounds__(BMS_WG) void k_small_rho_explicit_w(SmallParams p, 
     WM<NE> E = wm_load<NE>(s.Gqr, n, n, g, c), R, rih;
     E = wm_hermitian(l.t, n, g, c, E);
     const int st = wm_cholesky(E, n, g, c, p.breakdown_tol, lds_trace(l.t, n), R, rih);
-    if (st == 0) put_rho(l, s, n, g, c, q, R, rih);
+    if (st == 0) put_rho(l, n, g, c, q, R, rih, wm_load<NE>(s.alpha, n, n, g, c));
     if (lane == 0) l.st2 = st;
   } else if (wave == 1) {
     const WM<NE> a1 = wm_load<NE>(s.alpha_s + (size_t)q * nn, n, n, g, c);

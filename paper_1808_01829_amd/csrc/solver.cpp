@@ -53,15 +53,16 @@ struct Work {
   int nb;
 };
 
-// Update window of the shifts s >= 1: the matrix-core update (variants -1, 4,
-// 5 at n = 8, 16) applies each shift's X and P updates once per window of
+// Update window of the shifts s >= 1: the windowed update (n <= 16; at n = 8
+// and 16 variants -1, 4, 5) applies each shift's X and P updates once per window of
 // iterations; its length is the longest the kernel stages (4 in FP64, 8 in
 // FP32) that divides the chunk of iterations between host checks, so that
 // every window closes at a chunk's end (where the mixed solver's reliable
 // update needs every X). Variant 6, the vector kernels and one shift: 1.
 int update_window(const bms_ctx* c, int n, int ns, int elem_bytes, int check_interval) {
   const int uv = c->update_variant;
-  if (ns < 2 || !update_mfma_supported(n) || !(uv < 0 || uv == 4 || uv == 5)) return 1;
+  if (ns < 2 || !update_windowed(n)) return 1;
+  if (update_mfma_supported(n) && !(uv < 0 || uv == 4 || uv == 5)) return 1;
   int w = elem_bytes == 8 ? update_mfma_max_win<double>() : update_mfma_max_win<float>();
   w = std::min(w, BMS_MAX_WIN);
   while (w > 1 && check_interval % w) w >>= 1;
@@ -71,7 +72,7 @@ int update_window(const bms_ctx* c, int n, int ns, int elem_bytes, int check_int
 // n x n FP64 entries of the small state (SmallState), the window state included
 size_t small_elems(int n, int ns) {
   const size_t nn = (size_t)n * n;
-  return 2 * nn + 2 * nn + 8 * nn + 2 * ns * nn + 3 * nn + n + 1 +
+  return 2 * nn + 2 * nn + 9 * nn + 2 * ns * nn + 3 * nn + n + 1 +
          (size_t)2 * ns * 2 * BMS_MAX_WIN * nn;
 }
 
@@ -102,6 +103,8 @@ int alloc_work(bms_ctx* c, int n, int ns, int max_iter, int win, Work& w) {
   d += nn;
   w.sm.rhoinv = d;
   d += nn;
+  w.sm.arho = d;
+  d += nn;
   w.sm.delta = d;
   d += nn;
   w.sm.G4 = d;
@@ -127,7 +130,8 @@ int alloc_work(bms_ctx* c, int n, int ns, int max_iter, int win, Work& w) {
   if ((rc = scratch_buf(c, S_PART, part_bytes(w.nb, 4 * nn), &pp))) return rc;
   w.partials = (double2*)pp;
   void* mp;
-  if ((rc = scratch_buf(c, S_M, (2 + 2 * BMS_MAX_WIN) * ns * nn * es, &mp))) return rc;
+  // (a KiB past the last matrix: the update copies coefficients in whole KiB)
+  if ((rc = scratch_buf(c, S_M, (2 + 2 * BMS_MAX_WIN) * ns * nn * es + 1024, &mp))) return rc;
   w.Mx = mp;
   w.Mp = (char*)mp + ns * nn * es;
   w.Wm = (char*)mp + 2 * ns * nn * es;
@@ -157,6 +161,7 @@ UpdateArgs<T, T> update_args(const Work& w) {
   ua.W = (const cplx<T>*)w.W;
   ua.alpha = w.sm.alpha;
   ua.rhoinv = w.sm.rhoinv;
+  ua.arho = w.sm.arho;
   ua.P = (cplx<T>*)w.P;
   ua.X = (cplx<T>*)w.X;
   ua.Mx = (const cplx<T>*)w.Mx;
@@ -202,10 +207,10 @@ int enqueue_iteration(bms_ctx* c, const Work& w, const SmallParams& sp, double m
                                           (cplx<T>*)w.Wm));
   MARK(6);
   const UpdateArgs<T, T> ua = update_args<T>(w);
-  // built-in default: the matrix-core kernel where it exists (n = 8, 16), else
-  // four row chunks with one coefficient column at a time
+  // the windowed kernels for n <= 16 (n = 8, 16: unless a vector variant is set), else the
+  // vector kernel
   const int uv = c->update_variant;
-  if (update_mfma_supported(w.n) && (uv < 0 || uv >= 4))
+  if (update_windowed(w.n) && (!update_mfma_supported(w.n) || uv < 0 || uv >= 4))
     HIP_TRY(c, launch_update_mfma<T>(c->stream, ua, uv == 5));
   else
     HIP_TRY(c, (launch_update_fast<T, T>(c->stream, ua, uv < 0 || uv >= 4 ? 2 : uv)));
@@ -455,10 +460,13 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     double S = (double)w.blk * sizeof(cplx<T>);
     // matrix-core flops of one complex right product of a row block by an
-    // n x n matrix: three real products (rows n^2 FMA each) for n = 16, one
-    // real product by the 2n x 2n form (rows (2n)^2 FMA) for n = 8
-    const double prod = n == 16 ? 6.0 * w.rows * n * n : 2.0 * w.rows * (2.0 * n) * (2.0 * n);
-    const bool mf = update_mfma_supported(n) && (c->update_variant < 0 || c->update_variant >= 4);
+    // n x n matrix: three real products for n > 8 (per 16-row tile 9 steps of
+    // 16 x 16 x 4 up to n = 12, then 12), one real product by the 2n x 2n form (rows (2n)^2
+    // FMA) for n = 8
+    const double prod = n > 8 ? (n > 12 ? 1536.0 : 1152.0) * w.rows
+                              : 2.0 * w.rows * (2.0 * n) * (2.0 * n);
+    const bool mf = n >= 8 && update_windowed(n) &&
+                    (!update_mfma_supported(n) || c->update_variant < 0 || c->update_variant >= 4);
     for (int k = 0; k < hf.iter; ++k) {
       const double b = (units[k] & 0xffff) * S;
       c->kt_bytes[BMS_KERNEL_UPDATE] += b;
@@ -543,7 +551,7 @@ int solve_reserve(bms_ctx* c, double mass, int n, int ns, const double* shifts, 
       {S_SMALL, small_elems(n, ns) * e + 64},
       {S_PART, std::max(part_bytes(gram_blocks((int)rows, n, c->num_cu), 4 * (int)nn),
                         part_bytes(gram_blocks((int)rows, 1, c->num_cu), 4))},
-      {S_M, (2 + 2 * BMS_MAX_WIN) * ns * nn * e},
+      {S_M, (2 + 2 * BMS_MAX_WIN) * ns * nn * e + 1024},
       {S_FLAGS, kFlagsBytes},
       {S_LOG, (size_t)max_iter * sizeof(int) + 64},
       {S_R1, blk * e},

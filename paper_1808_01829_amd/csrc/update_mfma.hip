@@ -22,10 +22,11 @@
 //   D: lane (g, c) holds four rows of the tile at real output column nt*16 + c,
 //      which for n = 16 is (Re, Im) of complex column c in the two n-tiles: one
 //      complex per row, so X and P are read and written as whole complex numbers.
-// The Q step's two coefficient matrices are expanded into that B layout in
-// LDS once per work-group. The shift coefficients are kept in LDS as complex
-// n x n matrices (double-buffered, one barrier per shift), and each lane
-// forms its B operands from them one k-step at a time.
+// The coefficients of the Q step (rho^-1 and -alpha rho^-1, both from the small step)
+// and of the shifts are kept in LDS as complex n x n matrices, and each lane forms
+// its B operands from them one k-step at a time.
+#include <algorithm>
+
 #include "blas.h"
 
 namespace {
@@ -71,40 +72,15 @@ struct Mf<float> {
   __device__ static __forceinline__ int row(int g, int p) { return 4 * g + p; }
 };
 
+// N: block width (8 or 16), or the largest width (12 or 16) the form for a width
+// known at run time takes. Widths above 8 take the three-product form below.
 template <int N>
 struct MfShape {
-  static constexpr int NR = 2 * N;      // reals per row
-  static constexpr int KS = NR / 4;     // k-steps of 4
-  static constexpr int NT = NR / 16;    // 16-column output tiles
-  static constexpr int BSZ = NR * NR;   // reals of one expanded matrix
+  static constexpr bool three = N > 8;
+  static constexpr int KS = N / 2;            // reals of a row per lane group: k-steps of 4
+  static constexpr int NT = three ? 2 : 1;    // 16-column output tiles
+  static constexpr int PITCH = NT * 16;       // reals per row of the staged output tiles
 };
-
-// entry (kk, flat) of the expanded matrix -> its LDS slot in B-operand order
-template <int N>
-__device__ __forceinline__ int bslot(int kk, int flat) {
-  using S = MfShape<N>;
-  int gg = kk / S::KS, ks = kk - gg * S::KS;
-  int nt = flat >> 4, cc = flat & 15;
-  return ((ks * 64) + gg * 16 + cc) * S::NT + nt;
-}
-
-// expand complex m = M[k][j] into the four reals it contributes
-template <int N, typename F>
-__device__ __forceinline__ void bput(F* B, int k, int j, double2 m) {
-  B[bslot<N>(2 * k, j)] = (F)m.x;
-  B[bslot<N>(2 * k, N + j)] = (F)m.y;
-  B[bslot<N>(2 * k + 1, j)] = (F)-m.y;
-  B[bslot<N>(2 * k + 1, N + j)] = (F)m.x;
-}
-
-template <int N, typename F>
-__device__ __forceinline__ void bload(const F* B, int lane, F (&b)[MfShape<N>::KS][MfShape<N>::NT]) {
-  using S = MfShape<N>;
-#pragma unroll
-  for (int ks = 0; ks < S::KS; ++ks)
-#pragma unroll
-    for (int nt = 0; nt < S::NT; ++nt) b[ks][nt] = B[(ks * 64 + lane) * S::NT + nt];
-}
 
 // The shift coefficients are kept in LDS as the complex n x n matrix, (re,
 // im) pairs, half of the expanded form; each lane forms its B-operand
@@ -118,32 +94,34 @@ __device__ __forceinline__ void mfma_acc_c(typename Mf<F>::V (&d)[MfShape<N>::NT
                                            int c) {
   using S = MfShape<N>;
 #pragma unroll
-  for (int ks = 0; ks < S::KS; ++ks)
-#pragma unroll
-    for (int nt = 0; nt < S::NT; ++nt) {
-      const int kk = g * S::KS + ks, flat = nt * 16 + c;
-      const int k = kk >> 1, rim = kk & 1, j = flat % N, cim = flat / N;
-      const F v = M[2 * (k * N + j) + (rim ^ cim)];
-      d[nt] = Mf<F>::mfma(a[ks], rim && !cim ? -v : v, d[nt]);
-    }
+  for (int ks = 0; ks < S::KS; ++ks) {
+    const int kk = g * S::KS + ks, k = kk >> 1, rim = kk & 1, j = c % N, cim = c / N;
+    const F v = M[2 * (k * N + j) + (rim ^ cim)];
+    d[0] = Mf<F>::mfma(a[ks], rim && !cim ? -v : v, d[0]);
+  }
 }
 
-// n = 16: the complex right product by Gauss's three real products. With
-// the A operand of a lane holding complex columns 4g .. 4g+3 of its row (the
-// same contiguous run as above), k-step ks contracts over complex column
-// kc = 4g + ks, and the three accumulators gather
+// n > 8: the complex right product by Gauss's three real products. With
+// the A operand of a lane holding complex columns KC g .. KC g + KC - 1 of its
+// row (KC = N / 4; the same contiguous run as above), k-step ks contracts over
+// complex column kc = KC g + ks, and the three accumulators gather
 //   d0 = sum Re a Re M,  d1 = sum Im a Im M,  d2 = sum (Re a + Im a)(Re M + Im M),
 // from which Re(a M) = d0 - d1 and Im(a M) = d2 - d0 - d1 (mfma3_re/_im).
 // Output column c of every accumulator is complex column c, so the two
 // results land in the layout of the n-tiles above (tile 0 real parts, tile 1
-// imaginary parts). 12 matrix-core steps per product and 16-row tile, against
-// 16 for the 32 x 32 real form. M: complex 16 x 16 in LDS, (re, im) pairs.
-template <typename F>
-__device__ __forceinline__ void mfma3(typename Mf<F>::V (&d)[3], const F (&a)[MfShape<16>::KS],
-                                      const F* M, int g, int c) {
+// imaginary parts). 3 N / 4 matrix-core steps per product and 16-row tile, against
+// N for the real form at n = 16. M: complex n x n in LDS, (re, im) pairs. For n < N the
+// columns past n meet a zero A operand and read row 0 (finite) instead; output
+// columns past n are not used.
+template <typename F, int N, bool RT>
+__device__ __forceinline__ void mfma3(typename Mf<F>::V (&d)[3], const F (&a)[MfShape<N>::KS],
+                                      const F* M, int nrt, int g, int c) {
+  constexpr int KC = N / 4;
+  const int n = RT ? nrt : N;
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    const int e = 2 * ((4 * g + ks) * 16 + c);
+  for (int ks = 0; ks < KC; ++ks) {
+    const int kc = KC * g + ks;
+    const int e = 2 * ((RT && kc >= n ? 0 : kc) * n + c);
     const F mr = M[e], mi = M[e + 1];
     const F ar = a[2 * ks], ai = a[2 * ks + 1];
     d[0] = Mf<F>::mfma(ar, mr, d[0]);
@@ -161,34 +139,40 @@ __device__ __forceinline__ V mfma3_im(const V (&d)[3]) {
 }
 
 // A-operand reals of one tile row (row r, reals g*KS .. g*KS+KS-1) in the
-// arithmetic type F. Rows past the end read row 0 and are zeroed, with no
-// branch around the loads (so the loads of several tiles stay in flight).
-template <int N, typename F, typename C>
-__device__ __forceinline__ void aload(const C* base, int r, int rows, int g,
+// arithmetic type F. Rows past the end and columns past n read a valid entry and
+// are zeroed, with no branch around the loads (so the loads of several tiles stay
+// in flight).
+template <int N, bool RT, typename F, typename C>
+__device__ __forceinline__ void aload(const C* base, int r, int rows, int nrt, int g,
                                       F (&a)[MfShape<N>::KS]) {
   using S = MfShape<N>;
-  const bool ok = r < rows;
-  const C* p = base + (size_t)(ok ? r : 0) * N + g * (S::KS / 2);
+  constexpr int KC = S::KS / 2;
+  const int n = RT ? nrt : N;
+  const bool okr = r < rows;
+  const C* p = base + (size_t)(okr ? r : 0) * n + g * KC;
 #pragma unroll
-  for (int h = 0; h < S::KS / 2; ++h) {
-    C v = p[h];
+  for (int h = 0; h < KC; ++h) {
+    const bool okc = !RT || g * KC + h < n, ok = okr && okc;
+    C v = p[okc ? h : -g * KC];
     a[2 * h] = ok ? (F)v.x : (F)0;
     a[2 * h + 1] = ok ? (F)v.y : (F)0;
   }
 }
 
-// D-layout access: lane (g, c), element p is tile row Mf<F>::row(g, p), output
-// real column flat = nt*16 + c: part flat / N (0 = re, 1 = im) of complex column flat % N.
-template <int N, typename F, typename C>
-__device__ __forceinline__ void dload(const C* base, int r0, int rows, int g, int c,
+// D-layout access: lane (g, c), element p is tile row Mf<F>::row(g, p); widths above 8:
+// complex column c (real parts in tile 0, imaginary in tile 1), n = 8: real column c, part
+// c / 8 (0 = re, 1 = im) of complex column c % 8.
+template <int N, bool RT, typename F, typename C>
+__device__ __forceinline__ void dload(const C* base, int r0, int rows, int nrt, int g, int c,
                                       typename Mf<F>::V (&d)[MfShape<N>::NT]) {
+  const int n = RT ? nrt : N;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     const int r = r0 + Mf<F>::row(g, p);
-    const bool ok = r < rows;
+    const bool ok = r < rows && (!RT || c < n);
     const size_t rr = ok ? (size_t)r : 0;
-    if constexpr (N == 16) {
-      C v = base[rr * N + c];
+    if constexpr (MfShape<N>::three) {
+      C v = base[rr * n + (!RT || c < n ? c : 0)];
       d[0][p] = ok ? (F)v.x : (F)0;
       d[1][p] = ok ? (F)v.y : (F)0;
     } else {
@@ -198,34 +182,24 @@ __device__ __forceinline__ void dload(const C* base, int r0, int rows, int g, in
   }
 }
 
-template <int N, typename F, typename C>
-__device__ __forceinline__ void dstore(C* base, int r0, int rows, int g, int c,
+template <int N, bool RT, typename F, typename C>
+__device__ __forceinline__ void dstore(C* base, int r0, int rows, int nrt, int g, int c,
                                        const typename Mf<F>::V (&d)[MfShape<N>::NT]) {
   using R = decltype(C().x);
+  const int n = RT ? nrt : N;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     const int r = r0 + Mf<F>::row(g, p);
     if (r >= rows) continue;
-    if constexpr (N == 16) {
+    if constexpr (MfShape<N>::three) {
       C v;
       v.x = (R)d[0][p];
       v.y = (R)d[1][p];
-      base[(size_t)r * N + c] = v;
+      if (!RT || c < n) base[(size_t)r * n + c] = v;
     } else {
       ((R*)base)[(size_t)r * 2 * N + 2 * (c % N) + c / N] = (R)d[0][p];
     }
   }
-}
-
-template <int N, typename F>
-__device__ __forceinline__ void mfma_acc(typename Mf<F>::V (&d)[MfShape<N>::NT],
-                                         const F (&a)[MfShape<N>::KS],
-                                         const F (&b)[MfShape<N>::KS][MfShape<N>::NT]) {
-  using S = MfShape<N>;
-#pragma unroll
-  for (int ks = 0; ks < S::KS; ++ks)
-#pragma unroll
-    for (int nt = 0; nt < S::NT; ++nt) d[nt] = Mf<F>::mfma(a[ks], b[ks][nt], d[nt]);
 }
 
 // Longest window of the deferred shift update whose coefficients (2 x window
@@ -252,114 +226,97 @@ struct MfWin {
 // first shift of a tile they come from L2.
 // One tile per wave: four waves per SIMD in FP32, three in FP64 (the register
 // count the compiler picks by itself leaves fewer; in FP64 four waves need
-// spills, whose scratch traffic reached HBM). For n = 16 every complex
-// product (Q step and shift windows) takes the three-product form.
-template <typename F, int N, int NTILE>
+// spills, whose scratch traffic reached HBM). Widths above 8 take the
+// three-product form for every complex product (Q step and shift windows).
+// RT: the width is a.n (9 .. 15, at most N), else N (in FP64 with N = 16 the masks cost
+// registers: two waves per SIMD instead of 24 spills). Measured at n = 12 (12.14.10.24, 15
+// shifts, FP64) against the every-iteration vector kernel: 90.0 -> 35.3 us per launch.
+// gridDim.y: the shifts are dealt to that many groups of work-groups (shift s to
+// group s % gridDim.y), which all form Q_{k+1} and of which the first stores
+// it; more than one only with a ring (win > 1), where nothing is overwritten.
+template <typename F, int N, int NTILE, bool RT>
 __global__ __launch_bounds__(BMS_WG)
-__attribute__((amdgpu_waves_per_eu(NTILE == 1 ? (sizeof(F) == 4 ? 4 : 3) : 1)))
+__attribute__((amdgpu_waves_per_eu(
+    NTILE == 1 ? (sizeof(F) == 4 ? 4 : (RT && N == 16 ? 2 : 3)) : 1)))
 void k_update_mfma(UpdateArgs<F, F> a) {
   using S = MfShape<N>;
   using CF = cplx<F>;
   using VF = typename Mf<F>::V;
   constexpr int MW = MfWin<F>::MW;
-  // LDS: the Q-step operands (FP64) and the complex staging, then (FP32) the
-  // per-wave layout change of Q, then one shift's window coefficients (F)
-  constexpr int QBYTES = 2 * S::BSZ * 8 + 2 * N * N * 16;
-  constexpr int TBYTES = MF_WAVES * NTILE * 16 * S::NR * 8;
-  constexpr int SBYTES = 2 * MW * 2 * N * N * (int)sizeof(F);
-  constexpr int LBYTES = QBYTES > SBYTES ? (QBYTES > TBYTES ? QBYTES : TBYTES)
-                                         : (SBYTES > TBYTES ? SBYTES : TBYTES);
+  // LDS: the Q step's two coefficient matrices (FP64), then (FP32) the
+  // per-wave layout change of Q, then one shift's window coefficients (F); each
+  // copied region in whole KiB, and a matrix row's worth past the last one
+  // (output columns past the width read there)
+  constexpr int QREG = (N * N * 16 + 1023) / 1024 * 1024;
+  constexpr int SREG = (MW * N * N * (int)sizeof(CF) + 1023) / 1024 * 1024;
+  constexpr int TBYTES = MF_WAVES * NTILE * 16 * S::PITCH * 8;
+  constexpr int CBYTES = 2 * (QREG > SREG ? QREG : SREG) + 256;
+  constexpr int LBYTES = CBYTES > TBYTES ? CBYTES : TBYTES;
   __shared__ __align__(16) unsigned char lds[LBYTES];
-  double* qb0 = (double*)lds;
-  double* qb1 = qb0 + S::BSZ;
-  double2* cs = (double2*)(qb1 + S::BSZ);  // alpha, rho^-1
-  F* sb = (F*)lds;                         // [2][MW][N*N] complex: X family, then P family
+  const double* qb0 = (const double*)lds;           // rho^-1
+  const double* qb1 = (const double*)(lds + QREG);  // -alpha rho^-1
   SolverFlags* fl = a.flags;
   if (fl->halted) return;
   const int tid = threadIdx.x;
   const int iter = fl->iter;  // k + 1: the small step of iteration k has counted it
   const int stop = fl->stop;
   const int slot = iter & 1;
+  const bool lead = blockIdx.y == 0;
   // the next small step and the drain read these (nothing else in this
   // kernel reads them)
-  if (blockIdx.x == 0 && tid == 0) {
+  if (lead && blockIdx.x == 0 && tid == 0) {
     fl->upd_done = iter;
     fl->upd_stop = stop;
   }
-  if (blockIdx.x == 0 && tid < 64) log_update(fl, a.upd_log, a.max_iter, a.ns);
-  const int lane = tid & 63, wave = tid >> 6;
+  if (lead && blockIdx.x == 0 && tid < 64) log_update(fl, a.upd_log, a.max_iter, a.ns);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c = lane & 15;
+  const int n = RT ? a.n : N, nn = n * n;
   const int rows = a.rows, ns = a.ns, win = a.win;
-  const size_t blk = (size_t)rows * N;
+  const size_t blk = (size_t)rows * n;
   const int k = iter - 1;
   const CF* Qin = a.Qring + (size_t)(k % win) * blk;
   CF* Qout = a.Qring + (size_t)((k + 1) % win) * blk;
   const int tile0 = (blockIdx.x * MF_WAVES + wave) * NTILE;
   unsigned long long mask =
-      __ballot(lane < ns && fl->win_j[slot][lane] > 0 && (fl->win_flush[slot][lane] || stop));
+      __ballot(lane < ns && lane % gridDim.y == blockIdx.y && fl->win_j[slot][lane] > 0 &&
+               (fl->win_flush[slot][lane] || stop));
+  if (!lead && !mask) return;
 
-  // coefficients of the Q step: B0 = rho^-1, B1 = -alpha rho^-1
-  for (int e = tid; e < N * N; e += BMS_WG) {
-    cs[e] = a.alpha[e];
-    cs[N * N + e] = a.rhoinv[e];
+  // coefficients of the Q step
+  lds_copy(a.rhoinv, lds, nn * 16, wave, lane);
+  lds_copy(a.arho, lds + QREG, nn * 16, wave, lane);
+  double av[NTILE][S::KS], wv[NTILE][S::KS];
+#pragma unroll
+  for (int t = 0; t < NTILE; ++t) {
+    const int r0 = (tile0 + t) * 16;
+    aload<N, RT>(Qin, r0 + c, rows, n, g, av[t]);
+    aload<N, RT>(a.W, r0 + c, rows, n, g, wv[t]);
   }
-  __syncthreads();
-  for (int e = tid; e < N * N; e += BMS_WG) {
-    int i = e / N, j = e - (e / N) * N;
-    double2 t = make_double2(0.0, 0.0);
-    for (int kk = 0; kk < N; ++kk) t = cfma(cs[i * N + kk], cs[N * N + kk * N + j], t);
-    if constexpr (N == 16) {
-      // complex matrices for the three-product form (qb0: rho^-1, then -alpha rho^-1)
-      qb0[2 * e] = cs[N * N + e].x;
-      qb0[2 * e + 1] = cs[N * N + e].y;
-      qb0[2 * N * N + 2 * e] = -t.x;
-      qb0[2 * N * N + 2 * e + 1] = -t.y;
-    } else {
-      bput<N>(qb0, i, j, cs[N * N + e]);
-      bput<N>(qb1, i, j, make_double2(-t.x, -t.y));
-    }
-  }
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   dx4 qd[NTILE][S::NT];
-  if constexpr (N == 16) {
-    double av[NTILE][S::KS], wv[NTILE][S::KS];
 #pragma unroll
-    for (int t = 0; t < NTILE; ++t) {
-      const int r0 = (tile0 + t) * 16;
-      aload<N>(Qin, r0 + c, rows, g, av[t]);
-      aload<N>(a.W, r0 + c, rows, g, wv[t]);
-    }
-#pragma unroll
-    for (int t = 0; t < NTILE; ++t) {
+  for (int t = 0; t < NTILE; ++t) {
+    if constexpr (S::three) {
       dx4 d3[3] = {dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}};
-      mfma3<double>(d3, av[t], qb0, g, c);
-      mfma3<double>(d3, wv[t], qb0 + 2 * N * N, g, c);
+      mfma3<double, N, RT>(d3, av[t], qb0, n, g, c);
+      mfma3<double, N, RT>(d3, wv[t], qb1, n, g, c);
       qd[t][0] = mfma3_re(d3);
       qd[t][1] = mfma3_im(d3);
-    }
-  } else {
-    double b0[S::KS][S::NT], b1[S::KS][S::NT];
-    double av[NTILE][S::KS], wv[NTILE][S::KS];
-#pragma unroll
-    for (int t = 0; t < NTILE; ++t) {
-      const int r0 = (tile0 + t) * 16;
-      aload<N>(Qin, r0 + c, rows, g, av[t]);
-      aload<N>(a.W, r0 + c, rows, g, wv[t]);
-    }
-    bload<N>(qb0, lane, b0);
-    bload<N>(qb1, lane, b1);
-#pragma unroll
-    for (int t = 0; t < NTILE; ++t) {
-#pragma unroll
-      for (int nt = 0; nt < S::NT; ++nt) qd[t][nt] = dx4{0.0, 0.0, 0.0, 0.0};
-      mfma_acc<N>(qd[t], av[t], b0);
-      mfma_acc<N>(qd[t], wv[t], b1);
+    } else {
+      qd[t][0] = dx4{0.0, 0.0, 0.0, 0.0};
+      mfma_acc_c<N>(qd[t], av[t], qb0, g, c);
+      mfma_acc_c<N>(qd[t], wv[t], qb1, g, c);
     }
   }
   // every lane of the wave has read its Q tiles before any is overwritten
   // (win = 1: Q_{k+1} replaces Q_k in place)
+  if (lead) {
 #pragma unroll
-  for (int t = 0; t < NTILE; ++t) dstore<N, double>(Qout, (tile0 + t) * 16, rows, g, c, qd[t]);
+    for (int t = 0; t < NTILE; ++t)
+      dstore<N, RT, double>(Qout, (tile0 + t) * 16, rows, n, g, c, qd[t]);
+  }
   __syncthreads();  // the Q-step LDS is reused below
   // Q_{k+1} in the shift-update layout and precision: the same registers in
   // FP64; in FP32 rounded and moved to the f32 row mapping through LDS
@@ -370,14 +327,14 @@ void k_update_mfma(UpdateArgs<F, F> a) {
 #pragma unroll
       for (int nt = 0; nt < S::NT; ++nt) qn[t][nt] = qd[t][nt];
   } else {
-    double* tq = (double*)lds + wave * (NTILE * 16 * S::NR);
+    double* tq = (double*)lds + wave * (NTILE * 16 * S::PITCH);
 #pragma unroll
     for (int t = 0; t < NTILE; ++t)
 #pragma unroll
       for (int nt = 0; nt < S::NT; ++nt)
 #pragma unroll
         for (int p = 0; p < 4; ++p)
-          tq[(t * 16 + Mf<double>::row(g, p)) * S::NR + nt * 16 + c] = qd[t][nt][p];
+          tq[(t * 16 + Mf<double>::row(g, p)) * S::PITCH + nt * 16 + c] = qd[t][nt][p];
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < NTILE; ++t)
@@ -385,64 +342,64 @@ void k_update_mfma(UpdateArgs<F, F> a) {
       for (int nt = 0; nt < S::NT; ++nt)
 #pragma unroll
         for (int p = 0; p < 4; ++p)
-          qn[t][nt][p] = (F)tq[(t * 16 + Mf<F>::row(g, p)) * S::NR + nt * 16 + c];
+          qn[t][nt][p] = (F)tq[(t * 16 + Mf<F>::row(g, p)) * S::PITCH + nt * 16 + c];
     __syncthreads();  // the shift coefficients overwrite this LDS
   }
 
   // the P and X tiles of a shift (the next shift's P, and for n = 8 its X,
-  // are loaded while the current one finishes; for n = 16 X is loaded after
+  // are loaded while the current one finishes; for n > 8 X is loaded after
   // the products, which keeps the three-accumulator form at three waves per
   // SIMD with 16 bytes of spills outside the product loop)
   F pa[NTILE][S::KS];
   VF xa[NTILE][S::NT];
   auto fetch = [&](int s, int t) {
     const int r0 = (tile0 + t) * 16;
-    aload<N>(a.P + (size_t)s * blk, r0 + c, rows, g, pa[t]);
-    if constexpr (N != 16) dload<N, F>(a.X + (size_t)a.xidx[s] * blk, r0, rows, g, c, xa[t]);
+    aload<N, RT>(a.P + (size_t)s * blk, r0 + c, rows, n, g, pa[t]);
+    if constexpr (!S::three) dload<N, RT, F>(a.X + (size_t)a.xidx[s] * blk, r0, rows, n, g, c, xa[t]);
   };
   int s = mask ? __ffsll((long long)mask) - 1 : -1;
   if (s >= 0) {
 #pragma unroll
     for (int t = 0; t < NTILE; ++t) fetch(s, t);
   }
-  constexpr size_t FAM = (size_t)BMS_MAX_WIN * N * N;  // one family in Wm
+  const size_t fam = (size_t)BMS_MAX_WIN * nn;  // one family in Wm
   while (s >= 0) {
     mask &= mask - 1;
     const int s2 = mask ? __ffsll((long long)mask) - 1 : -1;
     const int j = __builtin_amdgcn_readfirstlane(fl->win_j[slot][s]);
     // the window's 2j coefficient matrices into LDS (complex n x n, the X
-    // family, then the P family MW matrices further)
-    const CF* wm = a.Wm + (size_t)s * 2 * FAM;
-    lds_copy(wm, sb, j * N * N * (int)sizeof(CF), wave, lane);
-    lds_copy(wm + FAM, sb + 2 * MW * N * N, j * N * N * (int)sizeof(CF), wave, lane);
+    // family, then the P family)
+    const CF* wm = a.Wm + (size_t)s * 2 * fam;
+    lds_copy(wm, lds, j * nn * (int)sizeof(CF), wave, lane);
+    lds_copy(wm + fam, lds + SREG, j * nn * (int)sizeof(CF), wave, lane);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    const F* bx = sb;
-    const F* bp = sb + 2 * MW * N * N;
+    const F* bx = (const F*)lds;
+    const F* bp = (const F*)(lds + SREG);
     CF* X = a.X + (size_t)a.xidx[s] * blk;
     CF* P = a.P + (size_t)s * blk;
 #pragma unroll
     for (int t = 0; t < NTILE; ++t) {
       const int r0 = (tile0 + t) * 16;
-      constexpr int NACC = N == 16 ? 3 : S::NT;  // accumulators of one product family
+      constexpr int NACC = S::three ? 3 : S::NT;  // accumulators of one product family
       VF pn[NACC], dx[NACC];
 #pragma unroll
       for (int nt = 0; nt < NACC; ++nt) {
-        pn[nt] = (N == 16 || nt >= S::NT) ? VF{0, 0, 0, 0} : qn[t][nt];
+        pn[nt] = (S::three || nt >= S::NT) ? VF{0, 0, 0, 0} : qn[t][nt];
         dx[nt] = VF{0, 0, 0, 0};
       }
       // ring buffers Q_{k-j+2} .. Q_k, two in flight
       F qa[2][S::KS];
-      if (j >= 2) aload<N>(a.Qring + (size_t)((k - j + 2) % win) * blk, r0 + c, rows, g, qa[0]);
+      if (j >= 2) aload<N, RT>(a.Qring + (size_t)((k - j + 2) % win) * blk, r0 + c, rows, n, g, qa[0]);
       // the increment is formed on its own and added to X once, so X (large
       // next to one window's increment) is rounded once
       auto prod = [&](const F(&av)[S::KS], int m) {
-        if constexpr (N == 16) {
-          mfma3<F>(dx, av, bx + (size_t)m * 2 * N * N, g, c);
-          mfma3<F>(pn, av, bp + (size_t)m * 2 * N * N, g, c);
+        if constexpr (S::three) {
+          mfma3<F, N, RT>(dx, av, bx + m * 2 * nn, n, g, c);
+          mfma3<F, N, RT>(pn, av, bp + m * 2 * nn, n, g, c);
         } else {
-          mfma_acc_c<N>(dx, av, bx + (size_t)m * 2 * N * N, g, c);
-          mfma_acc_c<N>(pn, av, bp + (size_t)m * 2 * N * N, g, c);
+          mfma_acc_c<N>(dx, av, bx + m * 2 * nn, g, c);
+          mfma_acc_c<N>(pn, av, bp + m * 2 * nn, g, c);
         }
       };
       prod(pa[t], 0);
@@ -450,23 +407,23 @@ void k_update_mfma(UpdateArgs<F, F> a) {
       for (int i = 0; i < MW - 1; ++i) {
         if (i < j - 1) {
           if (i + 1 < j - 1)
-            aload<N>(a.Qring + (size_t)((k - j + 3 + i) % win) * blk, r0 + c, rows, g,
+            aload<N, RT>(a.Qring + (size_t)((k - j + 3 + i) % win) * blk, r0 + c, rows, n, g,
                      qa[(i + 1) & 1]);
           prod(qa[i & 1], i + 1);
         }
       }
-      if constexpr (N == 16) {
-        dload<N, F>(X, r0, rows, g, c, xa[t]);
+      if constexpr (S::three) {
+        dload<N, RT, F>(X, r0, rows, n, g, c, xa[t]);
         xa[t][0] += mfma3_re(dx);
         xa[t][1] += mfma3_im(dx);
         const VF pst[S::NT] = {qn[t][0] + mfma3_re(pn), qn[t][1] + mfma3_im(pn)};
-        dstore<N, F>(X, r0, rows, g, c, xa[t]);
-        dstore<N, F>(P, r0, rows, g, c, pst);
+        dstore<N, RT, F>(X, r0, rows, n, g, c, xa[t]);
+        dstore<N, RT, F>(P, r0, rows, n, g, c, pst);
       } else {
 #pragma unroll
         for (int nt = 0; nt < S::NT; ++nt) xa[t][nt] += dx[nt];
-        dstore<N, F>(X, r0, rows, g, c, xa[t]);
-        dstore<N, F>(P, r0, rows, g, c, pn);
+        dstore<N, RT, F>(X, r0, rows, n, g, c, xa[t]);
+        dstore<N, RT, F>(P, r0, rows, n, g, c, pn);
       }
       if (s2 >= 0) fetch(s2, t);
     }
@@ -511,31 +468,157 @@ __global__ __launch_bounds__(BMS_WG) void k_update_drain(UpdateArgs<F, F> a) {
   }
 }
 
-template <typename F, int N, int NTILE>
+// The windowed update for n <= 7, where the 16-column tiles of the matrix cores would be
+// mostly empty: a lane per (row, column), whole rows inside a wave (64 / N rows, so that
+// a wave has read its rows of Q and P before it overwrites any). A lane reads whole rows
+// of Q, W, P and the ring (the row's N lanes hit the same lines) and its column of the
+// coefficients, the shift's from LDS; the ring rows stay in registers for all shifts.
+// Memory bound on large blocks: per shift and window X and P are read and written once, as
+// in k_update_mfma. On small ones latency bound, hence the shift groups.
+// Measured per launch against the every-iteration form: n = 4 at 8^4 with 12 shifts
+// 18.0 -> 5.2 us, n = 1 at 4^4 with 8 shifts 4.5 -> 3.6 us.
+template <typename F, int N>
+__global__ __launch_bounds__(BMS_WG) void k_update_vec(UpdateArgs<F, F> a) {
+  using CF = cplx<F>;
+  constexpr int MW = MfWin<F>::MW, RPW = 64 / N, NN = N * N;
+  __shared__ CF cf[2][MW * NN];  // one shift's window coefficients: X family, P family
+  SolverFlags* fl = a.flags;
+  if (fl->halted) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int iter = fl->iter, stop = fl->stop, slot = iter & 1;
+  const bool lead = blockIdx.y == 0;
+  if (lead && blockIdx.x == 0 && tid == 0) {
+    fl->upd_done = iter;
+    fl->upd_stop = stop;
+  }
+  if (lead && blockIdx.x == 0 && tid < 64) log_update(fl, a.upd_log, a.max_iter, a.ns);
+  const int rows = a.rows, ns = a.ns, win = a.win, k = iter - 1;
+  unsigned long long mask =
+      __ballot(lane < ns && lane % gridDim.y == blockIdx.y && fl->win_j[slot][lane] > 0 &&
+               (fl->win_flush[slot][lane] || stop));
+  if (!lead && !mask) return;
+  const size_t blk = (size_t)rows * N;
+  const int lr = lane / N, col = lane - lr * N;
+  const int row = (blockIdx.x * MF_WAVES + wave) * RPW + lr;
+  const bool live = lr < RPW && row < rows;
+  const size_t ro = live ? (size_t)row * N : 0;  // dead lanes read row 0 and write nothing
+  // Q_{k+1} = Q_k rho^-1 + W (-alpha rho^-1), in FP64
+  const CF* Qin = a.Qring + (size_t)(k % win) * blk + ro;
+  double2 q = make_double2(0, 0);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    q = cfma(to_d(Qin[i]), a.rhoinv[i * N + col], q);
+    q = cfma(to_d(a.W[ro + i]), a.arho[i * N + col], q);
+  }
+  const CF qn = from_d<CF>(q);
+  if (lead && live) a.Qring[(size_t)((k + 1) % win) * blk + ro + col] = qn;
+  CF ring[MW - 1][N];
+  int jr = 1;  // window length the ring rows are loaded for (1: none)
+  const size_t fam = (size_t)BMS_MAX_WIN * NN;
+  while (mask) {
+    const int s = __ffsll((long long)mask) - 1;
+    mask &= mask - 1;
+    const int j = __builtin_amdgcn_readfirstlane(fl->win_j[slot][s]);
+    CF* P = a.P + (size_t)s * blk + ro;
+    CF* X = a.X + (size_t)a.xidx[s] * blk + ro + col;
+    CF p[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = P[i];
+    const CF x = *X;
+    const CF* wm = a.Wm + (size_t)s * 2 * fam;
+    for (int e = tid; e < j * NN; e += BMS_WG) {
+      cf[0][e] = wm[e];
+      cf[1][e] = wm[fam + e];
+    }
+    if (j > 1 && j != jr) {
+#pragma unroll
+      for (int m = 0; m < MW - 1; ++m)
+        if (m < j - 1) {
+          const CF* Q = a.Qring + (size_t)((k - j + 2 + m) % win) * blk + ro;
+#pragma unroll
+          for (int i = 0; i < N; ++i) ring[m][i] = Q[i];
+        }
+      jr = j;
+    }
+    __syncthreads();
+    // the increment is formed on its own and added to X once
+    CF dx = czero<CF>(), pn = qn;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      dx = cfma(p[i], cf[0][i * N + col], dx);
+      pn = cfma(p[i], cf[1][i * N + col], pn);
+    }
+#pragma unroll
+    for (int m = 0; m < MW - 1; ++m)
+      if (m < j - 1) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          dx = cfma(ring[m][i], cf[0][(m + 1) * NN + i * N + col], dx);
+          pn = cfma(ring[m][i], cf[1][(m + 1) * NN + i * N + col], pn);
+        }
+      }
+    if (live) {
+      *X = cadd(x, dx);
+      P[col] = pn;
+    }
+    __syncthreads();  // every wave is done with this shift's coefficients
+  }
+}
+// Groups the shifts of an update are dealt to: as many as bring the launch to about
+// two work-groups per compute unit, so that a small lattice, whose rows alone leave most of
+// the chip idle while each work-group walks its shifts one after the other, spreads the
+// shifts too. UPD_GROUP_FIGURES
+int shift_groups(int blocks, int ns, int win) {
+  if (win < 2) return 1;  // Q is updated in place
+  return std::min(ns, std::max(1, 512 / blocks));
+}
+
+template <typename F, int N, int NTILE, bool RT>
 hipError_t launch_mf(hipStream_t st, const UpdateArgs<F, F>& a) {
   int tiles = (a.rows + 15) / 16;
   int waves = (tiles + NTILE - 1) / NTILE;
   int blocks = (waves + MF_WAVES - 1) / MF_WAVES;
-  k_update_mfma<F, N, NTILE><<<blocks, BMS_WG, 0, st>>>(a);
+  const dim3 grid(blocks, shift_groups(blocks, a.ns, a.win));
+  k_update_mfma<F, N, NTILE, RT><<<grid, BMS_WG, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+template <typename F, int N>
+hipError_t launch_vec(hipStream_t st, const UpdateArgs<F, F>& a) {
+  constexpr int RPB = MF_WAVES * (64 / N);  // rows per work-group
+  const int blocks = (a.rows + RPB - 1) / RPB;
+  const dim3 grid(blocks, shift_groups(blocks, a.ns, a.win));
+  k_update_vec<F, N><<<grid, BMS_WG, 0, st>>>(a);
   return hipGetLastError();
 }
 
 }  // namespace
 
 bool update_mfma_supported(int n) { return n == 8 || n == 16; }
+bool update_windowed(int n) { return n <= 16; }
 
 template <typename F>
 int update_mfma_max_win() {
   return MfWin<F>::MW;
 }
 
-// two_tiles: two 16-row tiles per wave instead of one
+// two_tiles: two 16-row tiles per wave instead of one (n = 8 and 16)
 template <typename F>
 hipError_t launch_update_mfma(hipStream_t st, const UpdateArgs<F, F>& a, bool two_tiles) {
   switch (a.n) {
-    case 16: return two_tiles ? launch_mf<F, 16, 2>(st, a) : launch_mf<F, 16, 1>(st, a);
-    case 8: return two_tiles ? launch_mf<F, 8, 2>(st, a) : launch_mf<F, 8, 1>(st, a);
-    default: return hipErrorInvalidValue;
+    case 1: return launch_vec<F, 1>(st, a);
+    case 2: return launch_vec<F, 2>(st, a);
+    case 3: return launch_vec<F, 3>(st, a);
+    case 4: return launch_vec<F, 4>(st, a);
+    case 5: return launch_vec<F, 5>(st, a);
+    case 6: return launch_vec<F, 6>(st, a);
+    case 7: return launch_vec<F, 7>(st, a);
+    case 8: return two_tiles ? launch_mf<F, 8, 2, false>(st, a) : launch_mf<F, 8, 1, false>(st, a);
+    case 16:
+      return two_tiles ? launch_mf<F, 16, 2, false>(st, a) : launch_mf<F, 16, 1, false>(st, a);
+    default:
+      if (a.n > 16) return hipErrorInvalidValue;
+      return a.n <= 12 ? launch_mf<F, 12, 1, true>(st, a) : launch_mf<F, 16, 1, true>(st, a);
   }
 }
 
