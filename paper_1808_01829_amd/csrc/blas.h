@@ -135,6 +135,9 @@ struct SmallParams {
   double tol, freeze_tol, breakdown_tol;
   double sigma[BMS_MAX_SHIFTS];  // sorted shifts
   int win;  // window of the shifts s >= 1 (matrix-core update; 1 = every iteration)
+  // n <= 16: whether the fallback kernels (explicit V^H V, k_small_rho_explicit) follow in
+  // every iteration (1), or the iteration pauses when it needs them (0)
+  int inline_explicit;
 };
 
 // initial QR of B: from G = B^H B, delta_0 = chol(G)^H, out Rinv = delta_0^-1;
@@ -148,10 +151,15 @@ hipError_t launch_small_init_pass2(hipStream_t st, const SmallParams& p, SmallSt
 hipError_t launch_small_reliable(hipStream_t st, const SmallParams& p, SmallState s,
                                  SolverFlags* fl, const double2* Gin, double2* Rinv_out);
 // Wm: the window coefficients of every shift in the block precision, for the
-// matrix-core update ([ns][2][BMS_MAX_WIN][n*n], the layout of SmallState::wst)
+// matrix-core update ([ns][2][BMS_MAX_WIN][n*n], the layout of SmallState::wst).
+// part, nparts: the Grams' partials, summed by every block of the kernel (small_sums_grams),
+// or nparts = 0: the Grams are in SmallState::G4
 template <typename T>
 hipError_t launch_small_iter(hipStream_t st, const SmallParams& p, SmallState s, SolverFlags* fl,
-                             cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm);
+                             cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm, const double2* part,
+                             int nparts);
+// a paused iteration goes on (flags->stop = 2 -> 0)
+hipError_t launch_resume(hipStream_t st, SolverFlags* fl);
 template <typename T>
 hipError_t launch_small_rho_explicit(hipStream_t st, const SmallParams& p, SmallState s,
                                      SolverFlags* fl, cplx<T>* Mp, cplx<T>* Wm);
@@ -159,7 +167,15 @@ hipError_t launch_small_rho_explicit(hipStream_t st, const SmallParams& p, Small
 __host__ __device__ constexpr bool small_wave_supported(int n) { return n <= 16; }
 template <typename T>
 hipError_t launch_small_iter_w(hipStream_t st, const SmallParams& p, SmallState s, SolverFlags* fl,
-                               cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm);
+                               cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm, const double2* part,
+                               int nparts);
+// Whether the n x n step itself adds the Grams' partials instead of a kernel before it:
+// at most 64 loads a thread, so that the extra loads (every block repeats them) stay below
+// the launch they replace (2.3 to 4 us on the lattices this takes; with the fallback kernels
+// left out an 8^4, n = 4 iteration went from 42 to 37 us).
+constexpr bool small_sums_grams(int n, int nparts) {
+  return small_wave_supported(n) && nparts * 4 * n * n <= 64 * BMS_WG;
+}
 template <typename T>
 hipError_t launch_small_rho_explicit_w(hipStream_t st, const SmallParams& p, SmallState s,
                                        SolverFlags* fl, cplx<T>* Mp, cplx<T>* Wm);
@@ -168,9 +184,10 @@ hipError_t launch_small_rho_explicit_w(hipStream_t st, const SmallParams& p, Sma
 // rows staged through LDS with 1, 2 or 4 chunks in flight (n = 8, 16; other n
 // take the vector kernel). nb blocks at most (the size of partials); given the
 // compute-unit count, the matrix-core kernels launch one round of resident
-// blocks. A second kernel sums the blocks' partials into G4.
+// blocks. A second kernel sums the blocks' partials into G4, unless
+// small_sums_grams(n, their number): *nparts is that number then, else 0.
 template <typename T>
 hipError_t launch_gram4(hipStream_t st, int rows, int n, const void* P, const void* Q,
                         const void* W, double2* G4, double2* partials, int nb,
-                        const int* skip, int variant = -1, int num_cu = 0);
+                        const int* skip, int variant, int num_cu, int* nparts);
 bool gram4_mfma_supported(int n);

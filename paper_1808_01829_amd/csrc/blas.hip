@@ -1107,13 +1107,22 @@ bool gram4_mfma_supported(int n) { return n == 8 || n == 16; }
 template <typename T>
 hipError_t launch_gram4(hipStream_t st, int rows, int n, const void* P, const void* Q,
                         const void* W, double2* G4, double2* partials, int nb,
-                        const int* skip, int variant, int num_cu) {
+                        const int* skip, int variant, int num_cu, int* nparts) {
   int per = rows_per_block(rows, nb);
+  *nparts = 0;
   const cplx<T>* p = (const cplx<T>*)P;
   const cplx<T>* q = (const cplx<T>*)Q;
   const cplx<T>* w = (const cplx<T>*)W;
   const int P4 = 4 * n * n;  // the four Grams' entries per partial
   int grid = nb;
+  auto finish = [&]() -> hipError_t {
+    HIP_RET(hipGetLastError());
+    if (small_sums_grams(n, grid)) {
+      *nparts = grid;
+      return hipSuccess;
+    }
+    return launch_sum_partials(st, partials, grid, P4, G4, skip, nullptr);
+  };
   if (variant >= 3 && gram4_mfma_supported(n)) {
     // chunks in flight per block: variant 3 one, 4 two, 5 four
     // one round of resident blocks: the deeper rings need more registers and
@@ -1133,8 +1142,7 @@ hipError_t launch_gram4(hipStream_t st, int rows, int n, const void* P, const vo
       if (depth == 1) GL(8, 1); else if (depth == 2) GL(8, 2); else GL(8, 4);
     }
 #undef GL
-    HIP_RET(hipGetLastError());
-    return launch_sum_partials(st, partials, grid, P4, G4, skip, nullptr);
+    return finish();
   }
   if ((variant < 0 || variant == 1 || variant == 2) && gram4_mfma_supported(n)) {
     // steps in flight per wave: variant 1 four, 2 (and the default) eight
@@ -1152,8 +1160,7 @@ hipError_t launch_gram4(hipStream_t st, int rows, int n, const void* P, const vo
       if (variant == 1) GR_(8, 4); else GR_(8, 8);
     }
 #undef GR_
-    HIP_RET(hipGetLastError());
-    return launch_sum_partials(st, partials, grid, P4, G4, skip, nullptr);
+    return finish();
   }
   if (!gram4_fits(n)) {  // four pairwise passes
     const cplx<T>* xs[4] = {p, q, w, q};
@@ -1172,15 +1179,14 @@ hipError_t launch_gram4(hipStream_t st, int rows, int n, const void* P, const vo
     default:
       k_gram4<T, 1><<<nb, BMS_WG, 0, st>>>(rows, n, per, p, q, w, partials, skip);
   }
-  HIP_RET(hipGetLastError());
-  return launch_sum_partials(st, partials, nb, P4, G4, skip, nullptr);
+  return finish();
 }
 template hipError_t launch_gram4<double>(hipStream_t, int, int, const void*, const void*,
                                          const void*, double2*, double2*, int, const int*, int,
-                                         int);
+                                         int, int*);
 template hipError_t launch_gram4<float>(hipStream_t, int, int, const void*, const void*,
                                         const void*, double2*, double2*, int, const int*, int,
-                                        int);
+                                        int, int*);
 
 // ---- fused update, specialised on the block width ---------------------------
 // Same arithmetic as k_update. Thread (row lr, column j) of each of NCH chunks

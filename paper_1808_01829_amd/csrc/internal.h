@@ -46,8 +46,9 @@ enum Slot {
 // Device-side solver control block (all written by kernels, read by the host
 // between graph chunks).
 struct SolverFlags {
-  int stop;       // iteration over: converged, max_iter or error (skip flag)
-  int halted;     // the update kernel skips too (set one step after stop)
+  int stop;       // iteration over: converged, max_iter or error (skip flag); 2: paused,
+                  // the host finishes the iteration with the explicit Gram
+  int halted;     // the update kernel skips too (set one step after stop, or with a pause)
   int error;      // 0 or a BMS_E* code raised on the device
   int iter;       // completed block iterations
   int need_explicit;  // V^H V must come from the explicit Gram this iteration

@@ -632,7 +632,16 @@ __global__ __launch_bounds__(BMS_WG) void k_small_rho_explicit(SmallParams p, Sm
   rho_part<T>(p, s, fl, Mp, Wm, R, Gk, T0, T1, T2, q, cur);
 }
 
+__global__ void k_resume(SolverFlags* fl) {
+  if (fl->stop == 2) fl->stop = fl->halted = 0;
+}
+
 }  // namespace
+
+hipError_t launch_resume(hipStream_t st, SolverFlags* fl) {
+  k_resume<<<1, 1, 0, st>>>(fl);
+  return hipGetLastError();
+}
 
 hipError_t launch_small_init(hipStream_t st, const SmallParams& p, SmallState s, SolverFlags* fl,
                              const double2* Gb_in, double2* Rinv_out) {
@@ -654,8 +663,10 @@ hipError_t launch_small_reliable(hipStream_t st, const SmallParams& p, SmallStat
 
 template <typename T>
 hipError_t launch_small_iter(hipStream_t st, const SmallParams& p, SmallState s, SolverFlags* fl,
-                             cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm) {
-  if (small_wave_supported(p.n)) return launch_small_iter_w<T>(st, p, s, fl, Mx, Mp, Wm);
+                             cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm, const double2* part,
+                             int nparts) {
+  if (small_wave_supported(p.n))
+    return launch_small_iter_w<T>(st, p, s, fl, Mx, Mp, Wm, part, nparts);
   k_small_iter<T><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm);
   return hipGetLastError();
 }
@@ -670,7 +681,7 @@ hipError_t launch_small_rho_explicit(hipStream_t st, const SmallParams& p, Small
 
 #define INST_SMALL(T, C)                                                                    \
   template hipError_t launch_small_iter<T>(hipStream_t, const SmallParams&, SmallState,     \
-                                           SolverFlags*, C*, C*, C*);                       \
+                                           SolverFlags*, C*, C*, C*, const double2*, int);  \
   template hipError_t launch_small_rho_explicit<T>(hipStream_t, const SmallParams&,         \
                                                    SmallState, SolverFlags*, C*, C*);
 INST_SMALL(double, double2)

@@ -243,20 +243,30 @@ struct SmallLds {
   int st1, st2, st3;
 };
 
-// One block's arrival: the last one ends the solve when every shift met tol
-// (or raised an error) and advances the iteration counter. Everything the
-// last block needs is in the counter (arrivals, shifts done, errors), so no
-// fence orders the blocks' other writes; the next kernel sees them all.
+// One block's arrival. kind: 0 its shift is above tol, 1 it met tol (or is frozen), 2 it
+// raised an error, 3 it waits for the explicit Gram. The last block ends the solve when
+// every shift met tol (or raised an error) and advances the iteration counter, or, if
+// blocks wait, pauses the iteration (raises need_explicit; with no fallback kernels
+// behind it, stop and halted too). Only the last arrival may write those flags: every block
+// has read them by then. Everything it needs is in the counter (arrivals, shifts done,
+// errors, waiting blocks in 8 bits each), so no fence orders the blocks' other
+// writes; the next kernel sees them all.
 __device__ __forceinline__ void arrive(const SmallParams& p, const SmallState& s, SolverFlags* fl,
-                                       bool done, bool err) {
-  const int add = 1 + (done ? 1 << 8 : 0) + (err ? 1 << 16 : 0);
+                                       int kind) {
+  const int add = kind == 0 ? 1 : (kind == 1 ? 1 + (1 << 8) : (kind == 2 ? 1 + (1 << 16) : 1 << 24));
   const int v = atomicAdd(s.counter, add) + add;
-  if ((v & 0xff) == p.ns) {
-    if (((v >> 8) & 0xff) == p.ns || (v >> 16)) fl->stop = 1;
-    fl->need_explicit = 0;
-    fl->iter = fl->iter + 1;
-    atomicExch(s.counter, 0);
+  const int waiting = v >> 24;
+  if ((v & 0xff) + waiting != p.ns) return;
+  if (waiting) {
+    fl->need_explicit = 1;
+    if (!p.inline_explicit) fl->stop = fl->halted = 2;
+    atomicSub(s.counter, waiting << 24);
+    return;
   }
+  if (((v >> 8) & 0xff) == p.ns || ((v >> 16) & 0xff)) fl->stop = 1;
+  fl->need_explicit = 0;
+  fl->iter = fl->iter + 1;
+  atomicExch(s.counter, 0);
 }
 
 __device__ __forceinline__ void set_error(SolverFlags* fl, int code) {
@@ -314,7 +324,7 @@ __device__ __forceinline__ void rho_part_w(const SmallParams& p, const SmallStat
       }
       fl->win_j[ws][q] = j0 + 1;
       fl->win_flush[ws][q] = (j0 + 1 >= (q == 0 ? 1 : p.win)) || conv;
-      arrive(p, s, fl, r < p.tol, r >= 1e300);
+      arrive(p, s, fl, r >= 1e300 ? 2 : (r < p.tol ? 1 : 0));
     }
   } else if (wave == 2) {
     wm_store(Mp + (size_t)q * nn, n, n, g, c, mp);
@@ -375,17 +385,23 @@ __device__ __forceinline__ void put_rho(SmallLds& l, int n, int g, int c, int q,
 // the state are those of k_small_iter). Blocks read the flags of one launch while
 // another block may raise an error (stop): the waves of a block can then disagree and
 // some leave early, which only leaves values behind that a stopped solve never reads.
-template <typename T, int NE>
+// SUM: the Grams come as nparts partials, added here in a fixed order (the same in every
+// block).
+template <typename T, int NE, bool SUM>
 __global__ __launch_bounds__(BMS_WG) void k_small_iter_w(SmallParams p, SmallState s,
                                                          SolverFlags* fl, cplx<T>* Mx,
-                                                         cplx<T>* Mp, cplx<T>* Wm) {
+                                                         cplx<T>* Mp, cplx<T>* Wm,
+                                                         const double2* __restrict__ part,
+                                                         int nparts) {
   __shared__ SmallLds l;
+  __shared__ double2 gs[SUM ? (64 * NE * NE > BMS_WG ? 64 * NE * NE : BMS_WG) : 1];
   const int n = p.n, nn = n * n, q = blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, c = lane & 15;
-  if (fl->stop || fl->iter >= p.max_iter) {
-    if (q == 0 && threadIdx.x == 0) {
+  const int stop = fl->stop;
+  if (stop || fl->iter >= p.max_iter) {
+    if (q == 0 && threadIdx.x == 0 && stop != 2) {
       fl->stop = 1;
       fl->halted = 1;
     }
@@ -398,16 +414,37 @@ __global__ __launch_bounds__(BMS_WG) void k_small_iter_w(SmallParams p, SmallSta
       fl->active[q] = 0;
       fl->win_j[prev][q] = 0;
       fl->win_flush[prev][q] = 1;
-      arrive(p, s, fl, true, false);
+      arrive(p, s, fl, 1);
     }
     return;
   }
   const int j0 = q == 0 ? 0 : window_fill(fl, cur, q);
+  if constexpr (SUM) {
+    const int E = 4 * nn, ng = E < BMS_WG ? BMS_WG / E : 1;
+    const int grp = threadIdx.x / E;
+    if (grp < ng)
+      for (int e = threadIdx.x - grp * E; e < E; e += BMS_WG) {
+        double2 a = make_double2(0, 0);
+#pragma unroll 8
+        for (int b = grp; b < nparts; b += ng) a = cadd(a, part[(size_t)b * E + e]);
+        gs[grp * E + e] = a;
+      }
+    __syncthreads();
+    if (ng > 1) {
+      double2 a = make_double2(0, 0);
+      if ((int)threadIdx.x < E)
+        for (int k = 0; k < ng; ++k) a = cadd(a, gs[k * E + threadIdx.x]);
+      __syncthreads();
+      if ((int)threadIdx.x < E) gs[threadIdx.x] = a;
+      __syncthreads();
+    }
+  }
+  const double2* G4 = SUM ? gs : s.G4;
   WM<NE> ga, dl;
   if (wave < 2) {
     // G_k = P^H (A + s0) P, Hermitian up to rounding
-    WM<NE> G = wm_load<NE>(s.G4, n, n, g, c);
-    const WM<NE> Gt = wm_loadh<NE>(s.G4, n, n, g, c);
+    WM<NE> G = wm_load<NE>(G4, n, n, g, c);
+    const WM<NE> Gt = wm_loadh<NE>(G4, n, n, g, c);
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
       G.re[e] = 0.5 * (G.re[e] + Gt.re[e]);
@@ -415,9 +452,9 @@ __global__ __launch_bounds__(BMS_WG) void k_small_iter_w(SmallParams p, SmallSta
     }
     if (q == 0) dl = wm_load<NE>(s.delta, n, n, g, c);
     if (wave == 0) {
-      const WM<NE> qwh = wm_loadh<NE>(s.G4 + nn, n, n, g, c);    // (Q^H W)^H
-      const WM<NE> ww = wm_load<NE>(s.G4 + 2 * nn, n, n, g, c);  // W^H W
-      const WM<NE> qq = wm_load<NE>(s.G4 + 3 * nn, n, n, g, c);
+      const WM<NE> qwh = wm_loadh<NE>(G4 + nn, n, n, g, c);    // (Q^H W)^H
+      const WM<NE> ww = wm_load<NE>(G4 + 2 * nn, n, n, g, c);  // W^H W
+      const WM<NE> qq = wm_load<NE>(G4 + 3 * nn, n, n, g, c);
       if (q == 0) wm_store(s.Gb + (size_t)cur * nn, n, n, g, c, G);
       WM<NE> A = G;
       const int st1 = wm_inverse(A, n, g, c);  // alpha_k
@@ -499,11 +536,11 @@ __global__ __launch_bounds__(BMS_WG) void k_small_iter_w(SmallParams p, SmallSta
     return;
   }
   if (l.st2) {
-    if (q == 0 && threadIdx.x == 0) {
-      if (l.st2 == BMS_ENAN)
+    if (threadIdx.x == 0) {
+      if (l.st2 != BMS_ENAN)
+        arrive(p, s, fl, 3);  // the explicit Gram finishes this iteration
+      else if (q == 0)
         set_error(fl, BMS_ENAN);
-      else
-        fl->need_explicit = 1;  // the explicit Gram finishes this iteration
     }
     return;
   }
@@ -559,17 +596,29 @@ __global__ __launch_bounds__(BMS_WG) void k_small_rho_explicit_w(SmallParams p, 
 
 }  // namespace
 
-template <typename T>
-hipError_t launch_small_iter_w(hipStream_t st, const SmallParams& p, SmallState s,
-                               SolverFlags* fl, cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm) {
+template <typename T, bool SUM>
+static hipError_t small_iter_w(hipStream_t st, const SmallParams& p, SmallState s,
+                               SolverFlags* fl, cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm,
+                               const double2* part, int nparts) {
+#define ITER_W(NE) \
+  k_small_iter_w<T, NE, SUM><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm, part, nparts)
   switch ((p.n + 3) / 4) {
-    case 1: k_small_iter_w<T, 1><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm); break;
-    case 2: k_small_iter_w<T, 2><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm); break;
-    case 3: k_small_iter_w<T, 3><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm); break;
-    case 4: k_small_iter_w<T, 4><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm); break;
+    case 1: ITER_W(1); break;
+    case 2: ITER_W(2); break;
+    case 3: ITER_W(3); break;
+    case 4: ITER_W(4); break;
     default: return hipErrorInvalidValue;
   }
+#undef ITER_W
   return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_small_iter_w(hipStream_t st, const SmallParams& p, SmallState s,
+                               SolverFlags* fl, cplx<T>* Mx, cplx<T>* Mp, cplx<T>* Wm,
+                               const double2* part, int nparts) {
+  return nparts ? small_iter_w<T, true>(st, p, s, fl, Mx, Mp, Wm, part, nparts)
+                : small_iter_w<T, false>(st, p, s, fl, Mx, Mp, Wm, part, 0);
 }
 
 template <typename T>
@@ -587,7 +636,7 @@ hipError_t launch_small_rho_explicit_w(hipStream_t st, const SmallParams& p, Sma
 
 #define INST_W(T, C)                                                                        \
   template hipError_t launch_small_iter_w<T>(hipStream_t, const SmallParams&, SmallState,   \
-                                             SolverFlags*, C*, C*, C*);                     \
+                                             SolverFlags*, C*, C*, C*, const double2*, int); \
   template hipError_t launch_small_rho_explicit_w<T>(hipStream_t, const SmallParams&,       \
                                                      SmallState, SolverFlags*, C*, C*);
 INST_W(double, double2)

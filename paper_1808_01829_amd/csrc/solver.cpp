@@ -5,7 +5,8 @@
 //   G4 = [P^H W, Q^H W, W^H W, Q^H Q]        (one pass, FP64)
 //   alpha_k, beta^(s)_k, alpha^(s)_k, rho_k, delta^(s)_k, convergence
 //                                            (one work-group per shift)
-//   [explicit V^H V and rho_k, only if the expansion lost its pivot]
+//   [explicit V^H V and rho_k, only if the expansion lost its pivot: for n <= 16 the
+//    iteration pauses there the first time, see solve_core]
 //   Q_k, X^(s), P^(s) for all active shifts  (fused update)
 // The host only enqueues chunks of iterations and reads a small flag block
 // between chunks; stopping, freezing of converged shifts and the iteration
@@ -179,32 +180,42 @@ UpdateArgs<T, T> update_args(const Work& w) {
 // ev: NULL, or 8 timing events recorded around the 7 launches (direct
 // launches only: event-record nodes of a replayed graph carry no usable
 // timestamps on this runtime, measured).
-// k: the iteration's index (Q_k is in ring buffer k % win).
+// k: the iteration's index (Q_k is in ring buffer k % win). tail: only what follows the
+// small step of a paused iteration, the explicit Gram included (the small step's events are
+// then recorded again: that launch counts no time).
 template <typename T>
 int enqueue_iteration(bms_ctx* c, const Work& w, const SmallParams& sp, double mass, long k,
-                      hipEvent_t* ev) {
+                      hipEvent_t* ev, bool tail = false) {
   const int* skip = &w.flags->stop;
   cplx<T>* P0 = (cplx<T>*)w.P;
   const cplx<T>* Qk = (const cplx<T>*)w.Q + (size_t)(k % w.win) * w.blk;
 #define MARK(i) \
   if (ev) HIP_TRY(c, hipEventRecord(ev[i], c->stream))
-  MARK(0);
-  HIP_TRY(c, launch_hop<T>(c, 1, w.n, P0, w.W1, nullptr, 0.0, 1.0, skip));
-  MARK(1);
-  HIP_TRY(c, launch_hop<T>(c, 0, w.n, w.W1, w.W, P0, mass * mass + sp.sigma[0], -1.0, skip));
-  MARK(2);
-  HIP_TRY(c, launch_gram4<T>(c->stream, w.rows, w.n, P0, Qk, w.W, w.sm.G4, w.partials, w.nb,
-                             skip, c->gram_variant, c->num_cu));
-  MARK(3);
-  HIP_TRY(c, launch_small_iter<T>(c->stream, sp, w.sm, w.flags, (cplx<T>*)w.Mx,
-                                  (cplx<T>*)w.Mp, (cplx<T>*)w.Wm));
+  if (!tail) {
+    MARK(0);
+    HIP_TRY(c, launch_hop<T>(c, 1, w.n, P0, w.W1, nullptr, 0.0, 1.0, skip));
+    MARK(1);
+    HIP_TRY(c, launch_hop<T>(c, 0, w.n, w.W1, w.W, P0, mass * mass + sp.sigma[0], -1.0, skip));
+    MARK(2);
+    int nparts = 0;
+    HIP_TRY(c, launch_gram4<T>(c->stream, w.rows, w.n, P0, Qk, w.W, w.sm.G4, w.partials, w.nb,
+                               skip, c->gram_variant, c->num_cu, &nparts));
+    MARK(3);
+    HIP_TRY(c, launch_small_iter<T>(c->stream, sp, w.sm, w.flags, (cplx<T>*)w.Mx,
+                                    (cplx<T>*)w.Mp, (cplx<T>*)w.Wm, w.partials, nparts));
+  } else {
+    HIP_TRY(c, launch_resume(c->stream, w.flags));
+    MARK(3);
+  }
   MARK(4);
   // explicit Cholesky-QR Gram, only when the expansion lost its pivot
-  HIP_TRY(c, launch_cholqr_gram<T>(c->stream, w.rows, w.n, Qk, w.W, w.sm.alpha, w.sm.Gqr,
-                                   w.partials, w.nb, &w.flags->need_explicit));
+  if (tail || sp.inline_explicit)
+    HIP_TRY(c, launch_cholqr_gram<T>(c->stream, w.rows, w.n, Qk, w.W, w.sm.alpha, w.sm.Gqr,
+                                     w.partials, w.nb, &w.flags->need_explicit));
   MARK(5);
-  HIP_TRY(c, launch_small_rho_explicit<T>(c->stream, sp, w.sm, w.flags, (cplx<T>*)w.Mp,
-                                          (cplx<T>*)w.Wm));
+  if (tail || sp.inline_explicit)
+    HIP_TRY(c, launch_small_rho_explicit<T>(c->stream, sp, w.sm, w.flags, (cplx<T>*)w.Mp,
+                                            (cplx<T>*)w.Wm));
   MARK(6);
   const UpdateArgs<T, T> ua = update_args<T>(w);
   // the windowed kernels for n <= 16 (n = 8, 16: unless a vector variant is set), else the
@@ -387,6 +398,11 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
   sp.breakdown_tol = 10.0 * n * (mixed ? kEps32 : kEps);
   for (int s = 0; s < ns; ++s) sp.sigma[s] = sigma[s];
   sp.win = update_window(c, n, ns, (int)sizeof(T), o.check_interval);
+  // Iterations that need the explicit Gram are rare (V small next to Q: at a heavy mass, or
+  // where a small lattice's Krylov space ends), and its three launches cost 6 to 11 us an
+  // iteration even when they exit at once. So they are left out until an iteration asks
+  // for them: it pauses, the host finishes the chunk, and the rest of the solve has them.
+  sp.inline_explicit = small_wave_supported(n) ? 0 : 1;
   Work w;
   if ((rc = alloc_work<T>(c, n, ns, max_iter, sp.win, w))) return rc;
   void *R1 = nullptr, *R2 = nullptr, *R0 = nullptr;
@@ -410,12 +426,21 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
   }
   while (true) {
     if ((rc = enqueue_chunk<T>(c, w, sp, mass, K, o.use_graph != 0))) return rc;
-    if (mixed && enqueued + K - last_rel >= o.reliable_interval) {
-      if ((rc = enqueue_reliable(c, w, sp, mass, B, Xout, xmap, R1, R2, R0, false))) return rc;
-      last_rel = enqueued + K;
+    const bool rel = mixed && enqueued + K - last_rel >= o.reliable_interval;
+    while (true) {
+      if (rel && (rc = enqueue_reliable(c, w, sp, mass, B, Xout, xmap, R1, R2, R0, false)))
+        return rc;
+      HIP_TRY(c, hipMemcpyAsync(&hf, w.flags, sizeof hf, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(c, hipStreamSynchronize(c->stream));
+      if (hf.stop != 2) break;
+      // paused in iteration hf.iter of this chunk (what followed it did nothing)
+      sp.inline_explicit = 1;
+      for (int k = (int)(hf.iter - enqueued); k < K; ++k)
+        if ((rc = enqueue_iteration<T>(c, w, sp, mass, k, c->timing ? &c->evpool[8 * k] : nullptr,
+                                       k == (int)(hf.iter - enqueued))))
+          return rc;
     }
-    HIP_TRY(c, hipMemcpyAsync(&hf, w.flags, sizeof hf, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (rel) last_rel = enqueued + K;
     if (c->timing) {
       // links read by one half hop: nine entries, or six for two-row links
       const int epl = c->links_two_rows && c->nlinks == 8 ? 6 : 9;

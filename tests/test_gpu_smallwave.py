@@ -45,3 +45,25 @@ def test_small_step_matches_oracle_iterates(n, k, mass):
     for s in range(len(SHIFTS)):
         err = np.linalg.norm(X[s] - oo["X"][s]) / np.linalg.norm(oo["X"][s])
         assert err <= 1e-11, (s, err)
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("timing", [False, True])
+@pytest.mark.parametrize("n,interval", [(1, 8), (4, 3), (8, 8), (11, 1), (16, 8), (20, 8)])
+def test_paused_iteration_goes_on(n, interval, timing, mixed):
+    """At mass 8 the residual falls by more than 100 in an iteration, so the first solve's
+    iteration pauses for the explicit Gram (n <= 16) and the chunk is finished by the host;
+    a second solve on the context starts again without the fallback kernels."""
+    torch = torch_gpu()
+    from paper_1808_01829_amd import bms
+    U, B = random_gauge(DIMS, 0.3, 900 + n), gaussian_block(DIMS, n, 901 + n)
+    ctx = bms.Context(DIMS, BC)
+    ctx.set_gauge(to_dev(torch, U))
+    ctx.timing(timing)
+    Bd = to_dev(torch, B)
+    for mass in (8.0, 0.3, 8.0):
+        X, st = ctx.solve(mass, SHIFTS, Bd, tol=1e-11, check_interval=interval,
+                          precision=bms.BMS_PREC_MIXED if mixed else bms.BMS_PREC_F64)
+        tr = O.true_residuals(DIMS, BC, U, mass, SHIFTS, B, to_np(X))
+        assert tr.max() <= 1e-11
+        assert st["iterations"] < 400
