@@ -161,30 +161,19 @@ extern "C" int bms_set_gauge(bms_ctx* c, const void* U) {
   if (!U) return set_err(c, BMS_EINVAL, "bms_set_gauge: U is NULL");
   int rc = stream_begin(c);
   if (rc) return rc;
-  size_t nlink = (size_t)2 * c->nblk * 72 << c->sbl;
-  if ((rc = ensure_buf(c, c->links64, nlink * sizeof(double2)))) return rc;
-  if ((rc = ensure_buf(c, c->links32, nlink * sizeof(float2)))) return rc;
-  // padding sites of the last block are never read; zero them once
-  HIP_TRY(c, launch_fill_zero(c->stream, c->links64.p, nlink * sizeof(double2)));
-  HIP_TRY(c, launch_fill_zero(c->stream, c->links32.p, nlink * sizeof(float2)));
-  const bool two = c->link_rows == 2;
-  if (two) {
+  c->gauge_set = false;  // a failure below leaves no links
+  // (padding sites of the last block are never read)
+  c->links_two_rows = false;
+  c->link_dev = -1;
+  if (c->link_rows == 2) {
     const size_t nrow = (size_t)2 * c->nblk * 48 << c->sbl;
     if ((rc = ensure_buf(c, c->links64r, nrow * sizeof(double2)))) return rc;
     if ((rc = ensure_buf(c, c->links32r, nrow * sizeof(float2)))) return rc;
     if ((rc = ensure_buf(c, c->lsign, (size_t)2 * c->vh * sizeof(uint32_t)))) return rc;
     if ((rc = ensure_buf(c, c->lcheck, 256))) return rc;
-    HIP_TRY(c, launch_fill_zero(c->stream, c->links64r.p, nrow * sizeof(double2)));
-    HIP_TRY(c, launch_fill_zero(c->stream, c->links32r.p, nrow * sizeof(float2)));
     HIP_TRY(c, launch_fill_zero(c->stream, c->lcheck.p, 16));
-  }
-  HIP_TRY(c, launch_gauge_import(c, U, c->links64.p, c->links32.p, two ? c->links64r.p : nullptr,
-                                 two ? c->links32r.p : nullptr, two ? c->lsign.p : nullptr,
-                                 two ? c->lcheck.p : nullptr));
-  c->links_two_rows = false;
-  c->link_dev = -1;
-  if (two) {
-    // the hop reads two rows only if every third row is the SU(3) one to 1e-12
+    HIP_TRY(c, launch_gauge_import(c, U, c->links64r.p, c->links32r.p, 6, c->lsign.p, c->lcheck.p));
+    // two rows are used only if every third row is the SU(3) one to 1e-12
     unsigned long long bits = 0;
     HIP_TRY(c, hipMemcpyAsync(&bits, c->lcheck.p, sizeof bits, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -192,6 +181,12 @@ extern "C" int bms_set_gauge(bms_ctx* c, const void* U) {
     memcpy(&dev, &bits, sizeof dev);
     c->link_dev = dev;
     c->links_two_rows = dev <= 1e-12;
+  }
+  if (!c->links_two_rows) {
+    const size_t nlink = (size_t)2 * c->nblk * 72 << c->sbl;
+    if ((rc = ensure_buf(c, c->links64, nlink * sizeof(double2)))) return rc;
+    if ((rc = ensure_buf(c, c->links32, nlink * sizeof(float2)))) return rc;
+    HIP_TRY(c, launch_gauge_import(c, U, c->links64.p, c->links32.p, 9, nullptr, nullptr));
   }
   c->nlinks = 8;
   c->gauge_set = true;
@@ -220,11 +215,10 @@ extern "C" int bms_set_gauge_improved(bms_ctx* c, const void* V, const void* W) 
       return set_err(c, BMS_EINVAL, "the improved operator needs every extent >= 4");
   int rc = stream_begin(c);
   if (rc) return rc;
+  c->gauge_set = false;  // a failure below leaves no links
   size_t nlink = (size_t)2 * c->nblk * 144 << c->sbl;
   if ((rc = ensure_buf(c, c->links64, nlink * sizeof(double2)))) return rc;
   if ((rc = ensure_buf(c, c->links32, nlink * sizeof(float2)))) return rc;
-  HIP_TRY(c, launch_fill_zero(c->stream, c->links64.p, nlink * sizeof(double2)));
-  HIP_TRY(c, launch_fill_zero(c->stream, c->links32.p, nlink * sizeof(float2)));
   HIP_TRY(c, launch_gauge_import_improved(c, V, W, c->links64.p, c->links32.p));
   c->links_two_rows = false;
   c->link_dev = -1;

@@ -21,12 +21,24 @@ struct ForceArgs {
   int n, ns, sbl, lie, add;
   const double2* X;      // [ns][vh][3][n] even sites
   const double2* Y;      // [ns][vh][3][n] odd sites, Y = D_oe X
-  const double2* links;  // FP64 internal links, both parities
+  const double2* links;  // FP64 internal links, both parities, epl entries each
   size_t pstride;        // complex elements per parity of `links`
+  int epl;               // 9, or 6 for links kept as two rows
   double2* G;            // raw gradient [mu][idx][3][3]
   double* F;             // Lie-algebra force [mu][idx][8]
   double alpha[BMS_MAX_SHIFTS];
 };
+
+// entry e of link k of checkerboard site s; with two-row links an entry of the third row
+// is conj(row0 x row1) / scale, scale = +-1/2
+__device__ __forceinline__ double2 link_entry(const double2* L, uint32_t s, int k, int e, int sbl,
+                                              int epl, double scale) {
+  if (epl == 9 || e < 6) return L[link_off(s, k, e, sbl, 8 * epl, epl)];
+  const int b = e - 6, b1 = b == 2 ? 0 : b + 1, b2 = b == 0 ? 2 : b - 1;
+  auto at = [&](int i) { return L[link_off(s, k, i, sbl, 48, 6)]; };
+  const double2 x = csub(cmul(at(b1), at(3 + b2)), cmul(at(b2), at(3 + b1)));
+  return cscale(cconj(x), 1.0 / scale);
+}
 
 // Sum of a complex value over the LPL lanes of this lane's group (LPL a power
 // of two dividing the wave): every lane of the group ends with the total.
@@ -124,7 +136,8 @@ __global__ __launch_bounds__(BMS_WG) void k_force(ForceArgs a, int lpl) {
   const double2* L = a.links + (size_t)par * a.pstride;
   double2 u[9];
   double f = 2.0 * ((esum & 1) ? -1.0 : 1.0) * ((co[mu] == g.L[mu] - 1) ? a.bc[mu] : 1);
-  for (int e = 0; e < 9; ++e) u[e] = cscale(L[link_off(cb, mu, e, a.sbl)], f);
+  for (int e = 0; e < 9; ++e)
+    u[e] = cscale(link_entry(L, cb, mu, e, a.sbl, a.epl, 0.25 * f), f);
   // W = U M; F^a = Im Tr[T^a W], T^a = lambda_a / 2
   double2 w[9];
   for (int i = 0; i < 3; ++i)
@@ -219,16 +232,31 @@ __global__ __launch_bounds__(BMS_WG, WAVES) void k_force_fused(ForceArgs a) {
   double2 la[9], lb[9];
   if (LDS_LINKS) {
     // the four g-lanes of (site, q) stage the site's links mu and 4 + mu
-    for (int e = gl; e < 9; e += 4) {
-      lds[sl * kLinkPitch + mu * 9 + e] = L[link_off(z, mu, e, a.sbl)];
-      lds[sl * kLinkPitch + (4 + mu) * 9 + e] = L[link_off(z, 4 + mu, e, a.sbl)];
+    double2* sa = lds + sl * kLinkPitch + mu * 9;
+    double2* sb_ = sa + 36;
+    for (int e = gl; e < a.epl; e += 4) {
+      sa[e] = L[link_off(z, mu, e, a.sbl, 8 * a.epl, a.epl)];
+      sb_[e] = L[link_off(z, 4 + mu, e, a.sbl, 8 * a.epl, a.epl)];
+    }
+    if (a.epl == 6) {
+      // the third rows, from the first two of the same four lanes (one wave)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (gl < 3) {
+        const int b1 = gl == 2 ? 0 : gl + 1, b2 = gl == 0 ? 2 : gl - 1;
+        sa[6 + gl] = cscale(cconj(csub(cmul(sa[b1], sa[3 + b2]), cmul(sa[b2], sa[3 + b1]))),
+                            2.0 * eta * bf);
+        sb_[6 + gl] = cscale(cconj(csub(cmul(sb_[b1], sb_[3 + b2]), cmul(sb_[b2], sb_[3 + b1]))),
+                             -2.0 * eta * be);
+      }
     }
     __syncthreads();
   } else {
 #pragma unroll
     for (int e = 0; e < 9; ++e) {
-      la[e] = L[link_off(z, mu, e, a.sbl)];
-      lb[e] = L[link_off(z, 4 + mu, e, a.sbl)];
+      la[e] = link_entry(L, z, mu, e, a.sbl, a.epl, 0.5 * eta * bf);
+      lb[e] = link_entry(L, z, 4 + mu, e, a.sbl, a.epl, -0.5 * eta * be);
     }
   }
   double2 ma[9], mb[9];
@@ -408,8 +436,9 @@ extern "C" int bms_force(bms_ctx* c, int n, int ns, const double* alpha, const v
   a.add = (flags & BMS_FORCE_ADD) != 0;
   a.X = (const double2*)X;
   a.Y = (const double2*)Y;
-  a.links = (const double2*)c->links64.p;
-  a.pstride = (size_t)c->nblk * 72 << c->sbl;
+  a.epl = c->links_two_rows ? 6 : 9;
+  a.links = (const double2*)(c->links_two_rows ? c->links64r.p : c->links64.p);
+  a.pstride = (size_t)c->nblk * (8 * a.epl) << c->sbl;
   a.G = (double2*)out;
   a.F = (double*)out;
   for (int s = 0; s < ns; ++s) a.alpha[s] = alpha[s];

@@ -3,6 +3,7 @@
 #include <cstring>
 
 #include "internal.h"
+#include "links.h"
 
 namespace {
 
@@ -13,79 +14,93 @@ struct Bc {
 // U[mu][idx][a][b] complex128 -> per output parity p and cb site s the 8 links
 //   k = mu     :  +1/2 eta_mu(x) bf U_mu(x)              (hop to x+mu)
 //   k = 4 + mu :  -1/2 eta_mu(x) bb U_mu(x-mu)^dag       (hop to x-mu)
-// bf / bb = bc[mu] if that hop crosses the boundary. FP64 and FP32 copies.
-// With r64 set, also the two-row copies (entries 0..5 of each link, FP64 and
-// FP32), bit k of sign[p][s] set when link k's scale c (+-1/2) is negative,
-// and in *dev the largest difference, over the links and the parts of their
-// entries, between a third row and the one the first two give for an SU(3)
-// matrix, row2(c V) = conj(row0 x row1) / c (+inf if not finite). A
-// non-negative double orders like its bit pattern, so an integer atomic
-// maximum of the bits keeps it.
-__device__ __forceinline__ void store_link(const double2 (&v)[9], double f, uint32_t s, int k,
-                                           size_t pbase, size_t rbase, int sbl, double2* l64,
-                                           float2* l32, double2* r64, float2* r32,
-                                           unsigned long long* dev, uint32_t& mask) {
-  for (int e = 0; e < 9; ++e) {
-    const size_t o = pbase + link_off(s, k, e, sbl);
-    l64[o] = v[e];
-    l32[o] = make_float2((float)v[e].x, (float)v[e].y);
-  }
-  if (!r64) return;
-  for (int e = 0; e < 6; ++e) {
-    const size_t o = rbase + link_off(s, k, e, sbl, 48, 6);
-    r64[o] = v[e];
-    r32[o] = make_float2((float)v[e].x, (float)v[e].y);
-  }
-  if (f < 0) mask |= 1u << k;
-  const double inv = 1.0 / f;
-  double d = 0;
-  for (int b = 0; b < 3; ++b) {
-    const int b1 = (b + 1) % 3, b2 = (b + 2) % 3;
-    const double2 x = csub(cmul(v[b1], v[3 + b2]), cmul(v[b2], v[3 + b1]));
-    const double2 r = cscale(cconj(x), inv);
-    const double dx = fabs(r.x - v[6 + b].x), dy = fabs(r.y - v[6 + b].y);
-    d = dx > d ? dx : d;
-    d = dy > d ? dy : d;
-    if (!(dx == dx) || !(dy == dy)) d = __builtin_huge_val();
-  }
-  if (d > 0) atomicMax(dev, (unsigned long long)__double_as_longlong(d));
-}
-
+// bf / bb = bc[mu] if that hop crosses the boundary, in FP64 and FP32, EPL entries of each:
+// EPL = 9: whole links. EPL = 6: the first two rows, and bit k of sign[p][s] set when link
+// k's scale c (+-1/2) is negative, and in *dev the largest difference, over the links and
+// the parts of their entries, between a third row and the one the first two give for an
+// SU(3) matrix, row2(c V) = conj(row0 x row1) / c (+inf if not finite). A non-negative
+// double orders like its bit pattern, so an integer atomic maximum of the bits keeps it (one
+// per work-group, and none where the maximum is there already).
+// One thread per site, a wave over 64 consecutive ones, so that U is read as whole lines
+// (links.h) and either parity's entries are written as runs of 32 sites. Bound by that
+// traffic, the writes above all. Measured at 16^3 x 32: 206 us with both forms written,
+// an atomic per link and links read a thread each, and 60 us of fills -> 42 us.
+template <int EPL>
 __global__ __launch_bounds__(BMS_WG) void k_gauge_import(
     const double2* __restrict__ U, double2* __restrict__ l64, float2* __restrict__ l32,
-    double2* __restrict__ r64, float2* __restrict__ r32, uint32_t* __restrict__ sign,
-    unsigned long long* __restrict__ dev, Geom g, Bc bc, int sbl, int nblk, int vol) {
-  uint32_t tid = blockIdx.x * BMS_WG + threadIdx.x;
-  if (tid >= 2u * (uint32_t)g.vh) return;
-  int par = tid >= (uint32_t)g.vh;
-  uint32_t s = tid - (par ? g.vh : 0);
-  SiteCoord c = site_coords(s, g, par);
-  int co[4] = {c.x, c.y, c.z, c.t};
-  const size_t pbase = (size_t)par * nblk * 72 << sbl;
-  const size_t rbase = (size_t)par * nblk * 48 << sbl;
-  auto lex = [&](const int* q) { return q[0] + g.L[0] * (q[1] + g.L[1] * (q[2] + g.L[2] * q[3])); };
-  int idx = lex(co);
+    uint32_t* __restrict__ sign, unsigned long long* __restrict__ dev, Geom g, Bc bc, int sbl,
+    int nblk, int vol) {
+  __shared__ double2 stage[BMS_WG / 64][WL_ENTRIES];
+  __shared__ double wdev[BMS_WG / 64];
+  double2* lds = stage[threadIdx.x >> 6];
+  const uint32_t x0 = blockIdx.x * BMS_WG + threadIdx.x;
+  const bool live = x0 < (uint32_t)vol;
+  const uint32_t idx = live ? x0 : (uint32_t)vol - 1;  // past the end: a valid site, no writes
+  const uint32_t s = idx >> 1;
+  SiteCoord c = site_coords(s, g, 0);
+  c.x = (int)(idx - (idx / (uint32_t)g.L[0]) * (uint32_t)g.L[0]);
+  const int co[4] = {c.x, c.y, c.z, c.t};
+  const int par = (c.x + c.y + c.z + c.t) & 1;
+  const size_t pbase = (size_t)par * nblk * (8 * EPL) << sbl;
+  const int st[4] = {1, g.L[0], g.L[0] * g.L[1], g.L[0] * g.L[1] * g.L[2]};
   uint32_t mask = 0;
-  for (int mu = 0; mu < 4; ++mu) {
-    int esum = 0;
-    for (int nu = 0; nu < mu; ++nu) esum += co[nu];
-    double eta = (esum & 1) ? -0.5 : 0.5;
+  double d = 0;
+  M3 next;
+  wl_fetch(U, (int)idx, next);
+  int esum = 0;
+#pragma unroll
+  for (int h = 0; h < 8; ++h) {
+    // forward and backward link of direction mu in turn
+    const int mu = h >> 1, k = h & 1 ? 4 + mu : mu;
+    const double eta = (esum & 1) ? -0.5 : 0.5;
+    const double f = h & 1 ? -eta * (co[mu] == 0 ? bc.b[mu] : 1)
+                           : eta * (co[mu] == g.L[mu] - 1 ? bc.b[mu] : 1);
+    const M3 u = wl_own(next, lds);
+    if (h < 7) {
+      const int m2 = (h + 1) >> 1;
+      const int back = co[m2] == 0 ? g.L[m2] - 1 : -1;
+      wl_fetch(U, m2 * vol + (int)idx + ((h + 1) & 1 ? back * st[m2] : 0), next);
+    }
     double2 v[9];
-    // forward
-    const double ff = eta * ((co[mu] == g.L[mu] - 1) ? bc.b[mu] : 1);
-    const double2* uf = U + ((size_t)mu * vol + idx) * 9;
-    for (int e = 0; e < 9; ++e) v[e] = cscale(uf[e], ff);
-    store_link(v, ff, s, mu, pbase, rbase, sbl, l64, l32, r64, r32, dev, mask);
-    // backward: daggered link of the neighbour x - mu
-    int nb[4] = {co[0], co[1], co[2], co[3]};
-    nb[mu] = co[mu] == 0 ? g.L[mu] - 1 : co[mu] - 1;
-    const double fb = -eta * ((co[mu] == 0) ? bc.b[mu] : 1);
-    const double2* ub = U + ((size_t)mu * vol + lex(nb)) * 9;
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) v[3 * a + b] = cscale(cconj(ub[3 * b + a]), fb);
-    store_link(v, fb, s, 4 + mu, pbase, rbase, sbl, l64, l32, r64, r32, dev, mask);
+#pragma unroll
+    for (int e = 0; e < 9; ++e)
+      v[e] = h & 1 ? cscale(cconj(u.e[3 * (e % 3) + e / 3]), f) : cscale(u.e[e], f);
+    if (live) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        const size_t o = pbase + link_off(s, k, e, sbl, 8 * EPL, EPL);
+        l64[o] = v[e];
+        l32[o] = make_float2((float)v[e].x, (float)v[e].y);
+      }
+    }
+    if constexpr (EPL == 6) {
+      if (f < 0) mask |= 1u << k;
+      const double inv = 1.0 / f;
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        const int b1 = (b + 1) % 3, b2 = (b + 2) % 3;
+        const double2 x = csub(cmul(v[b1], v[3 + b2]), cmul(v[b2], v[3 + b1]));
+        const double2 r = cscale(cconj(x), inv);
+        const double dx = fabs(r.x - v[6 + b].x), dy = fabs(r.y - v[6 + b].y);
+        d = dx > d ? dx : d;
+        d = dy > d ? dy : d;
+        if (!(dx == dx) || !(dy == dy)) d = __builtin_huge_val();
+      }
+    }
+    if (h & 1) esum += co[mu];
   }
-  if (sign) sign[(size_t)par * g.vh + s] = mask;
+  if constexpr (EPL == 6) {
+    if (live) sign[(size_t)par * g.vh + s] = mask;
+    for (int off = 1; off < 64; off <<= 1) d = fmax(d, __shfl_xor(d, off));
+    if ((threadIdx.x & 63) == 0) wdev[threadIdx.x >> 6] = d;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < BMS_WG / 64; ++w) d = fmax(d, wdev[w]);
+      const unsigned long long bits = (unsigned long long)__double_as_longlong(d);
+      if (bits > __hip_atomic_load(dev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(dev, bits);
+    }
+  }
 }
 
 // Signed distance of hop k: one step forward (0..3) and back (4..7), for the
@@ -740,14 +755,19 @@ __global__ __launch_bounds__(BMS_WG) void k_hop_s(const cplx<T>* __restrict__ li
 
 }  // namespace
 
-hipError_t launch_gauge_import(const bms_ctx* c, const void* U, void* l64, void* l32,
-                               void* r64, void* r32, void* sign, void* dev) {
+hipError_t launch_gauge_import(const bms_ctx* c, const void* U, void* l64, void* l32, int entries,
+                               void* sign, void* dev) {
   Bc bc;
   for (int i = 0; i < 4; ++i) bc.b[i] = c->bc[i];
-  uint32_t nthr = 2u * c->vh;
-  k_gauge_import<<<(nthr + BMS_WG - 1) / BMS_WG, BMS_WG, 0, c->stream>>>(
-      (const double2*)U, (double2*)l64, (float2*)l32, (double2*)r64, (float2*)r32,
-      (uint32_t*)sign, (unsigned long long*)dev, c->geom, bc, c->sbl, c->nblk, (int)c->vol);
+  const unsigned nblk = (unsigned)((c->vol + BMS_WG - 1) / BMS_WG);
+  if (entries == 6)
+    k_gauge_import<6><<<nblk, BMS_WG, 0, c->stream>>>(
+        (const double2*)U, (double2*)l64, (float2*)l32, (uint32_t*)sign, (unsigned long long*)dev,
+        c->geom, bc, c->sbl, c->nblk, (int)c->vol);
+  else
+    k_gauge_import<9><<<nblk, BMS_WG, 0, c->stream>>>((const double2*)U, (double2*)l64,
+                                                      (float2*)l32, nullptr, nullptr, c->geom, bc,
+                                                      c->sbl, c->nblk, (int)c->vol);
   return hipGetLastError();
 }
 

@@ -1,0 +1,68 @@
+"""Kernels that read a caller's links as whole lines, where a wave or a work-group is
+not full: the import, the gauge force, the link update and the force from two-row links.
+
+Lattices: 16 sites (a quarter of a wave), whole waves but no whole work-group (192), neither
+(80, 240), and extents 2, where both neighbours coincide. Tolerances: one pass of products of
+SU(3) matrices and at most ten squarings of the exponential, each a few units of 2.2e-16:
+1e-13 as in the other gauge tests, for a step of |eps P| near 20 (about seven squarings,
+which double the rounding each) 1e-12.
+"""
+import numpy as np
+import pytest
+
+from gpu_common import rel, to_dev, to_np, torch_gpu
+from oracle import oracle as O
+from oracle import rhmc as R
+from paper_1808_01829_amd.inputs import configs, gaussian_block, random_gauge
+
+pytestmark = pytest.mark.gpu
+BC = (1, 1, 1, -1)
+DIMS = [(2, 2, 2, 2), (4, 2, 2, 6), (2, 10, 2, 2), (4, 4, 2, 6), (6, 4, 2, 10), (2, 6, 8, 10)]
+
+
+@pytest.mark.parametrize("dims", DIMS)
+def test_gauge_force_and_update(dims):
+    torch = torch_gpu()
+    from paper_1808_01829_amd import bms
+    U = random_gauge(dims, 0.7, 11)
+    P = np.random.default_rng(12).standard_normal((4, int(np.prod(dims)), 8))
+    c = bms.Context(dims, BC)
+    Ud, Pd = to_dev(torch, U), to_dev(torch, P)
+    c.gauge_force(5.6, Ud, Pd, -0.3)
+    assert rel(to_np(Pd), P - 0.3 * R.gauge_force(dims, U, 5.6)) < 1e-13
+    assert np.array_equal(to_np(Ud), U)
+    for eps, bar in ((0.05, 1e-13), (-0.4, 1e-13), (6.0, 1e-12)):
+        Ud = to_dev(torch, U)
+        c.gauge_update(eps, to_dev(torch, P), Ud)
+        assert rel(to_np(Ud), R.link_update(U, P, eps)) < bar
+
+
+@pytest.mark.parametrize("dims", DIMS)
+@pytest.mark.parametrize("field", ["su3", "one link off", "scaled"])
+def test_import_and_force_in_both_link_forms(dims, field):
+    torch = torch_gpu()
+    from paper_1808_01829_amd import bms
+    r = configs.workload_coefficients("c1")
+    U = random_gauge(dims, 0.6, 21)
+    if field == "one link off":
+        U[3, -1, 2, 0] += 1e-9
+    elif field == "scaled":
+        U *= 1.01
+    n = 3
+    v = gaussian_block(dims, n, 22)
+    X = np.stack([gaussian_block(dims, n, 30 + s) for s in range(len(r.beta))])
+    Go = O.force(dims, BC, U, r.alpha, X)
+    Fo = O.lie_force(U, Go)
+    c = bms.Context(dims, BC)
+    for rows in (2, 3, 2):
+        c.set_link_rows(rows)
+        c.set_gauge(to_dev(torch, U))
+        assert c.link_rows() == (2 if rows == 2 and field == "su3" else 3)
+        for par in (0, 1):
+            ref = np.stack([O.dslash_half(dims, BC, U, par, v[..., j]) for j in range(n)], axis=-1)
+            assert rel(to_np(c.apply_hop(par, to_dev(torch, v))), ref) < 1e-13
+        for variant in (-1, 0, 1):
+            c.set_variant(bms.BMS_KERNEL_FORCE, variant)
+            Xd = to_dev(torch, X)
+            assert rel(to_np(c.force(r.alpha, Xd, bms.BMS_FORCE_RAW)), Go) < 1e-12
+            assert rel(to_np(c.force(r.alpha, Xd, bms.BMS_FORCE_LIE)), Fo) < 1e-12
