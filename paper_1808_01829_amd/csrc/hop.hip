@@ -229,6 +229,15 @@ __device__ __forceinline__ uint32_t hop_first_site(const HopTiles& m, const Geom
   return hop_block_site(m, g, blockIdx.x);
 }
 
+// Hops whose loads a thread of the batched hop keeps in flight: as many of the 8 as leave
+// its registers (of 256, two waves per SIMD) to the sums, 0 where two hops are all that fit.
+// entries: link entries a thread loads per hop; columns: 3R.
+template <typename T>
+constexpr int hop_batch(int entries, int columns) {
+  const int per = (entries + columns) * 2 * (int)sizeof(T) / 4;
+  return 8 * per <= 144 ? 8 : (4 * per <= 176 ? 4 : 0);
+}
+
 // out(s) = b * sum_k L_k(s) in(nbr_k(s)) + a * aux(s) on n columns.
 // One thread per (site, column group g): the n/R threads of a site share its
 // links (the block operator reads each link once per n columns) and each link
@@ -240,7 +249,8 @@ __device__ __forceinline__ uint32_t hop_first_site(const HopTiles& m, const Geom
 // which the compiler loads as 16-byte vectors.
 // EPL: link entries stored, 9, or 6 for SU(3) links kept as two rows (the
 // third rebuilt from them and the site's sign mask `sgn`).
-template <typename T, int R, bool NT, int NL, int EPL>
+// BH: hops whose loads are all in flight together (0: two hops, unrolled), see hop_batch.
+template <typename T, int R, bool NT, int NL, int EPL, int BH>
 __global__ __launch_bounds__(BMS_WG) void k_hop(const cplx<T>* __restrict__ links,
                                                 const cplx<T>* __restrict__ in,
                                                 cplx<T>* __restrict__ out,
@@ -251,7 +261,7 @@ __global__ __launch_bounds__(BMS_WG) void k_hop(const cplx<T>* __restrict__ link
   using C = cplx<T>;
   if (skip && *skip) return;
   const uint32_t ngrp = dgrp.d;  // n / R column groups per site
-  uint32_t tid = blockIdx.x * BMS_WG + threadIdx.x;
+  uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
   if (tid >= (uint32_t)g.vh * ngrp) return;
   uint32_t s, grp;
   if (tiles.on) {
@@ -274,21 +284,18 @@ __global__ __launch_bounds__(BMS_WG) void k_hop(const cplx<T>* __restrict__ link
     for (int r = 0; r < R; ++r) acc[a3][r] = czero<C>();
   const size_t st = (size_t)1 << sbl;
   const uint32_t msk = EPL == 6 ? sgn[s] : 0u;
-#pragma unroll 2
-  for (int k = 0; k < NL; ++k) {
-    int mu = k & 3;
-    int nb = neighbour_cb((int)s, c, g, mu, hop_dist(k));
+  auto load = [&](int k, C (&l)[9], C (&v)[3][R]) {
+    const int nb = neighbour_cb((int)s, c, g, k & 3, hop_dist(k));
     const C* src = in + (size_t)nb * 3 * n + j0;
     const C* L = links + link_off(s, k, 0, sbl, EPL * NL, EPL);
-    C l[9], v[3][R];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) l[e] = link_ld<NT>(L + e * st);
 #pragma unroll
     for (int cb = 0; cb < 3; ++cb)
 #pragma unroll
       for (int r = 0; r < R; ++r) v[cb][r] = src[cb * n + r * cstep];
-    // all of the hop's loads in flight before the first use (as in k_hop_q)
-    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto accumulate = [&](int k, C (&l)[9], const C (&v)[3][R]) {
     if constexpr (EPL == 6) link_row2(l, (msk >> k) & 1);
 #pragma unroll
     for (int cb = 0; cb < 3; ++cb)
@@ -296,6 +303,26 @@ __global__ __launch_bounds__(BMS_WG) void k_hop(const cplx<T>* __restrict__ link
       for (int a3 = 0; a3 < 3; ++a3)
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[a3][r] = cfma(l[3 * a3 + cb], v[cb][r], acc[a3][r]);
+  };
+  if constexpr (BH > 0) {
+#pragma unroll 1
+    for (int k0 = 0; k0 < NL; k0 += BH) {
+      C l[BH][9], v[BH][3][R];
+#pragma unroll
+      for (int h = 0; h < BH; ++h) load(k0 + h, l[h], v[h]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < BH; ++h) accumulate(k0 + h, l[h], v[h]);
+    }
+  } else {
+#pragma unroll 2
+    for (int k = 0; k < NL; ++k) {
+      C l[9], v[3][R];
+      load(k, l, v);
+      // all of the hop's loads in flight before the first use (as in k_hop_q)
+      __builtin_amdgcn_sched_barrier(0);
+      accumulate(k, l, v);
+    }
   }
   size_t o = (size_t)s * 3 * n + j0;
 #pragma unroll
@@ -330,7 +357,8 @@ __device__ __forceinline__ double quad_bcast(double v) {
 // FP32).
 // With links kept as two rows (EPL = 6) thread q loads entries q and 4 + q%2,
 // and every thread rebuilds the third row.
-template <typename T, int R, bool NT, int NL, int EPL>
+// BH: as in k_hop; the batched form (small lattices) loads the -x columns like the others.
+template <typename T, int R, bool NT, int NL, int EPL, int BH>
 __global__ __launch_bounds__(BMS_WG) void k_hop_q(const cplx<T>* __restrict__ links,
                                                   const cplx<T>* __restrict__ in,
                                                   cplx<T>* __restrict__ out,
@@ -341,9 +369,9 @@ __global__ __launch_bounds__(BMS_WG) void k_hop_q(const cplx<T>* __restrict__ li
   using C = cplx<T>;
   if (skip && *skip) return;
   // whole quads leave together (4 * Vh threads), so every DPP source lane is active
-  if (blockIdx.x * BMS_WG + threadIdx.x >= (uint32_t)g.vh * 4) return;
+  if (blockIdx.x * blockDim.x + threadIdx.x >= (uint32_t)g.vh * 4) return;
   const uint32_t s = tiles.on ? hop_first_site(tiles, g) + (threadIdx.x >> 2)
-                              : (blockIdx.x * BMS_WG + threadIdx.x) >> 2;
+                              : (blockIdx.x * blockDim.x + threadIdx.x) >> 2;
   const int q = (int)(threadIdx.x & 3);
   constexpr bool kInterleave = sizeof(T) == 8;
   const int cstep = kInterleave ? 4 : 1;
@@ -394,48 +422,64 @@ __global__ __launch_bounds__(BMS_WG) void k_hop_q(const cplx<T>* __restrict__ li
 #pragma unroll
       for (int r = 0; r < R; ++r) v[cb][r] = src[cb * n + r * cstep];
   };
-  // The two x hops first. Along an x-row the -x neighbour of a site is the
-  // +x neighbour of the site before it (with the row's wrap, of the row's
-  // last site), so where the wave holds that site (four lanes down, the same
-  // q) the -x columns come from its +x columns by cross-lane moves instead of
-  // a second read from L2; the other lanes (first site of the wave, rows that
-  // do not fill the wave) load them.
-  {
-    const int lane = (int)(threadIdx.x & 63);
-    const bool full = blockIdx.x * BMS_WG + (threadIdx.x & ~63u) + 64 <= (uint32_t)g.vh * 4;
-    const int from = (lane - 4) & 63;
-    const int nb0 = neighbour_cb((int)s, c, g, 0, 1), nb4 = neighbour_cb((int)s, c, g, 0, -1);
-    C t0, t1, t2, v[3][R];
-    link_load(0, t0, t1, t2);
-    col_load(nb0, v);
-    __builtin_amdgcn_sched_barrier(0);
-    C u0, u1, u2, w[3][R];
-    link_load(4, u0, u1, u2);
-    const int there = __shfl(nb0, from);
+  if constexpr (BH > 0) {
+    // small launches, bound by the latency of the loads: BH hops' at once
+#pragma unroll 1
+    for (int k0 = 0; k0 < NL; k0 += BH) {
+      C t0[BH], t1[BH], t2[BH], v[BH][3][R];
 #pragma unroll
-    for (int cb = 0; cb < 3; ++cb)
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        w[cb][r].x = __shfl(v[cb][r].x, from);
-        w[cb][r].y = __shfl(v[cb][r].y, from);
+      for (int h = 0; h < BH; ++h) {
+        link_load(k0 + h, t0[h], t1[h], t2[h]);
+        col_load(neighbour_cb((int)s, c, g, (k0 + h) & 3, hop_dist(k0 + h)), v[h]);
       }
-    if (!((lane >= 4 || full) && there == nb4)) col_load(nb4, w);
-    accumulate(0, v, t0, t1, t2);
-    accumulate(4, w, u0, u1, u2);
-  }
-  // The other hops: every load of a hop (three link elements, 3R input
-  // columns) is issued before any of them is used; the scheduling barrier
-  // keeps the scheduler from spreading them next to their uses, which leaves
-  // about two in flight.
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < BH; ++h) accumulate(k0 + h, v[h], t0[h], t1[h], t2[h]);
+    }
+  } else {
+    // The two x hops first. Along an x-row the -x neighbour of a site is the
+    // +x neighbour of the site before it (with the row's wrap, of the row's
+    // last site), so where the wave holds that site (four lanes down, the same
+    // q) the -x columns come from its +x columns by cross-lane moves instead of
+    // a second read from L2; the other lanes (first site of the wave, rows that
+    // do not fill the wave) load them.
+    {
+      const int lane = (int)(threadIdx.x & 63);
+      const bool full = blockIdx.x * blockDim.x + (threadIdx.x & ~63u) + 64 <= (uint32_t)g.vh * 4;
+      const int from = (lane - 4) & 63;
+      const int nb0 = neighbour_cb((int)s, c, g, 0, 1), nb4 = neighbour_cb((int)s, c, g, 0, -1);
+      C t0, t1, t2, v[3][R];
+      link_load(0, t0, t1, t2);
+      col_load(nb0, v);
+      __builtin_amdgcn_sched_barrier(0);
+      C u0, u1, u2, w[3][R];
+      link_load(4, u0, u1, u2);
+      const int there = __shfl(nb0, from);
+#pragma unroll
+      for (int cb = 0; cb < 3; ++cb)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          w[cb][r].x = __shfl(v[cb][r].x, from);
+          w[cb][r].y = __shfl(v[cb][r].y, from);
+        }
+      if (!((lane >= 4 || full) && there == nb4)) col_load(nb4, w);
+      accumulate(0, v, t0, t1, t2);
+      accumulate(4, w, u0, u1, u2);
+    }
+    // The other hops: every load of a hop (three link elements, 3R input
+    // columns) is issued before any of them is used; the scheduling barrier
+    // keeps the scheduler from spreading them next to their uses, which leaves
+    // about two in flight.
 #pragma unroll 2
-  for (int kk = 0; kk < NL - 2; ++kk) {
-    const int k = kk + (kk < 3 ? 1 : 2);
-    const int nb = neighbour_cb((int)s, c, g, k & 3, hop_dist(k));
-    C t0, t1, t2, v[3][R];
-    link_load(k, t0, t1, t2);
-    col_load(nb, v);
-    __builtin_amdgcn_sched_barrier(0);
-    accumulate(k, v, t0, t1, t2);
+    for (int kk = 0; kk < NL - 2; ++kk) {
+      const int k = kk + (kk < 3 ? 1 : 2);
+      const int nb = neighbour_cb((int)s, c, g, k & 3, hop_dist(k));
+      C t0, t1, t2, v[3][R];
+      link_load(k, t0, t1, t2);
+      col_load(nb, v);
+      __builtin_amdgcn_sched_barrier(0);
+      accumulate(k, v, t0, t1, t2);
+    }
   }
   const size_t o = (size_t)s * 3 * n + j0;
 #pragma unroll
@@ -803,10 +847,36 @@ static HopTiles hop_tiles(const bms_ctx* c, int spb, int ty, int tz, int tt) {
   return m;
 }
 
+namespace {
+// Work-group size and batching of a launch. Measured per half hop (FP64 / FP32): 256 threads
+// and two hops in flight against a wave and a batch, 8^4 n = 4 6.4 -> 4.8 us (5.9 -> 4.5),
+// n = 8 7.6 -> 5.7 (6.8 -> 5.3), 4^4 n = 1 4.7 -> 3.9; the batch stops paying between one
+// wave per SIMD and two (16^4, n = 8 FP64: 14.0 with it, 13.4 without). Waves as
+// work-groups go round the XCDs in steps of 16 sites instead of 64, so that on the extents
+// of such lattices a site's z and t neighbours tend to be on its own XCD: 16^3 x 32 n = 16
+// 54 -> 42 us, with tiles 40 (FP32 26.7 -> 24.4, 23); from 20^4 on the two are even or 256 is
+// better (24^4 n = 8 79 against 87). The per-group kernel gains less and earlier turns (n = 12
+// at 16^4 25.0 -> 24.2, at 16^3 x 32 49 -> 53).
+struct HopSmall {
+  int wg;
+  bool batch;
+};
+HopSmall hop_small(const bms_ctx* c, int n, bool quad) {
+  const int R = (n % 4 == 0) ? 4 : ((n % 2 == 0) ? 2 : 1);
+  const long waves = (long)c->vh * (quad ? 4 : n / R) / 64;
+  const long simds = 4L * (c->num_cu > 0 ? c->num_cu : 256);
+  HopSmall h;
+  h.wg = (quad ? c->vh <= 64 * simds : waves <= 2 * simds) ? 64 : BMS_WG;
+  h.batch = waves <= simds;
+  return h;
+}
+}  // namespace
+
 bool hop_tiling_valid(const bms_ctx* c, int n, int ty, int tz, int tt) {
   const bool quad = n == 4 || n == 8 || n == 16 || n == 32;
   const int R = (n % 4 == 0) ? 4 : ((n % 2 == 0) ? 2 : 1);
-  const int spb = quad ? BMS_WG / 4 : (BMS_WG % (n / R) == 0 ? BMS_WG / (n / R) : 0);
+  const int wg = hop_small(c, n, quad).wg;
+  const int spb = quad ? wg / 4 : (wg % (n / R) == 0 ? wg / (n / R) : 0);
   return spb > 0 && hop_tiles(c, spb, ty, tz, tt).on != 0;
 }
 
@@ -838,6 +908,17 @@ HopPlan hop_plan(const bms_ctx* c, int n, bool fp64) {
   // inside each XCD's L2 (at 32^4 FP64 n = 16 513 -> 455 us natural order).
   p.cap = hc.cap >= 0 ? hc.cap : (n >= 16 ? 2 : (n == 8 ? 3 : 0));
   p.nt = hc.nt > 0;
+  // Small launches: a wave per work-group, and up to one wave per SIMD also more hops in
+  // flight (hop_small); the default traversal there is natural, but 8 x 4 x 4 tiles at the
+  // widths whose columns do not stay in L2 (n >= 8 in FP64, 16 in FP32).
+  const HopSmall sm = hop_small(c, n, p.quad);
+  p.wg = sm.wg;
+  p.batch = sm.batch && !p.nt;
+  if (p.wg == 64 && hc.ty < 0 && hv < 2) {
+    p.tiled = hv < 0 && p.quad && n >= (fp64 ? 8 : 16);
+    p.tz = 4;
+  }
+  if (p.wg == 64 && hc.cap < 0) p.cap = 0;
   // Variant 4 (n = 16, whole groups of 16 sites over 8 XCDs): the streamed
   // kernel, tiled unless the configuration asks for the natural order; the
   // configuration's cap is its ring depth (2 or 4 slots per wave; the
@@ -920,29 +1001,33 @@ hipError_t launch_hop(const bms_ctx* c, int par, int n, const void* in, void* ou
 #undef HOPS
     return hipGetLastError();
   }
-  const size_t lds = hop_cap_lds(c, hp.cap);
+  const unsigned wg = (unsigned)hp.wg;
+  // the cap counts work-groups of BMS_WG threads
+  const size_t lds = hop_cap_lds(c, hp.cap * BMS_WG / hp.wg);
   if (hp.quad) {
-    dim3 qgrid((4u * (uint32_t)c->vh + BMS_WG - 1) / BMS_WG);
-    HopTiles tiles = hp.tiled ? hop_tiles(c, BMS_WG / 4, hp.ty, hp.tz, hp.tt) : HopTiles{};
-#define HOPQ(RR, NT, NL, EPL)                                                              \
-  k_hop_q<T, RR, NT, NL, EPL><<<qgrid, BMS_WG, lds, c->stream>>>(                          \
+    dim3 qgrid((4u * (uint32_t)c->vh + wg - 1) / wg);
+    HopTiles tiles = hp.tiled ? hop_tiles(c, wg / 4, hp.ty, hp.tz, hp.tt) : HopTiles{};
+#define HOPQ(RR, NT, NL, EPL, BH)                                                          \
+  k_hop_q<T, RR, NT, NL, EPL, BH><<<qgrid, wg, lds, c->stream>>>(                          \
       links, (const cplx<T>*)in, (cplx<T>*)out, (const cplx<T>*)aux, (T)a, (T)b, c->geom,  \
       n, par, c->sbl, skip, tiles, sgn)
-#define HOPQN(RR)                                   \
-  if (c->nlinks == 16) {                            \
-    if (hp.nt)                                      \
-      HOPQ(RR, true, 16, 9);                        \
-    else                                            \
-      HOPQ(RR, false, 16, 9);                       \
-  } else if (two) {                                 \
-    if (hp.nt)                                      \
-      HOPQ(RR, true, 8, 6);                         \
-    else                                            \
-      HOPQ(RR, false, 8, 6);                        \
-  } else if (hp.nt)                                 \
-    HOPQ(RR, true, 8, 9);                           \
-  else                                              \
-    HOPQ(RR, false, 8, 9)
+#define HOPQB(RR, NL, EPL)                                                \
+  do {                                                                    \
+    constexpr int bh = hop_batch<T>(EPL == 6 ? 2 : 3, 3 * RR);            \
+    if (hp.batch && bh > 0)                                               \
+      HOPQ(RR, false, NL, EPL, bh);                                       \
+    else if (hp.nt)                                                       \
+      HOPQ(RR, true, NL, EPL, 0);                                         \
+    else                                                                  \
+      HOPQ(RR, false, NL, EPL, 0);                                        \
+  } while (0)
+#define HOPQN(RR)          \
+  if (c->nlinks == 16)     \
+    HOPQB(RR, 16, 9);      \
+  else if (two)            \
+    HOPQB(RR, 8, 6);       \
+  else                     \
+    HOPQB(RR, 8, 9)
     switch (n) {
       case 4: HOPQN(1); break;
       case 8: HOPQN(2); break;
@@ -950,36 +1035,39 @@ hipError_t launch_hop(const bms_ctx* c, int par, int n, const void* in, void* ou
       default: HOPQN(8);
     }
 #undef HOPQN
+#undef HOPQB
 #undef HOPQ
     return hipGetLastError();
   }
   const int R = (n % 4 == 0) ? 4 : ((n % 2 == 0) ? 2 : 1);
   uint32_t ngrp = (uint32_t)(n / R);
   uint32_t nthr = (uint32_t)c->vh * ngrp;
-  dim3 grid((nthr + BMS_WG - 1) / BMS_WG);
+  dim3 grid((nthr + wg - 1) / wg);
   FastDiv dg = make_fastdiv(ngrp);
-  HopTiles tiles = hp.tiled && BMS_WG % ngrp == 0
-                       ? hop_tiles(c, BMS_WG / (int)ngrp, hp.ty, hp.tz, hp.tt)
+  HopTiles tiles = hp.tiled && wg % ngrp == 0
+                       ? hop_tiles(c, (int)(wg / ngrp), hp.ty, hp.tz, hp.tt)
                        : HopTiles{};
-#define HOP_LAUNCH(RR, NT, NL, EPL)                                                        \
-  k_hop<T, RR, NT, NL, EPL><<<grid, BMS_WG, lds, c->stream>>>(                             \
+#define HOP_LAUNCH(RR, NT, NL, EPL, BH)                                                    \
+  k_hop<T, RR, NT, NL, EPL, BH><<<grid, wg, lds, c->stream>>>(                             \
       links, (const cplx<T>*)in, (cplx<T>*)out, (const cplx<T>*)aux, (T)a, (T)b, c->geom,  \
       n, dg, par, c->sbl, skip, tiles, sgn)
-#define HOPN(RR)                                    \
-  if (c->nlinks == 16) {                            \
-    if (hp.nt)                                      \
-      HOP_LAUNCH(RR, true, 16, 9);                  \
-    else                                            \
-      HOP_LAUNCH(RR, false, 16, 9);                 \
-  } else if (two) {                                 \
-    if (hp.nt)                                      \
-      HOP_LAUNCH(RR, true, 8, 6);                   \
-    else                                            \
-      HOP_LAUNCH(RR, false, 8, 6);                  \
-  } else if (hp.nt)                                 \
-    HOP_LAUNCH(RR, true, 8, 9);                     \
-  else                                              \
-    HOP_LAUNCH(RR, false, 8, 9)
+#define HOPB(RR, NL, EPL)                                    \
+  do {                                                       \
+    constexpr int bh = hop_batch<T>(EPL, 3 * RR);            \
+    if (hp.batch && bh > 0)                                  \
+      HOP_LAUNCH(RR, false, NL, EPL, bh);                    \
+    else if (hp.nt)                                          \
+      HOP_LAUNCH(RR, true, NL, EPL, 0);                      \
+    else                                                     \
+      HOP_LAUNCH(RR, false, NL, EPL, 0);                     \
+  } while (0)
+#define HOPN(RR)           \
+  if (c->nlinks == 16)     \
+    HOPB(RR, 16, 9);       \
+  else if (two)            \
+    HOPB(RR, 8, 6);        \
+  else                     \
+    HOPB(RR, 8, 9)
   if (R == 4)
     HOPN(4);
   else if (R == 2)
@@ -987,6 +1075,7 @@ hipError_t launch_hop(const bms_ctx* c, int par, int n, const void* in, void* ou
   else
     HOPN(1);
 #undef HOPN
+#undef HOPB
 #undef HOP_LAUNCH
   return hipGetLastError();
 }

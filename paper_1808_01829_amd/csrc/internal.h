@@ -86,6 +86,8 @@ struct HopCfg {
 struct HopPlan {
   bool quad = false, tiled = false, nt = false;
   int ty = 8, tz = 8, tt = 4, cap = 0;
+  int wg = BMS_WG;      // threads per work-group: BMS_WG, or 64 in small launches
+  bool batch = false;   // more hops in flight per thread (the smallest launches)
   bool stream = false;  // k_hop_s: persistent waves with `depth` hops in flight
   int depth = 0;
 };
