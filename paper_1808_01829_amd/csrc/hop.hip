@@ -313,6 +313,7 @@ __global__ __launch_bounds__(BMS_WG) void k_hop(const cplx<T>* __restrict__ link
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int h = 0; h < BH; ++h) accumulate(k0 + h, l[h], v[h]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   } else {
 #pragma unroll 2
@@ -423,18 +424,25 @@ __global__ __launch_bounds__(BMS_WG) void k_hop_q(const cplx<T>* __restrict__ li
       for (int r = 0; r < R; ++r) v[cb][r] = src[cb * n + r * cstep];
   };
   if constexpr (BH > 0) {
-    // small launches, bound by the latency of the loads: BH hops' at once
-#pragma unroll 1
+    // small launches, bound by the latency of the loads: BH hops' at once, in the order of
+    // the other form (the two x hops first), so that the sums are the same
+    // (two-row links: unrolled, so that every direction is a constant; the other forms' two
+    // batches would spill)
+    constexpr int UB = EPL == 6 ? 2 : 1;
+    auto hop_no = [](int i) { return i == 1 ? 4 : (i > 1 && i < 5 ? i - 1 : i); };
+#pragma unroll UB
     for (int k0 = 0; k0 < NL; k0 += BH) {
       C t0[BH], t1[BH], t2[BH], v[BH][3][R];
 #pragma unroll
       for (int h = 0; h < BH; ++h) {
-        link_load(k0 + h, t0[h], t1[h], t2[h]);
-        col_load(neighbour_cb((int)s, c, g, (k0 + h) & 3, hop_dist(k0 + h)), v[h]);
+        const int k = hop_no(k0 + h);
+        link_load(k, t0[h], t1[h], t2[h]);
+        col_load(neighbour_cb((int)s, c, g, k & 3, hop_dist(k)), v[h]);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int h = 0; h < BH; ++h) accumulate(k0 + h, v[h], t0[h], t1[h], t2[h]);
+      for (int h = 0; h < BH; ++h) accumulate(hop_no(k0 + h), v[h], t0[h], t1[h], t2[h]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   } else {
     // The two x hops first. Along an x-row the -x neighbour of a site is the
