@@ -102,6 +102,7 @@ int ensure_device(bms_ctx* c) {
 int stream_begin(bms_ctx* c) {
   int rc = ensure_device(c);
   if (rc) return rc;
+  c->ordered = false;
   HIP_TRY(c, hipEventRecord(c->ev_in, c->user_stream));
   HIP_TRY(c, hipStreamWaitEvent(c->stream, c->ev_in, 0));
   return BMS_OK;
@@ -111,7 +112,16 @@ int stream_begin(bms_ctx* c) {
 int stream_end(bms_ctx* c) {
   HIP_TRY(c, hipEventRecord(c->ev_out, c->stream));
   HIP_TRY(c, hipStreamWaitEvent(c->user_stream, c->ev_out, 0));
+  c->ordered = true;
   return BMS_OK;
+}
+
+// the library's device state, and the caller's stream ordered after the library's (it
+// is, unless the last call failed on the way)
+int user_stream_begin(bms_ctx* c) {
+  int rc = ensure_device(c);
+  if (rc) return rc;
+  return c->ordered ? BMS_OK : stream_end(c);
 }
 
 int ensure_buf(bms_ctx* c, DevBuf& b, size_t bytes) {
@@ -139,7 +149,8 @@ int scratch_buf(bms_ctx* c, int slot, size_t bytes, void** p) {
 
 extern "C" int bms_destroy(bms_ctx* c) {
   if (!c) return BMS_EINVAL;
-  // teardown: a failing release cannot be reported past this point
+  // teardown: a failing release cannot be reported past this point. (hipFree waits for
+  // the device, so for work on the caller's stream too; that stream may be gone by now.)
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
   if (c->links64.p) (void)hipFree(c->links64.p);
@@ -159,8 +170,9 @@ extern "C" int bms_destroy(bms_ctx* c) {
 extern "C" int bms_set_gauge(bms_ctx* c, const void* U) {
   if (!c) return BMS_EINVAL;
   if (!U) return set_err(c, BMS_EINVAL, "bms_set_gauge: U is NULL");
-  int rc = stream_begin(c);
+  int rc = user_stream_begin(c);
   if (rc) return rc;
+  UserStream us(c);
   c->gauge_set = false;  // a failure below leaves no links
   // (padding sites of the last block are never read)
   c->links_two_rows = false;
@@ -190,7 +202,7 @@ extern "C" int bms_set_gauge(bms_ctx* c, const void* U) {
   }
   c->nlinks = 8;
   c->gauge_set = true;
-  return stream_end(c);
+  return BMS_OK;
 }
 
 extern "C" int bms_set_link_rows(bms_ctx* c, int rows) {
@@ -213,8 +225,9 @@ extern "C" int bms_set_gauge_improved(bms_ctx* c, const void* V, const void* W) 
   for (int i = 0; i < 4; ++i)
     if (c->dims[i] < 4)
       return set_err(c, BMS_EINVAL, "the improved operator needs every extent >= 4");
-  int rc = stream_begin(c);
+  int rc = user_stream_begin(c);
   if (rc) return rc;
+  UserStream us(c);
   c->gauge_set = false;  // a failure below leaves no links
   size_t nlink = (size_t)2 * c->nblk * 144 << c->sbl;
   if ((rc = ensure_buf(c, c->links64, nlink * sizeof(double2)))) return rc;
@@ -224,7 +237,7 @@ extern "C" int bms_set_gauge_improved(bms_ctx* c, const void* V, const void* W) 
   c->link_dev = -1;
   c->nlinks = 16;
   c->gauge_set = true;
-  return stream_end(c);
+  return BMS_OK;
 }
 
 static int check_prec_op(bms_ctx* c, int prec) {
@@ -243,12 +256,13 @@ extern "C" int bms_apply_hop(bms_ctx* c, int parity_out, int n, const void* in, 
   int rc = check_prec_op(c, prec);
   if (rc) return rc;
   if (!c->gauge_set) return set_err(c, BMS_ESTATE, "no gauge field set");
-  if ((rc = stream_begin(c))) return rc;
+  if ((rc = user_stream_begin(c))) return rc;
+  UserStream us(c);
   if (prec == BMS_PREC_F64)
     HIP_TRY(c, launch_hop<double>(c, parity_out, n, in, out, nullptr, 0.0, 1.0, nullptr));
   else
     HIP_TRY(c, launch_hop<float>(c, parity_out, n, in, out, nullptr, 0.0, 1.0, nullptr));
-  return stream_end(c);
+  return BMS_OK;
 }
 
 extern "C" int bms_apply_mdagm(bms_ctx* c, double mass, double sigma, int n, const void* in,
@@ -261,10 +275,11 @@ extern "C" int bms_apply_mdagm(bms_ctx* c, double mass, double sigma, int n, con
   int rc = check_prec_op(c, prec);
   if (rc) return rc;
   if (!c->gauge_set) return set_err(c, BMS_ESTATE, "no gauge field set");
-  if ((rc = stream_begin(c))) return rc;
+  if ((rc = user_stream_begin(c))) return rc;
+  UserStream us(c);
   size_t es = prec == BMS_PREC_F64 ? sizeof(double2) : sizeof(float2);
   void* tmp;
-  if ((rc = scratch_buf(c, 0, (size_t)c->vh * 3 * n * es, &tmp))) return rc;
+  if ((rc = scratch_buf(c, S_TMP, (size_t)c->vh * 3 * n * es, &tmp))) return rc;
   double d = mass * mass + sigma;
   if (prec == BMS_PREC_F64) {
     HIP_TRY(c, launch_hop<double>(c, 1, n, in, tmp, nullptr, 0.0, 1.0, nullptr));
@@ -273,7 +288,7 @@ extern "C" int bms_apply_mdagm(bms_ctx* c, double mass, double sigma, int n, con
     HIP_TRY(c, launch_hop<float>(c, 1, n, in, tmp, nullptr, 0.0, 1.0, nullptr));
     HIP_TRY(c, launch_hop<float>(c, 0, n, tmp, out, in, d, -1.0, nullptr));
   }
-  return stream_end(c);
+  return BMS_OK;
 }
 
 extern "C" int bms_timing_enable(bms_ctx* c, int enable) {

@@ -420,7 +420,8 @@ extern "C" int bms_force(bms_ctx* c, int n, int ns, const double* alpha, const v
   if (c->nlinks != 8)
     return set_err(c, BMS_EINVAL, "the force is defined for the unimproved operator only");
   int rc;
-  if ((rc = stream_begin(c))) return rc;
+  if ((rc = user_stream_begin(c))) return rc;
+  UserStream us(c);
   const size_t blk = (size_t)c->vh * 3 * n;
   const bool fused = c->force_variant != 0;
   void* Y = nullptr;
@@ -486,5 +487,5 @@ extern "C" int bms_force(bms_ctx* c, int n, int ns, const double* alpha, const v
     (void)hipEventDestroy(ev[0]);
     (void)hipEventDestroy(ev[1]);
   }
-  return stream_end(c);
+  return BMS_OK;
 }

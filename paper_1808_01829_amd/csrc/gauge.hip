@@ -453,10 +453,10 @@ extern "C" int bms_gauge_action(bms_ctx* c, double beta, const void* U, double* 
   if (!c) return BMS_EINVAL;
   if (!U || !S) return set_err(c, BMS_EINVAL, "null pointer");
   if (!std::isfinite(beta)) return set_err(c, BMS_EINVAL, "beta not finite");
-  int rc = stream_begin(c);
+  int rc = user_stream_begin(c);
   if (rc) return rc;
-  if ((rc = gauge_action_dev(c, beta, U, S))) return rc;
-  return stream_end(c);
+  UserStream us(c);
+  return gauge_action_dev(c, beta, U, S);
 }
 
 extern "C" int bms_gauge_force(bms_ctx* c, double beta, const void* U, void* P, double scale) {
@@ -464,27 +464,27 @@ extern "C" int bms_gauge_force(bms_ctx* c, double beta, const void* U, void* P, 
   if (!U || !P) return set_err(c, BMS_EINVAL, "null pointer");
   if (!std::isfinite(beta) || !std::isfinite(scale))
     return set_err(c, BMS_EINVAL, "beta or scale not finite");
-  int rc = stream_begin(c);
+  int rc = user_stream_begin(c);
   if (rc) return rc;
-  if ((rc = gauge_force_dev(c, beta, U, P, scale))) return rc;
-  return stream_end(c);
+  UserStream us(c);
+  return gauge_force_dev(c, beta, U, P, scale);
 }
 
 extern "C" int bms_gauge_update(bms_ctx* c, double eps, const void* P, void* U) {
   if (!c) return BMS_EINVAL;
   if (!U || !P) return set_err(c, BMS_EINVAL, "null pointer");
   if (!std::isfinite(eps)) return set_err(c, BMS_EINVAL, "eps not finite");
-  int rc = stream_begin(c);
+  int rc = user_stream_begin(c);
   if (rc) return rc;
-  if ((rc = link_update_dev(c, eps, P, U))) return rc;
-  return stream_end(c);
+  UserStream us(c);
+  return link_update_dev(c, eps, P, U);
 }
 
 extern "C" int bms_kinetic_energy(bms_ctx* c, const void* P, double* K) {
   if (!c) return BMS_EINVAL;
   if (!P || !K) return set_err(c, BMS_EINVAL, "null pointer");
-  int rc = stream_begin(c);
+  int rc = user_stream_begin(c);
   if (rc) return rc;
-  if ((rc = kinetic_dev(c, P, K))) return rc;
-  return stream_end(c);
+  UserStream us(c);
+  return kinetic_dev(c, P, K);
 }

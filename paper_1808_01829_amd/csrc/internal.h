@@ -103,6 +103,7 @@ struct bms_ctx {
   hipStream_t user_stream = nullptr;
   hipStream_t stream = nullptr;  // library-owned work stream
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
+  bool ordered = true;  // everything on the library stream is ordered before user_stream
   int device = -1;
   int num_cu = 0;  // compute units of the device (set with the stream)
   int lds_per_cu = 0;  // bytes of LDS per compute unit (set with the stream)
@@ -166,6 +167,24 @@ int solve_validate(bms_ctx* c, double mass, int n, int ns, const double* shifts,
 int solve_reserve(bms_ctx* c, double mass, int n, int ns, const double* shifts, double tol,
                   int max_iter, const bms_opts* opts, const void* B, const void* X);
 int stream_end(bms_ctx* c);
+
+// The calls other than the solves enqueue their work on the caller's stream itself: while
+// a UserStream lives, c->stream is that stream (the launchers and ensure_buf use it).
+// Every call ends with the caller's stream ordered after the library's, and the solves order
+// the library's stream, which their graphs need, after the caller's first
+// (stream_begin), so going through it would only add two events and two waits to each call
+// (8 us of host time and the GPU's hand-over between queues: the 4^4 n = 1 operator took
+// 36 us against 10, 16^4 n = 8 in FP32 42 against 21). Use after user_stream_begin, and not
+// around ensure_device or a solve.
+int user_stream_begin(bms_ctx* c);
+struct UserStream {
+  bms_ctx* c;
+  hipStream_t own;
+  explicit UserStream(bms_ctx* ctx) : c(ctx), own(ctx->stream) { c->stream = c->user_stream; }
+  ~UserStream() { c->stream = own; }
+  UserStream(const UserStream&) = delete;
+  UserStream& operator=(const UserStream&) = delete;
+};
 
 // gauge-field steps of the RHMC trajectory (gauge.hip), on c->stream
 int gauge_action_dev(bms_ctx* c, double beta, const void* U, double* S);

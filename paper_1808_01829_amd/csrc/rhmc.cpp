@@ -74,7 +74,9 @@ int gauge_drift(Traj& t, double len) {
   const bms_rhmc_params& p = *t.p;
   const int m = p.n_gauge;
   const double g = len / m, lam = p.lambda;
-  int rc;
+  int rc = user_stream_begin(t.c);
+  if (rc) return rc;
+  UserStream us(t.c);
   if ((rc = gauge_force_dev(t.c, p.beta, t.U, t.P, lam * g))) return rc;
   for (int k = 0; k < m; ++k) {
     if ((rc = link_update_dev(t.c, 0.5 * g, t.P, t.U))) return rc;
@@ -86,9 +88,13 @@ int gauge_drift(Traj& t, double len) {
 }
 
 int energies(Traj& t, double* K, double* Sg, double* Sf) {
-  int rc;
-  if ((rc = kinetic_dev(t.c, t.P, K))) return rc;
-  if ((rc = gauge_action_dev(t.c, t.p->beta, t.U, Sg))) return rc;
+  int rc = user_stream_begin(t.c);
+  if (rc) return rc;
+  {
+    UserStream us(t.c);
+    if ((rc = kinetic_dev(t.c, t.P, K))) return rc;
+    if ((rc = gauge_action_dev(t.c, t.p->beta, t.U, Sg))) return rc;
+  }
   *Sf = 0;
   if (t.p->n > 0 && (rc = fermion_action(t, Sf))) return rc;
   return BMS_OK;
@@ -144,7 +150,7 @@ extern "C" int bms_rhmc_trajectory(bms_ctx* c, const bms_rhmc_params* p, void* U
       return set_err(c, BMS_EINVAL, "precision_md must be BMS_PREC_F64 or BMS_PREC_MIXED");
   }
   memset(r, 0, sizeof *r);
-  int rc = stream_begin(c);
+  int rc = user_stream_begin(c);
   if (rc) return rc;
   Traj t;
   t.c = c;
@@ -159,8 +165,11 @@ extern "C" int bms_rhmc_trajectory(bms_ctx* c, const bms_rhmc_params* p, void* U
   if (p->n > 0) {
     const size_t blk = (size_t)3 * c->vh * p->n;
     const int nsx = std::max(p->ns_hb, std::max(p->ns_acc, p->ns_md));
-    if ((rc = scratch_buf(c, S_PHI, blk * sizeof(double2), &t.phi))) return rc;
-    if ((rc = scratch_buf(c, S_XR, (size_t)nsx * blk * sizeof(double2), &t.X))) return rc;
+    {
+      UserStream us(c);
+      if ((rc = scratch_buf(c, S_PHI, blk * sizeof(double2), &t.phi))) return rc;
+      if ((rc = scratch_buf(c, S_XR, (size_t)nsx * blk * sizeof(double2), &t.X))) return rc;
+    }
     // heatbath phi = r_hb(A) eta
     if ((rc = bms_set_gauge(c, U))) return rc;
     bms_stats st;
@@ -186,5 +195,5 @@ extern "C" int bms_rhmc_trajectory(bms_ctx* c, const bms_rhmc_params* p, void* U
   r->H1 = r->K1 + r->Sg1 + r->Sf1;
   r->dH = r->H1 - r->H0;
   if (!std::isfinite(r->dH)) return set_err(c, BMS_ENAN, "non-finite energy in the trajectory");
-  return stream_end(c);
+  return BMS_OK;
 }

@@ -1082,9 +1082,10 @@ extern "C" int bms_rational_apply(bms_ctx* c, double mass, int n, int ns, double
     if (!std::isfinite(alpha[s])) return set_err(c, BMS_EINVAL, "alpha[%d] not finite", s);
   rc = bms_solve(c, mass, n, ns, shifts, tol, max_iter, opts, B, X, st);
   if (rc != BMS_OK) return rc;
-  if ((rc = stream_begin(c))) return rc;
+  if ((rc = user_stream_begin(c))) return rc;
+  UserStream us(c);
   HIP_TRY(c, launch_rational_combine(c->stream, (size_t)3 * c->vh * n, ns, a0, alpha, B, X, out));
-  return stream_end(c);
+  return BMS_OK;
 }
 
 extern "C" int bms_action(bms_ctx* c, int n, int ns, double a0, const double* alpha,
@@ -1095,7 +1096,8 @@ extern "C" int bms_action(bms_ctx* c, int n, int ns, double a0, const double* al
   if ((ns > 0 && (!alpha || !X)) || !B || !S) return set_err(c, BMS_EINVAL, "null pointer");
   if (!c->gauge_set) return set_err(c, BMS_ESTATE, "no gauge field set");
   int rc;
-  if ((rc = stream_begin(c))) return rc;
+  if ((rc = user_stream_begin(c))) return rc;
+  UserStream us(c);
   int rows = 3 * c->vh;
   void *al, *out, *pp;
   if ((rc = scratch_buf(c, S_RES, (size_t)(n + BMS_MAX_SHIFTS) * sizeof(double2) + 64, &out)))
@@ -1111,5 +1113,5 @@ extern "C" int bms_action(bms_ctx* c, int n, int ns, double a0, const double* al
   HIP_TRY(c, hipMemcpyAsync(h.data(), out, n * sizeof(double2), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   for (int i = 0; i < n; ++i) S[i] = h[i].x;
-  return stream_end(c);
+  return BMS_OK;
 }
