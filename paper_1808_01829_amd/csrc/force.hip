@@ -160,46 +160,60 @@ __global__ __launch_bounds__(BMS_WG) void k_force(ForceArgs a, int lpl) {
   for (int k = 0; k < 8; ++k) F[k] = a.add ? F[k] + fv[k] : fv[k];
 }
 
-// Quad sum by DPP: every lane of each group of four ends with the group's sum.
-__device__ __forceinline__ double dpp_xor1(double v) {
+// Sum over the four lanes of a row of 16 that are 4 apart, by DPP (row_ror:8, then row_ror:4
+// of what then repeats every 8 lanes): all four lanes end with the same sum.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
   long long u = __builtin_bit_cast(long long, v);
-  int lo = __builtin_amdgcn_mov_dpp((int)u, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
-  int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0xB1, 0xF, 0xF, false);
+  int lo = __builtin_amdgcn_mov_dpp((int)u, CTRL, 0xF, 0xF, false);
+  int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xF, 0xF, false);
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
-__device__ __forceinline__ double dpp_xor2(double v) {
-  long long u = __builtin_bit_cast(long long, v);
-  int lo = __builtin_amdgcn_mov_dpp((int)u, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
-  int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0x4E, 0xF, 0xF, false);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+__device__ __forceinline__ double2 dir_sum(double2 v) {
+  v.x += dpp_move<0x128>(v.x);
+  v.y += dpp_move<0x128>(v.y);
+  v.x += dpp_move<0x124>(v.x);
+  v.y += dpp_move<0x124>(v.y);
+  return v;
 }
-__device__ __forceinline__ double2 quad_sum(double2 v) {
-  v.x += dpp_xor1(v.x);
-  v.y += dpp_xor1(v.y);
-  v.x += dpp_xor2(v.x);
-  v.y += dpp_xor2(v.y);
+// sum over the four lanes of a quad (quad_perm [1,0,3,2], then [2,3,0,1])
+__device__ __forceinline__ double quad_sum(double v) {
+  v += dpp_move<0xB1>(v);
+  v += dpp_move<0x4E>(v);
   return v;
 }
 
 // Fused force, one odd site z per 16 lanes. Every link joins an odd and an
 // even site, so the links of z's forward hops (z, mu) and of its backward
-// hops (z - mu, mu) cover each link of the lattice once. Lane q = lane % 4
-// of the site owns direction mu = q, both links (as the half hop D_oe stores
-// them: 1/2 eta b U_mu(z) and -1/2 eta b' U_mu(z-mu)^dag); lane
-// g = (lane / 4) % 4 takes the flat columns c = g, g + 4, ... of the
+// hops (z - mu, mu) cover each link of the lattice once. Lane
+// q = (lane / 4) % 4 of the site owns direction mu = q, both links (as the
+// half hop D_oe stores them: 1/2 eta b U_mu(z) and -1/2 eta b' U_mu(z-mu)^dag);
+// lane g = lane % 4 takes the flat columns c = g, g + 4, ... of the
 // K = n * N_s columns (c = shift * n + column). Per column the four q-lanes
 // form their share of y(z) = (D_oe x)(z) from x(z + mu) and x(z - mu), add
-// the shares by DPP (a quad), and accumulate
+// the shares by DPP (a row of 16 lanes), and accumulate
 //   M_a += alpha x(z + mu) y(z)^dag     (link (z, mu),      z odd)
 //   M_b += alpha y(z) x(z - mu)^dag     (link (z - mu, mu), z - mu even),
 // so y never leaves the registers and each x load serves both. At the end the
 // four g-lanes add their partial 3 x 3 sums and write each link once.
 //
-// LDS_LINKS: the links wait in LDS (18 KB per work-group) instead of 72
-// registers, read back every column; the registers freed hold the x loads of
-// the next PF columns, issued before the current column is computed.
+// What bounds it is the rate of L1 accesses, then that of L2 reads. The column
+// group varies fastest over the lanes, so four neighbouring lanes read 64
+// consecutive bytes; with the direction fastest every lane read a line of its
+// own, and a load took 57 L1 accesses in place of 17 (2.3e8 against 7.0e7 at
+// 16^3 x 32, K = 128: 481 against 364 us). The 3.0e7 L2 reads that are left
+// run at 10.7 TB/s, near what L2 hands the CUs. Slower: blocks dealt to the
+// XCDs by slabs of the lattice (488), three waves a SIMD with one column in
+// flight (554).
+//
+// LDS_LINKS: the links wait in LDS (19 KB per work-group) instead of 72
+// registers, read back every step, each entry once for the PF columns of the
+// step; the registers freed hold the x loads of the next PF columns, issued
+// before the current ones are computed. A site's 72 entries lie kLinkPitch
+// apart: at 72 the four sites of a wave, and at 76 no two of them, read the
+// same banks.
 constexpr int kForceSites = BMS_WG / 16;  // odd sites per work-group
-constexpr int kLinkPitch = 8 * 9 + 1;     // complex per site in LDS (one pad)
+constexpr int kLinkPitch = 76;
 
 struct FCol {
   double2 va[3], vb[3];
@@ -210,7 +224,7 @@ template <int PF, bool LDS_LINKS, int WAVES>
 __global__ __launch_bounds__(BMS_WG, WAVES) void k_force_fused(ForceArgs a) {
   const Geom& g = a.g;
   const int lane = threadIdx.x & 63;
-  const int q = lane & 3, gl = (lane >> 2) & 3;
+  const int gl = lane & 3, q = (lane >> 2) & 3;
   const int sl = threadIdx.x >> 4;  // site within the work-group
   const uint32_t z0 = blockIdx.x * kForceSites + sl;
   const bool live = z0 < (uint32_t)g.vh;
@@ -270,75 +284,83 @@ __global__ __launch_bounds__(BMS_WG, WAVES) void k_force_fused(ForceArgs a) {
   const size_t blk = (size_t)g.vh * 3 * n;
   const double2* xf = a.X + (size_t)ef * 3 * n;
   const double2* xbk = a.X + (size_t)eb * 3 * n;
-  // load cursor: flat column c = j * n + i = 4 t + g. Every lane runs the
-  // same steps; columns past K load column 0 and add nothing.
-  const int T = (K + 3) >> 2;
-  int j = gl / n, i = gl - (gl / n) * n, c = gl;
-  auto load = [&](FCol& f) {
-    const bool valid = c < K;
-    const size_t o = valid ? (size_t)j * blk + i : 0;
+  // load cursor: flat column c = j * n + i, lane g taking columns 4 (PF t + u) + g (u < PF) in
+  // step t: the four lanes g of a site and direction read 64 consecutive bytes, and at PF = 2
+  // and n = 8 a step takes a colour's whole cache line. Every lane runs the same steps;
+  // columns past K load column 0 and add nothing.
+  const int T = (K + 4 * PF - 1) / (4 * PF);
+  int c = gl, j = gl / n, i = gl - (gl / n) * n;
+  auto load = [&](FCol (&f)[PF]) {
 #pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      f.va[b] = xf[o + (size_t)b * n];
-      f.vb[b] = xbk[o + (size_t)b * n];
-    }
-    f.al = valid ? a.alpha[valid ? j : 0] : 0.0;
-    c += 4;
-    i += 4;
-    while (i >= n) {
-      i -= n;
-      ++j;
+    for (int u = 0; u < PF; ++u) {
+      const bool valid = c < K;
+      const size_t o = valid ? (size_t)j * blk + i : 0;
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        f[u].va[b] = xf[o + (size_t)b * n];
+        f[u].vb[b] = xbk[o + (size_t)b * n];
+      }
+      f[u].al = valid ? a.alpha[valid ? j : 0] : 0.0;
+      c += 4;
+      i += 4;
+      while (i >= n) {
+        i -= n;
+        ++j;
+      }
     }
   };
   int lofs = sl * kLinkPitch + mu * 9;
-  auto compute = [&](const FCol& f) {
+  // PF columns at once: a link entry is read from LDS once for all of them
+  auto compute = [&](const FCol (&f)[PF]) {
     if (LDS_LINKS) {
-      // a fresh address every column keeps the LDS reads inside the loop
+      // a fresh address every time keeps the LDS reads inside the loop
       asm volatile("" : "+v"(lofs));
     }
-    double2 y[3];
+    double2 y[PF][3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
-      double2 t = make_double2(0, 0);
+      double2 t[PF];
+#pragma unroll
+      for (int u = 0; u < PF; ++u) t[u] = make_double2(0, 0);
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
         const double2 lfa = LDS_LINKS ? lds[lofs + 3 * r + b] : la[3 * r + b];
         const double2 lfb = LDS_LINKS ? lds[lofs + 36 + 3 * r + b] : lb[3 * r + b];
-        t = cfma(lfa, f.va[b], t);
-        t = cfma(lfb, f.vb[b], t);
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+          t[u] = cfma(lfa, f[u].va[b], t[u]);
+          t[u] = cfma(lfb, f[u].vb[b], t[u]);
+        }
       }
-      y[r] = cscale(quad_sum(t), f.al);
+#pragma unroll
+      for (int u = 0; u < PF; ++u) y[u][r] = cscale(dir_sum(t[u]), f[u].al);
     }
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
+    for (int u = 0; u < PF; ++u)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        ma[3 * r + b] = cjfma(y[b], f.va[r], ma[3 * r + b]);  // x_f[r] conj(y[b])
-        mb[3 * r + b] = cjfma(f.vb[b], y[r], mb[3 * r + b]);  // y[r] conj(x_b[b])
-      }
+      for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          ma[3 * r + b] = cjfma(y[u][b], f[u].va[r], ma[3 * r + b]);  // x_f[r] conj(y[b])
+          mb[3 * r + b] = cjfma(f[u].vb[b], y[u][r], mb[3 * r + b]);  // y[r] conj(x_b[b])
+        }
   };
   FCol buf[PF];
+  load(buf);
+  for (int t = 0; t < T; ++t) {
+    FCol cur[PF];
 #pragma unroll
-  for (int u = 0; u < PF; ++u) load(buf[u]);
-  for (int t = 0; t < T; t += PF) {
-#pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      const FCol cur = buf[u];
-      load(buf[u]);  // PF columns ahead
-      compute(cur);
-    }
+    for (int u = 0; u < PF; ++u) cur[u] = buf[u];
+    load(buf);  // a step ahead
+    compute(cur);
   }
-  // add the four column groups (lanes 4 and 8 apart)
+  // add the four column groups
 #pragma unroll
   for (int e = 0; e < 9; ++e) {
-    ma[e].x += __shfl_xor(ma[e].x, 4);
-    ma[e].y += __shfl_xor(ma[e].y, 4);
-    mb[e].x += __shfl_xor(mb[e].x, 4);
-    mb[e].y += __shfl_xor(mb[e].y, 4);
-    ma[e].x += __shfl_xor(ma[e].x, 8);
-    ma[e].y += __shfl_xor(ma[e].y, 8);
-    mb[e].x += __shfl_xor(mb[e].x, 8);
-    mb[e].y += __shfl_xor(mb[e].y, 8);
+    ma[e].x = quad_sum(ma[e].x);
+    ma[e].y = quad_sum(ma[e].y);
+    mb[e].x = quad_sum(mb[e].x);
+    mb[e].y = quad_sum(mb[e].y);
   }
   if (!live) return;
   // M_mu(z) = -eta b_f sum alpha x(z+mu) y(z)^dag ; M_mu(z-mu) = +eta b_e sum alpha y(z) x(z-mu)^dag
@@ -453,7 +475,7 @@ extern "C" int bms_force(bms_ctx* c, int n, int ns, const double* alpha, const v
   if (fused) {
     // 16 lanes per odd site. Variants: 1 links in registers, loads one
     // column ahead; 2 (default) links in LDS, loads two columns ahead.
-    // Measured at 16^3 x 32, K = 128: 511 and 499 us (hops + per-link
+    // Measured at 16^3 x 32, K = 128: 414 and 364 us (hops + per-link
     // kernel, variant 0: 998 us)
     const dim3 grid((c->vh + kForceSites - 1) / kForceSites);
     const int fv = c->force_variant < 0 ? 2 : c->force_variant;
