@@ -74,6 +74,9 @@ struct Mf<float> {
 
 // N: block width (8 or 16), or the largest width (12 or 16) the form for a width
 // known at run time takes. Widths above 8 take the three-product form below.
+// Waves and threads of a work-group of k_update_close.
+constexpr int CL_WAVES = 8, CL_THREADS = CL_WAVES * 64;
+
 template <int N>
 struct MfShape {
   static constexpr bool three = N > 8;
@@ -139,23 +142,23 @@ __device__ __forceinline__ V mfma3_im(const V (&d)[3]) {
 }
 
 // A-operand reals of one tile row (row r, reals g*KS .. g*KS+KS-1) in the
-// arithmetic type F. Rows past the end and columns past n read a valid entry and
-// are zeroed, with no branch around the loads (so the loads of several tiles stay
-// in flight).
+// arithmetic type F. Rows past the end read row 0 (a row only reaches its own results,
+// and those are not stored), with no branch around the loads and, at a fixed width, no
+// select behind them: a select waits for its load at once, and the loads of the next shift
+// would not be in flight while this one is computed. Columns past n are zeroed.
 template <int N, bool RT, typename F, typename C>
 __device__ __forceinline__ void aload(const C* base, int r, int rows, int nrt, int g,
                                       F (&a)[MfShape<N>::KS]) {
   using S = MfShape<N>;
   constexpr int KC = S::KS / 2;
   const int n = RT ? nrt : N;
-  const bool okr = r < rows;
-  const C* p = base + (size_t)(okr ? r : 0) * n + g * KC;
+  const C* p = base + (size_t)(r < rows ? r : 0) * n + g * KC;
 #pragma unroll
   for (int h = 0; h < KC; ++h) {
-    const bool okc = !RT || g * KC + h < n, ok = okr && okc;
+    const bool okc = !RT || g * KC + h < n;
     C v = p[okc ? h : -g * KC];
-    a[2 * h] = ok ? (F)v.x : (F)0;
-    a[2 * h + 1] = ok ? (F)v.y : (F)0;
+    a[2 * h] = okc ? (F)v.x : (F)0;
+    a[2 * h + 1] = okc ? (F)v.y : (F)0;
   }
 }
 
@@ -169,15 +172,13 @@ __device__ __forceinline__ void dload(const C* base, int r0, int rows, int nrt, 
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     const int r = r0 + Mf<F>::row(g, p);
-    const bool ok = r < rows && (!RT || c < n);
-    const size_t rr = ok ? (size_t)r : 0;
+    const size_t rr = r < rows ? (size_t)r : 0;
     if constexpr (MfShape<N>::three) {
       C v = base[rr * n + (!RT || c < n ? c : 0)];
-      d[0][p] = ok ? (F)v.x : (F)0;
-      d[1][p] = ok ? (F)v.y : (F)0;
+      d[0][p] = (F)v.x;
+      d[1][p] = (F)v.y;
     } else {
-      auto v = ((const decltype(C().x)*)base)[rr * 2 * N + 2 * (c % N) + c / N];
-      d[0][p] = ok ? (F)v : (F)0;
+      d[0][p] = (F)((const decltype(C().x)*)base)[rr * 2 * N + 2 * (c % N) + c / N];
     }
   }
 }
@@ -187,10 +188,11 @@ __device__ __forceinline__ void dstore(C* base, int r0, int rows, int nrt, int g
                                        const typename Mf<F>::V (&d)[MfShape<N>::NT]) {
   using R = decltype(C().x);
   const int n = RT ? nrt : N;
+  const bool whole = r0 + 16 <= rows;  // the same for the wave: no lane masks
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     const int r = r0 + Mf<F>::row(g, p);
-    if (r >= rows) continue;
+    if (!whole && r >= rows) continue;
     if constexpr (MfShape<N>::three) {
       C v;
       v.x = (R)d[0][p];
@@ -209,6 +211,23 @@ template <typename F>
 struct MfWin {
   static constexpr int MW = sizeof(F) == 8 ? 4 : 8;
 };
+
+// The shifts whose window this update applies (by lane, as a mask), and those of them
+// that k_update_close takes when it follows: windows of two iterations and more, if there
+// are kCloseMin of them at least (it reads Q_k and Q_{k+1} once more than k_update_mfma;
+// at 32^4, n = 16, one launch against the two: 2.15 and 1.92 ms in FP64, 1.65 and 1.59 in
+// FP32 with three such windows).
+constexpr int kCloseMin = 3;
+__device__ __forceinline__ unsigned long long windows_due(const SolverFlags* fl, int ns,
+                                                          int closing,
+                                                          unsigned long long& late) {
+  const int lane = threadIdx.x & 63, slot = fl->iter & 1;
+  const int j = lane < ns ? fl->win_j[slot][lane] : 0;
+  const bool due = j > 0 && (fl->win_flush[slot][lane] || fl->stop);
+  late = __ballot(due && closing && j > 1);
+  if (__popcll(late) < kCloseMin) late = 0;
+  return __ballot(due);
+}
 
 // F: block and shift-update arithmetic type (double, or float in the mixed
 // solver). NTILE: 16-row tiles per wave (processed one after the other inside
@@ -278,9 +297,9 @@ void k_update_mfma(UpdateArgs<F, F> a) {
   const CF* Qin = a.Qring + (size_t)(k % win) * blk;
   CF* Qout = a.Qring + (size_t)((k + 1) % win) * blk;
   const int tile0 = (blockIdx.x * MF_WAVES + wave) * NTILE;
-  unsigned long long mask =
-      __ballot(lane < ns && lane % gridDim.y == blockIdx.y && fl->win_j[slot][lane] > 0 &&
-               (fl->win_flush[slot][lane] || stop));
+  unsigned long long late;
+  unsigned long long mask = windows_due(fl, ns, a.closing, late);
+  mask &= ~late & __ballot(lane % gridDim.y == blockIdx.y);
   if (!lead && !mask) return;
 
   // coefficients of the Q step
@@ -432,6 +451,252 @@ void k_update_mfma(UpdateArgs<F, F> a) {
   }
 }
 
+// Rows r0 .. r0 + 15 of a block as a buffer: accesses past the last row read zero and
+// store nothing, so no access of the kernel below sits behind a branch. The waits for
+// loads in flight are counted in order with the stores, and a store that may not be
+// there would have to be waited for with the next load.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* base, int r0, int rows,
+                                                            int rowbytes) {
+  const int left = rows - r0;
+  const int nr = left < 0 ? 0 : (left < 16 ? left : 16);
+  const size_t p = (size_t)base + (size_t)(nr ? r0 : 0) * rowbytes;
+  const size_t lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)p);
+  const size_t hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(p >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(hi << 32 | lo), 0,
+                                           __builtin_amdgcn_readfirstlane(nr * rowbytes),
+                                           0x00027000);
+}
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+
+// aload, dload and dstore on such a tile
+template <int N, typename F>
+__device__ __forceinline__ void aload_b(__amdgpu_buffer_rsrc_t t, int g, int c,
+                                        F (&a)[MfShape<N>::KS]) {
+  constexpr int B = MfShape<N>::KS * (int)sizeof(F);  // bytes of a lane's run
+  typedef F fv __attribute__((ext_vector_type(16 / sizeof(F))));
+#pragma unroll
+  for (int h = 0; h < B / 16; ++h) {
+    const fv v = __builtin_bit_cast(
+        fv, __builtin_amdgcn_raw_buffer_load_b128(t, (4 * c + g) * B + 16 * h, 0, 0));
+#pragma unroll
+    for (int e = 0; e < (int)(16 / sizeof(F)); ++e) a[h * (int)(16 / sizeof(F)) + e] = v[e];
+  }
+}
+template <int N, typename F>
+__device__ __forceinline__ void dload_b(__amdgpu_buffer_rsrc_t t, int g, int c,
+                                        typename Mf<F>::V (&d)[MfShape<N>::NT]) {
+  typedef F f2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int o = Mf<F>::row(g, p) * 2 * N * (int)sizeof(F);
+    if constexpr (MfShape<N>::three) {
+      f2 v;
+      if constexpr (sizeof(F) == 8)
+        v = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b128(t, o + c * 16, 0, 0));
+      else
+        v = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(t, o + c * 8, 0, 0));
+      d[0][p] = v.x;
+      d[1][p] = v.y;
+    } else {
+      const int oc = o + (2 * (c % N) + c / N) * (int)sizeof(F);
+      if constexpr (sizeof(F) == 8)
+        d[0][p] = __builtin_bit_cast(F, __builtin_amdgcn_raw_buffer_load_b64(t, oc, 0, 0));
+      else
+        d[0][p] = __builtin_bit_cast(F, __builtin_amdgcn_raw_buffer_load_b32(t, oc, 0, 0));
+    }
+  }
+}
+template <int N, typename F>
+__device__ __forceinline__ void dstore_b(__amdgpu_buffer_rsrc_t t, int g, int c,
+                                         const typename Mf<F>::V (&d)[MfShape<N>::NT]) {
+  typedef F f2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int o = Mf<F>::row(g, p) * 2 * N * (int)sizeof(F);
+    if constexpr (MfShape<N>::three) {
+      const f2 v = {d[0][p], d[1][p]};
+      if constexpr (sizeof(F) == 8)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), t, o + c * 16, 0, 0);
+      else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), t, o + c * 8, 0, 0);
+    } else {
+      const int oc = o + (2 * (c % N) + c / N) * (int)sizeof(F);
+      const F v = d[0][p];
+      if constexpr (sizeof(F) == 8)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), t, oc, 0, 0);
+      else
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), t, oc, 0, 0);
+    }
+  }
+}
+
+// The windows that an update closes together (usually those of every shift but sigma_0),
+// after the launch above has formed Q_{k+1}; same products, same order of sums, same bits.
+//
+// In k_update_mfma each shift reads the ring tiles again (3 or 7 loads of a wave against
+// one each of P and X), 64 rows share a copy of the coefficients, and every wave waits for
+// these between shifts. Here a work-group of eight waves holds its 128 rows' ring tiles in
+// LDS for all shifts, and the coefficients of the next shift (in registers, then the other
+// half of their LDS buffer), its P tile and this shift's X are in flight while a shift is
+// computed. That fills the LDS of a compute unit at n = 16 (64 KiB coefficients, 96 KiB
+// ring; in FP32 Q_k stays in registers), so one work-group per compute unit walks the row
+// blocks. What bounds it then: HBM in FP64 (X and P of every shift read and written, 4.3 TB/s
+// of about 4.7), the matrix cores in FP32 (eight products a tile and window). Measured at
+// 32^4, n = 16, 20 shifts, full windows, both launches: FP64 9.8 -> 7.8 ms, FP32 8.0 -> 6.7;
+// at 16^4, n = 8, 16 shifts: FP64 268 -> 168 us, FP32 no gain (160 and 163: not taken). Slower: the window's
+// products unrolled (FP64 8.0, FP32 7.3), LDS operands read a product ahead (FP32 7.2).
+template <typename F, int N>
+__global__ __launch_bounds__(CL_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
+void k_update_close(UpdateArgs<F, F> a) {
+  using S = MfShape<N>;
+  using CF = cplx<F>;
+  using VF = typename Mf<F>::V;
+  constexpr int MW = MfWin<F>::MW;
+  // Q_k (whose A operand costs FP32 only N / 2 registers) stays in registers in FP32
+  constexpr bool QREG = sizeof(F) == 4;
+  constexpr int LR = QREG ? MW - 2 : MW - 1;        // ring tiles of a wave in LDS
+  constexpr int TB = 16 * N * (int)sizeof(CF);      // bytes of a tile
+  constexpr int FAM = MW * N * N * (int)sizeof(CF); // bytes of one coefficient family
+  constexpr int CR = 2 * FAM / 16 / CL_THREADS;     // 16-byte pieces of a shift per thread
+  constexpr int UPR = N * (int)sizeof(CF) / 16;     // 16-byte units of a row
+  constexpr int USH = UPR == 16 ? 0 : (UPR == 8 ? 1 : 2);
+  constexpr int RB = N * (int)sizeof(CF);           // bytes of a row
+  static_assert(CR * 16 * CL_THREADS == 2 * FAM && (UPR << USH) == 16, "shape");
+  __shared__ __align__(16) unsigned char lds[4 * FAM + CL_WAVES * LR * TB];
+  const SolverFlags* fl = a.flags;
+  if (fl->halted) return;
+  unsigned long long all;
+  windows_due(fl, a.ns, 1, all);
+  if (!all) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  const int rows = a.rows, win = a.win, k = fl->iter - 1, slot = fl->iter & 1;
+  const size_t blk = (size_t)rows * N;
+  unsigned char* ring = lds + 4 * FAM + wave * (LR * TB);
+  // lane s: the iterations in the window of shift s
+  const int jl = lane < a.ns ? fl->win_j[slot][lane] : 0;
+  auto wj = [&](int s) { return __builtin_amdgcn_readlane(jl, s); };
+  int jmax = 0;
+  for (unsigned long long m = all; m; m &= m - 1) jmax = max(jmax, wj(__ffsll((long long)m) - 1));
+
+  // coefficients of a shift: loaded by all threads a shift ahead, written to the buffer
+  // not in use when the shift before is done
+  u4 cr[CR];
+  auto cload = [&](int s) {
+    const unsigned char* wm = (const unsigned char*)(a.Wm + (size_t)s * 2 * BMS_MAX_WIN * N * N);
+#pragma unroll
+    for (int u = 0; u < CR; ++u) {
+      const int q = u * CL_THREADS + tid, f = q / (FAM / 16), o = (q % (FAM / 16)) * 16;
+      cr[u] = *(const u4*)(wm + (size_t)f * (BMS_MAX_WIN * N * N * sizeof(CF)) + o);
+    }
+  };
+  auto cstore = [&](int b) {
+#pragma unroll
+    for (int u = 0; u < CR; ++u) *(u4*)(lds + b * 2 * FAM + (u * CL_THREADS + tid) * 16) = cr[u];
+  };
+  const int sfirst = __ffsll((long long)all) - 1;
+  int buf = 0, s = sfirst, j = wj(s);
+  cload(s);
+  cstore(0);
+  __syncthreads();
+
+  F pa[S::KS];
+  aload_b<N>(tile_rsrc(a.P + (size_t)s * blk, (blockIdx.x * CL_WAVES + wave) * 16, rows, RB), g, c,
+             pa);
+  const int nblk = (rows + 16 * CL_WAVES - 1) / (16 * CL_WAVES);
+  for (int tb = blockIdx.x; tb < nblk; tb += gridDim.x) {
+    const int r0 = (tb * CL_WAVES + wave) * 16;
+    // the ring tiles Q_{k-m}, straight to LDS; rows past the end read row 0 (their results
+    // are not stored)
+    for (int m = QREG ? 1 : 0; m <= jmax - 2; ++m) {
+      const unsigned char* q = (const unsigned char*)(a.Qring + (size_t)((k - m) % win) * blk);
+#pragma unroll
+      for (int i = 0; i < TB / 1024; ++i) {
+        const int x = i * 64 + lane, r = x / UPR, u = (x % UPR) ^ ((r >> USH) & (UPR - 1));
+        const size_t row = r0 + r < rows ? r0 + r : 0;
+        __builtin_amdgcn_global_load_lds(
+            (glob_void*)(q + row * (N * sizeof(CF)) + u * 16),
+            (lds_void*)(ring + (m - (QREG ? 1 : 0)) * TB + i * 1024), 16, 0, 0);
+      }
+    }
+    F qk[QREG ? S::KS : 1];
+    if constexpr (QREG)
+      aload_b<N>(tile_rsrc(a.Qring + (size_t)(k % win) * blk, r0, rows, RB), g, c, qk);
+    VF qn[S::NT];
+    dload_b<N, F>(tile_rsrc(a.Qring + (size_t)((k + 1) % win) * blk, r0, rows, RB), g, c, qn);
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+    unsigned long long mask = all;
+    while (mask) {
+      mask &= mask - 1;
+      const int s2 = mask ? __ffsll((long long)mask) - 1 : sfirst, j2 = wj(s2);
+      cload(s2);
+      const __amdgpu_buffer_rsrc_t X = tile_rsrc(a.X + (size_t)a.xidx[s] * blk, r0, rows, RB);
+      const __amdgpu_buffer_rsrc_t P = tile_rsrc(a.P + (size_t)s * blk, r0, rows, RB);
+      VF xa[S::NT];
+      dload_b<N, F>(X, g, c, xa);
+      const F* bx = (const F*)(lds + buf * 2 * FAM);
+      const F* bp = (const F*)(lds + buf * 2 * FAM + FAM);
+      constexpr int NACC = S::three ? 3 : S::NT;
+      VF pn[NACC], dx[NACC];
+#pragma unroll
+      for (int nt = 0; nt < NACC; ++nt) {
+        pn[nt] = (S::three || nt >= S::NT) ? VF{0, 0, 0, 0} : qn[nt];
+        dx[nt] = VF{0, 0, 0, 0};
+      }
+      auto prod = [&](const F(&av)[S::KS], int m) {
+        if constexpr (S::three) {
+          mfma3<F, N, false>(dx, av, bx + m * 2 * N * N, N, g, c);
+          mfma3<F, N, false>(pn, av, bp + m * 2 * N * N, N, g, c);
+        } else {
+          mfma_acc_c<N>(dx, av, bx + m * 2 * N * N, g, c);
+          mfma_acc_c<N>(pn, av, bp + m * 2 * N * N, g, c);
+        }
+      };
+      auto rload = [&](int m, F(&av)[S::KS]) {
+        typedef F fv __attribute__((ext_vector_type(16 / sizeof(F))));
+        const unsigned char* p = ring + (m - (QREG ? 1 : 0)) * TB + c * (N * sizeof(CF));
+#pragma unroll
+        for (int h = 0; h < UPR / 4; ++h) {
+          const fv v = *(const fv*)(p + (((g * (UPR / 4) + h) ^ ((c >> USH) & (UPR - 1))) * 16));
+#pragma unroll
+          for (int e = 0; e < (int)(16 / sizeof(F)); ++e) av[h * (int)(16 / sizeof(F)) + e] = v[e];
+        }
+      };
+      const int rn = mask ? r0 : r0 + (int)gridDim.x * CL_WAVES * 16;
+      prod(pa, 0);
+      // the P tile of the next shift, or of the first shift of the next rows
+      aload_b<N>(tile_rsrc(a.P + (size_t)s2 * blk, rn, rows, RB), g, c, pa);
+      for (int m = j - 2; m >= (QREG ? 1 : 0); --m) {
+        F qa[S::KS];
+        rload(m, qa);
+        prod(qa, j - 1 - m);
+      }
+      if constexpr (QREG) prod(qk, j - 1);
+      if constexpr (S::three) {
+        xa[0] += mfma3_re(dx);
+        xa[1] += mfma3_im(dx);
+        const VF pst[S::NT] = {qn[0] + mfma3_re(pn), qn[1] + mfma3_im(pn)};
+        dstore_b<N, F>(X, g, c, xa);
+        dstore_b<N, F>(P, g, c, pst);
+      } else {
+#pragma unroll
+        for (int nt = 0; nt < S::NT; ++nt) xa[nt] += dx[nt];
+        dstore_b<N, F>(X, g, c, xa);
+        dstore_b<N, F>(P, g, c, pn);
+      }
+      cstore(buf ^ 1);
+      __syncthreads();
+      buf ^= 1;
+      s = s2;
+      j = j2;
+    }
+  }
+}
+
 // After the last iteration: every update window still open (the solve ended
 // without its update applying it) is applied to X,
 //   X += P Cx + sum_{i < j-1} Q_{k-j+2+i} Ex_i
@@ -567,7 +832,8 @@ __global__ __launch_bounds__(BMS_WG) void k_update_vec(UpdateArgs<F, F> a) {
 // Groups the shifts of an update are dealt to: as many as bring the launch to about
 // two work-groups per compute unit, so that a small lattice, whose rows alone leave most of
 // the chip idle while each work-group walks its shifts one after the other, spreads the
-// shifts too. UPD_GROUP_FIGURES
+// shifts too. Measured at 8^4, FP64, 16 shifts, full windows, one group and with this rule:
+// n = 4 23.3 and 12.8 us, n = 8 49.9 and 20.2, n = 16 114 and 40.
 int shift_groups(int blocks, int ns, int win) {
   if (win < 2) return 1;  // Q is updated in place
   return std::min(ns, std::max(1, 512 / blocks));
@@ -579,7 +845,17 @@ hipError_t launch_mf(hipStream_t st, const UpdateArgs<F, F>& a) {
   int waves = (tiles + NTILE - 1) / NTILE;
   int blocks = (waves + MF_WAVES - 1) / MF_WAVES;
   const dim3 grid(blocks, shift_groups(blocks, a.ns, a.win));
-  k_update_mfma<F, N, NTILE, RT><<<grid, BMS_WG, 0, st>>>(a);
+  UpdateArgs<F, F> b = a;
+  // where the rows alone fill the chip, the windows that close together go to their own
+  // kernel (FP32 at n = 8: no gain)
+  constexpr bool own = !RT && (N == 16 || sizeof(F) == 8);
+  b.closing = own && a.win > 2 && grid.y == 1;
+  k_update_mfma<F, N, NTILE, RT><<<grid, BMS_WG, 0, st>>>(b);
+  if constexpr (own)
+    if (b.closing) {
+      const int nblk = (a.rows + 16 * CL_WAVES - 1) / (16 * CL_WAVES);
+      k_update_close<F, N><<<std::min(nblk, 256), CL_THREADS, 0, st>>>(b);
+    }
   return hipGetLastError();
 }
 

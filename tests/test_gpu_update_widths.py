@@ -63,3 +63,31 @@ def test_update_widths_solve(n, mixed):
     X, st = ctx.solve(MASS, r.beta, to_dev(torch, B), tol=1e-10,
                       precision=bms.BMS_PREC_MIXED if mixed else bms.BMS_PREC_F64)
     assert O.true_residuals(dims, BC, U, MASS, r.beta, B, to_np(X)).max() <= 1e-10
+
+
+CLOSE_DIMS = (6, 14, 14, 10)  # 17640 rows: 1102.5 tiles of 16
+
+
+@pytest.mark.parametrize("n,k", [(8, 4), (8, 7), (16, 2), (16, 9), (16, 11)])
+def test_closed_windows_match_oracle_iterates(n, k):
+    torch = torch_gpu()
+    bms, ctx, U, B = _problem(torch, CLOSE_DIMS, n, 700 + n)
+    r = configs.workload_coefficients("c2")
+    oo = O.sbcgrq_lattice(CLOSE_DIMS, BC, U, MASS, r.beta, B, 1e-30, maxiter=k)
+    X, st = ctx.solve(MASS, r.beta, to_dev(torch, B), tol=1e-15, max_iter=k, max_refine=0,
+                      check_interval=8, raise_on_error=False)
+    X = to_np(X)
+    assert st["iterations"] == k
+    for s in range(len(r.beta)):
+        err = np.linalg.norm(X[s] - oo["X"][s]) / np.linalg.norm(oo["X"][s])
+        assert err <= 1e-11, (s, err)
+
+
+@pytest.mark.parametrize("n", [8, 16])
+def test_closed_windows_mixed_solve(n):
+    torch = torch_gpu()
+    bms, ctx, U, B = _problem(torch, CLOSE_DIMS, n, 800 + n)
+    r = configs.workload_coefficients("c2")
+    X, st = ctx.solve(0.2, r.beta, to_dev(torch, B), tol=1e-10,
+                      precision=bms.BMS_PREC_MIXED)
+    assert O.true_residuals(CLOSE_DIMS, BC, U, 0.2, r.beta, B, to_np(X)).max() <= 1e-10
