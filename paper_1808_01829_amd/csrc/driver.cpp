@@ -26,8 +26,8 @@ int* variant_slot(bms_ctx* c, int kernel) {
 // candidate variants of a kernel class for block width n (all accepted by
 // bms_set_variant; ones that do not apply fall back to a default kernel and
 // simply time like it)
-std::vector<int> candidates(int kernel, int n) {
-  const bool quad = n == 4 || n == 8 || n == 16 || n == 32;
+std::vector<int> candidates(const bms_ctx* c, int kernel, int n) {
+  const bool quad = hop_quad(c, n);
   const bool mf = n == 8 || n == 16;
   switch (kernel) {
     // -1 (the built-in default) picks per precision, which one fixed variant
@@ -224,7 +224,7 @@ extern "C" int bms_autotune(bms_ctx* c, double mass, int n, int ns, const double
   const int kinds[2] = {BMS_KERNEL_GRAM, BMS_KERNEL_UPDATE};
   for (int kind : kinds) {
     int* slot = variant_slot(c, kind);
-    std::vector<int> cand = candidates(kind, n);
+    std::vector<int> cand = candidates(c, kind, n);
     int best = *slot;
     double best_us = 1e300;
     for (int v : cand) {

@@ -238,6 +238,24 @@ constexpr int hop_batch(int entries, int columns) {
   return 8 * per <= 144 ? 8 : (4 * per <= 176 ? 4 : 0);
 }
 
+// The columns of thread g of the G threads of a site, R each: hop_col0 + hop_col(r). FP64:
+// g + G r, so that a load of the site's threads reads one run. FP32: consecutive (16-byte
+// loads of two), and in pairs, 2 (g + G (r/2)) and the next (the last of an odd R on its
+// own), at R = 3 and above 4. With 8 consecutive columns to a thread every lane of a load
+// was an L1 access of its own: n = 32 at 32^4 460 us, 355 in pairs (31.3 and 20.1 at 16^4).
+// At R = 4 what L2 hands the CUs binds as well, and pairs lose (n = 16, 32^4: 206 and 212).
+template <typename T, int R>
+constexpr bool kPairs = sizeof(T) == 4 && (R == 3 || R > 4);
+template <typename T, int R>
+__device__ __forceinline__ int hop_col0(int g) {
+  return sizeof(T) == 8 ? g : (kPairs<T, R> ? 2 * g : g * R);
+}
+template <typename T, int R>
+__device__ __forceinline__ int hop_col(int r, int g, int G) {
+  if (kPairs<T, R>) return r < (R & ~1) ? 2 * G * (r >> 1) + (r & 1) : G * r - g;
+  return sizeof(T) == 8 ? G * r : r;
+}
+
 // out(s) = b * sum_k L_k(s) in(nbr_k(s)) + a * aux(s) on n columns.
 // One thread per (site, column group g): the n/R threads of a site share its
 // links (the block operator reads each link once per n columns) and each link
@@ -245,8 +263,7 @@ constexpr int hop_batch(int entries, int columns) {
 // In FP64 the columns are interleaved this way, so that every load and store
 // instruction touches one contiguous run per site (the site's threads read
 // neighbouring columns) and a wave touches as few cache lines as the bytes
-// allow. In FP32 a thread's R columns are consecutive instead (g*R .. g*R+R-1),
-// which the compiler loads as 16-byte vectors.
+// allow. In FP32 see hop_col.
 // EPL: link entries stored, 9, or 6 for SU(3) links kept as two rows (the
 // third rebuilt from them and the site's sign mask `sgn`).
 // BH: hops whose loads are all in flight together (0: two hops, unrolled), see hop_batch.
@@ -273,9 +290,8 @@ __global__ __launch_bounds__(BMS_WG) void k_hop(const cplx<T>* __restrict__ link
     s = fdiv(tid, dgrp);
     grp = tid - s * ngrp;
   }
-  constexpr bool kInterleave = sizeof(T) == 8;
-  const int cstep = kInterleave ? (int)ngrp : 1;  // column stride of a thread
-  const int j0 = (int)grp * (kInterleave ? 1 : R);  // its first column
+  const int j0 = hop_col0<T, R>((int)grp);
+  auto col = [&](int r) { return hop_col<T, R>(r, (int)grp, (int)ngrp); };
   SiteCoord c = site_coords(s, g, par);
   C acc[3][R];
 #pragma unroll
@@ -293,7 +309,7 @@ __global__ __launch_bounds__(BMS_WG) void k_hop(const cplx<T>* __restrict__ link
 #pragma unroll
     for (int cb = 0; cb < 3; ++cb)
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[cb][r] = src[cb * n + r * cstep];
+      for (int r = 0; r < R; ++r) v[cb][r] = src[cb * n + col(r)];
   };
   auto accumulate = [&](int k, C (&l)[9], const C (&v)[3][R]) {
     if constexpr (EPL == 6) link_row2(l, (msk >> k) & 1);
@@ -330,7 +346,7 @@ __global__ __launch_bounds__(BMS_WG) void k_hop(const cplx<T>* __restrict__ link
   for (int a3 = 0; a3 < 3; ++a3)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      size_t oo = o + a3 * n + r * cstep;
+      size_t oo = o + a3 * n + col(r);
       out[oo] = aux ? cadd(cscale(aux[oo], a), cscale(acc[a3][r], b)) : cscale(acc[a3][r], b);
     }
 }
@@ -354,8 +370,7 @@ __device__ __forceinline__ double quad_bcast(double v) {
 // the site's links: for each hop, thread q of the site loads link elements q,
 // q+4 (and thread 0 element 8), a third of the link load instructions, and
 // element e reaches the other three threads of the quad by a DPP broadcast
-// from lane e % 4. Columns as in k_hop (interleaved in FP64, consecutive in
-// FP32).
+// from lane e % 4. Columns as in k_hop.
 // With links kept as two rows (EPL = 6) thread q loads entries q and 4 + q%2,
 // and every thread rebuilds the third row.
 // BH: as in k_hop; the batched form (small lattices) loads the -x columns like the others.
@@ -374,9 +389,8 @@ __global__ __launch_bounds__(BMS_WG) void k_hop_q(const cplx<T>* __restrict__ li
   const uint32_t s = tiles.on ? hop_first_site(tiles, g) + (threadIdx.x >> 2)
                               : (blockIdx.x * blockDim.x + threadIdx.x) >> 2;
   const int q = (int)(threadIdx.x & 3);
-  constexpr bool kInterleave = sizeof(T) == 8;
-  const int cstep = kInterleave ? 4 : 1;
-  const int j0 = kInterleave ? q : q * R;
+  const int j0 = hop_col0<T, R>(q);
+  auto col = [&](int r) { return hop_col<T, R>(r, q, 4); };
   // second and third entries this thread fetches: 9 entries, q + 4 and
   // (thread 0) 8, others repeat q + 4; 6 entries, 4 + q%2
   const int e1 = EPL == 6 ? 4 + (q & 1) : q + 4;
@@ -421,7 +435,7 @@ __global__ __launch_bounds__(BMS_WG) void k_hop_q(const cplx<T>* __restrict__ li
 #pragma unroll
     for (int cb = 0; cb < 3; ++cb)
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[cb][r] = src[cb * n + r * cstep];
+      for (int r = 0; r < R; ++r) v[cb][r] = src[cb * n + col(r)];
   };
   if constexpr (BH > 0) {
     // small launches, bound by the latency of the loads: BH hops' at once, in the order of
@@ -494,7 +508,7 @@ __global__ __launch_bounds__(BMS_WG) void k_hop_q(const cplx<T>* __restrict__ li
   for (int a3 = 0; a3 < 3; ++a3)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      size_t oo = o + a3 * n + r * cstep;
+      size_t oo = o + a3 * n + col(r);
       out[oo] = aux ? cadd(cscale(aux[oo], a), cscale(acc[a3][r], b)) : cscale(acc[a3][r], b);
     }
 }
@@ -880,8 +894,20 @@ HopSmall hop_small(const bms_ctx* c, int n, bool quad) {
 }
 }  // namespace
 
+// Whether the half hop takes four threads per site: the widths 4, 8, 16 and 32 always; 12, 20
+// and 24, where the threads of k_hop hold four columns and each load every link, from 1.5
+// waves per SIMD on. Measured k_hop / four threads, FP64 (FP32) us: n = 12 32^4 369 / 278
+// (222 / 169), 16^4 24.1 / 16.4 (15.0 / 11.9), 16^3 x 12 17.3 / 13.4; n = 20 and 24 at 16^4
+// 38 / 26 and 41 / 29. Below that k_hop has more waves, or its batch of hops in flight: n = 12
+// at 14^4 13.2 / 15.2, n = 24 at 12^4 15.1 / 16.8. (28 gains at 16^4 and loses at 20^4.)
+bool hop_quad(const bms_ctx* c, int n) {
+  const long simds = 4L * (c->num_cu > 0 ? c->num_cu : 256);
+  const bool pow2 = n == 4 || n == 8 || n == 16 || n == 32;
+  return pow2 || ((n == 12 || n == 20 || n == 24) && 4L * c->vh >= 96 * simds);
+}
+
 bool hop_tiling_valid(const bms_ctx* c, int n, int ty, int tz, int tt) {
-  const bool quad = n == 4 || n == 8 || n == 16 || n == 32;
+  const bool quad = hop_quad(c, n);
   const int R = (n % 4 == 0) ? 4 : ((n % 2 == 0) ? 2 : 1);
   const int wg = hop_small(c, n, quad).wg;
   const int spb = quad ? wg / 4 : (wg % (n / R) == 0 ? wg / (n / R) : 0);
@@ -902,11 +928,12 @@ HopPlan hop_plan(const bms_ctx* c, int n, bool fp64) {
   HopPlan p;
   const HopCfg& hc = c->hop_cfg[fp64 ? 0 : 1];
   const int hv = c->hop_variant;
-  p.quad = (n == 4 || n == 8 || n == 16 || n == 32) && (hv == 1 || hv == 3 || hv < 0);
+  p.quad = hop_quad(c, n) && (hv == 1 || hv == 3 || hv < 0);
   // tile extents: the configured ones, else 8 x 8 x 4; tiled for variants 2
   // and 3, or by the configuration (ty > 0; ty = 0 keeps the natural order),
-  // or by default in FP64 at n >= 16
-  const bool tiled_default = fp64 && n >= 16;
+  // or by default in FP64 at n >= 16 and 12
+  const bool quad12 = p.quad && n == 12;
+  const bool tiled_default = fp64 && (n >= 16 || quad12);
   p.tiled = hv == 2 || hv == 3 || (hv < 0 && (hc.ty > 0 || (hc.ty < 0 && tiled_default)));
   p.ty = hc.ty > 0 ? hc.ty : 8;
   p.tz = hc.ty > 0 ? hc.tz : 8;
@@ -914,7 +941,9 @@ HopPlan hop_plan(const bms_ctx* c, int n, bool fp64) {
   // At most `cap` resident work-groups per compute unit (by reserving LDS the
   // kernel does not use): fewer sites in flight keep the neighbours' re-reads
   // inside each XCD's L2 (at 32^4 FP64 n = 16 513 -> 455 us natural order).
-  p.cap = hc.cap >= 0 ? hc.cap : (n >= 16 ? 2 : (n == 8 ? 3 : 0));
+  // At n = 12 (32^4): FP64 294 us uncapped, 277 tiled with 2; FP32 175 and 169 with 3.
+  p.cap = hc.cap >= 0 ? hc.cap
+                      : (n >= 16 || (quad12 && fp64) ? 2 : (n == 8 || quad12 ? 3 : 0));
   p.nt = hc.nt > 0;
   // Small launches: a wave per work-group, and up to one wave per SIMD also more hops in
   // flight (hop_small); the default traversal there is natural, but 8 x 4 x 4 tiles at the
@@ -1021,7 +1050,8 @@ hipError_t launch_hop(const bms_ctx* c, int par, int n, const void* in, void* ou
       n, par, c->sbl, skip, tiles, sgn)
 #define HOPQB(RR, NL, EPL)                                                \
   do {                                                                    \
-    constexpr int bh = hop_batch<T>(EPL == 6 ? 2 : 3, 3 * RR);            \
+    constexpr bool pow2 = (RR & (RR - 1)) == 0; /* the others: never small */ \
+    constexpr int bh = pow2 ? hop_batch<T>(EPL == 6 ? 2 : 3, 3 * RR) : 0; \
     if (hp.batch && bh > 0)                                               \
       HOPQ(RR, false, NL, EPL, bh);                                       \
     else if (hp.nt)                                                       \
@@ -1039,7 +1069,10 @@ hipError_t launch_hop(const bms_ctx* c, int par, int n, const void* in, void* ou
     switch (n) {
       case 4: HOPQN(1); break;
       case 8: HOPQN(2); break;
+      case 12: HOPQN(3); break;
       case 16: HOPQN(4); break;
+      case 20: HOPQN(5); break;
+      case 24: HOPQN(6); break;
       default: HOPQN(8);
     }
 #undef HOPQN

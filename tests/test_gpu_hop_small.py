@@ -48,3 +48,11 @@ def test_small_hop(dims, widths, links):
         out = to_np(c.apply_mdagm(0.1, 0.2, to_dev(torch, v.astype(np.complex64)),
                                   bms.BMS_PREC_F32))[..., list(cols)]
         assert rel(out, ref) < 2e-6, n
+
+
+# 3, 5 and 6 columns a thread: four threads per site from 1.5 waves per SIMD on, the widths'
+# other form just below; and eight in single precision (pairs of columns).
+@pytest.mark.parametrize("dims", [(12, 16, 16, 16), (14, 16, 16, 14), (12, 16, 16, 14)])
+@pytest.mark.parametrize("links", ["two rows", "nine entries", "three-hop"])
+def test_four_threads_per_site(dims, links):
+    test_small_hop(dims, (12, 20, 24, 32), links)
