@@ -99,7 +99,7 @@ int tune_hop(bms_ctx* c, int n, bool fp64, double* best_us) {
   for (int v : {-1, 0}) {
     c->hop_variant = v;
     for (const auto& t : tiles) {
-      if (t[0] > 0 && !hop_tiling_valid(c, n, t[0], t[1], t[2])) continue;
+      if (t[0] > 0 && !hop_tiling_valid(c, n, fp64, t[0], t[1], t[2])) continue;
       for (int cap = 0; cap <= 4; ++cap)
         for (int nt = 0; nt <= 1; ++nt) {
           if (cap > 0 && hop_cap_lds(c, cap) == 0) continue;  // cap not applicable here

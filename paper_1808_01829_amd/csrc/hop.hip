@@ -879,14 +879,31 @@ namespace {
 // 54 -> 42 us, with tiles 40 (FP32 26.7 -> 24.4, 23); from 20^4 on the two are even or 256 is
 // better (24^4 n = 8 79 against 87). The per-group kernel gains less and earlier turns (n = 12
 // at 16^4 25.0 -> 24.2, at 16^3 x 32 49 -> 53).
+long hop_simds(const bms_ctx* c) { return 4L * (c->num_cu > 0 ? c->num_cu : 256); }
+
+// Columns of a thread of k_hop: 4, 2 or 1, as n divides, but fewer where that leaves under
+// half a wave per SIMD (FP32 down to one column: a quarter), and two at n = 12 with one-hop
+// links. Measured at 4 (or 2) columns and with this rule, FP64 (FP32) us: 8^4 n = 6 6.2 / 4.4
+// (5.4 / 4.3), n = 12 7.2 / 4.7 (6.2 / 4.4), n = 24 7.4 / 5.2; 12^4 n = 6 7.6 / 6.0, n = 12
+// 10.3 / 9.1 (7.7 / 6.6); 12 x 14 x 10 x 24 n = 12 16.3 / 14.5 (10.4 / 9.1). With more waves the
+// links, which every thread of a site loads, cost more than the waves give: n = 10 at 12^4
+// with 0.8 waves per SIMD at two columns 9.4 / 9.5 (6.5 / 7.4), three-hop links at n = 12,
+// 12 x 10 x 14 x 20, 24.7 / 29.7.
+int hop_columns(const bms_ctx* c, int n, bool fp64) {
+  const long simds = hop_simds(c);
+  int R = (n % 4 == 0) ? 4 : ((n % 2 == 0) ? 2 : 1);
+  if (n == 12 && c->nlinks == 8) R = 2;
+  while (R > 1 && (long)c->vh * (n / R) / 64 < (R == 2 && !fp64 ? simds / 4 : simds / 2)) R /= 2;
+  return R;
+}
+
 struct HopSmall {
   int wg;
   bool batch;
 };
-HopSmall hop_small(const bms_ctx* c, int n, bool quad) {
-  const int R = (n % 4 == 0) ? 4 : ((n % 2 == 0) ? 2 : 1);
-  const long waves = (long)c->vh * (quad ? 4 : n / R) / 64;
-  const long simds = 4L * (c->num_cu > 0 ? c->num_cu : 256);
+HopSmall hop_small(const bms_ctx* c, int n, bool quad, bool fp64) {
+  const long waves = (long)c->vh * (quad ? 4 : n / hop_columns(c, n, fp64)) / 64;
+  const long simds = hop_simds(c);
   HopSmall h;
   h.wg = (quad ? c->vh <= 64 * simds : waves <= 2 * simds) ? 64 : BMS_WG;
   h.batch = waves <= simds;
@@ -901,15 +918,15 @@ HopSmall hop_small(const bms_ctx* c, int n, bool quad) {
 // 38 / 26 and 41 / 29. Below that k_hop has more waves, or its batch of hops in flight: n = 12
 // at 14^4 13.2 / 15.2, n = 24 at 12^4 15.1 / 16.8. (28 gains at 16^4 and loses at 20^4.)
 bool hop_quad(const bms_ctx* c, int n) {
-  const long simds = 4L * (c->num_cu > 0 ? c->num_cu : 256);
+  const long simds = hop_simds(c);
   const bool pow2 = n == 4 || n == 8 || n == 16 || n == 32;
   return pow2 || ((n == 12 || n == 20 || n == 24) && 4L * c->vh >= 96 * simds);
 }
 
-bool hop_tiling_valid(const bms_ctx* c, int n, int ty, int tz, int tt) {
+bool hop_tiling_valid(const bms_ctx* c, int n, bool fp64, int ty, int tz, int tt) {
   const bool quad = hop_quad(c, n);
-  const int R = (n % 4 == 0) ? 4 : ((n % 2 == 0) ? 2 : 1);
-  const int wg = hop_small(c, n, quad).wg;
+  const int R = hop_columns(c, n, fp64);
+  const int wg = hop_small(c, n, quad, fp64).wg;
   const int spb = quad ? wg / 4 : (wg % (n / R) == 0 ? wg / (n / R) : 0);
   return spb > 0 && hop_tiles(c, spb, ty, tz, tt).on != 0;
 }
@@ -948,7 +965,7 @@ HopPlan hop_plan(const bms_ctx* c, int n, bool fp64) {
   // Small launches: a wave per work-group, and up to one wave per SIMD also more hops in
   // flight (hop_small); the default traversal there is natural, but 8 x 4 x 4 tiles at the
   // widths whose columns do not stay in L2 (n >= 8 in FP64, 16 in FP32).
-  const HopSmall sm = hop_small(c, n, p.quad);
+  const HopSmall sm = hop_small(c, n, p.quad, fp64);
   p.wg = sm.wg;
   p.batch = sm.batch && !p.nt;
   if (p.wg == 64 && hc.ty < 0 && hv < 2) {
@@ -1080,7 +1097,7 @@ hipError_t launch_hop(const bms_ctx* c, int par, int n, const void* in, void* ou
 #undef HOPQ
     return hipGetLastError();
   }
-  const int R = (n % 4 == 0) ? 4 : ((n % 2 == 0) ? 2 : 1);
+  const int R = hop_columns(c, n, sizeof(T) == 8);
   uint32_t ngrp = (uint32_t)(n / R);
   uint32_t nthr = (uint32_t)c->vh * ngrp;
   dim3 grid((nthr + wg - 1) / wg);

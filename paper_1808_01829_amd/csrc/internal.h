@@ -206,7 +206,7 @@ HopPlan hop_plan(const bms_ctx* c, int n, bool fp64);
 size_t hop_cap_lds(const bms_ctx* c, int cap);
 // whether ty x tz x tt tiles of whole x-rows divide this lattice for block width n
 bool hop_quad(const bms_ctx* c, int n);
-bool hop_tiling_valid(const bms_ctx* c, int n, int ty, int tz, int tt);
+bool hop_tiling_valid(const bms_ctx* c, int n, bool fp64, int ty, int tz, int tt);
 template <typename T>
 hipError_t launch_hop(const bms_ctx* c, int par, int n, const void* in, void* out, const void* aux,
                       double a, double b, const int* skip);

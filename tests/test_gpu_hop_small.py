@@ -56,3 +56,13 @@ def test_small_hop(dims, widths, links):
 @pytest.mark.parametrize("links", ["two rows", "nine entries", "three-hop"])
 def test_four_threads_per_site(dims, links):
     test_small_hop(dims, (12, 20, 24, 32), links)
+
+
+# One, two and four columns a thread of the per-group form, on either side of the lines
+# between them (half a wave per SIMD, a quarter in single precision).
+@pytest.mark.parametrize("dims,widths", [((8, 8, 8, 8), (2, 10, 12, 24)),
+                                         ((12, 12, 12, 12), (6, 10, 12, 24)),
+                                         ((12, 12, 12, 14), (6, 12, 20))])
+@pytest.mark.parametrize("links", ["two rows", "nine entries", "three-hop"])
+def test_columns_of_a_thread(dims, widths, links):
+    test_small_hop(dims, widths, links)
