@@ -15,7 +15,7 @@ struct UpdateArgs {
   const cplx<T>* W;           // [rows][n]  (A + s0) P^(0)
   const double2* alpha;       // n x n FP64
   const double2* rhoinv;      // n x n FP64
-  const double2* arho;        // n x n FP64: -alpha rho^-1 (n <= 16)
+  const double2* arho;        // n x n FP64: -alpha rho^-1
   cplx<T>* P;                 // [ns][rows][n] search directions, sorted shift order
   cplx<TX>* X;                // solutions; shift s at X + xidx[s]*rows*n
   const cplx<T>* Mx;          // [ns][n][n]
@@ -67,7 +67,7 @@ hipError_t launch_update_fast(hipStream_t st, const UpdateArgs<T, TX>& a, int va
 // matrix cores for n = 8 .. 16 (n = 8 and 16 with one or two 16-row tiles per wave), on the
 // vector units for n < 8
 bool update_mfma_supported(int n);  // n = 8, 16: the widths with a choice of kernels
-bool update_windowed(int n);        // n <= 16
+bool update_windowed(int n);        // n <= 32
 // The shifts s >= 1 are updated in windows of SmallParams::win iterations
 // (the small step gathers each window's coefficients, see SmallState::wst);
 // after the last iteration launch_update_drain applies every window still
@@ -78,7 +78,7 @@ template <typename F>
 hipError_t launch_update_drain(hipStream_t st, const UpdateArgs<F, F>& a);
 // longest window the matrix-core update of precision F stages in LDS
 template <typename F>
-int update_mfma_max_win();
+int update_mfma_max_win(int n);
 hipError_t launch_resid_norms(hipStream_t st, int rows, int n, const void* B, const void* Y,
                               double2* out, double2* partials, int nb);
 hipError_t launch_action(hipStream_t st, int rows, int n, int ns, double a0, const double* alpha,
@@ -112,7 +112,7 @@ struct SmallState {
   double2* rhob;    // [2][n*n]  rho_k
   double2* alpha;   // [n*n]     alpha_k
   double2* rhoinv;  // [n*n]     rho_k^-1
-  double2* arho;    // [n*n]     -alpha_k rho_k^-1 (n <= 16)
+  double2* arho;    // [n*n]     -alpha_k rho_k^-1
   double2* delta;   // [n*n]     delta_k (unshifted residual coefficients)
   double2* beta_s;  // [ns][n*n] beta^(s); for n <= 16: 1 - beta^(s)
   double2* alpha_s; // [ns][n*n] alpha^(s)

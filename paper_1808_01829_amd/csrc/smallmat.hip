@@ -441,6 +441,10 @@ __device__ void rho_part(const SmallParams& p, const SmallState& s, SolverFlags*
     sm_triinv_upper(T0, R, n);
     sm_store(s.rhoinv, T0, n);
     sm_store(s.rhob + cur * nn, R, n);
+    sm_load(T1, s.alpha, n);
+    sm_mm(D, T1, 0, T0, 0, n);  // alpha_k rho_k^-1
+    for (int e = threadIdx.x; e < nn; e += BMS_WG) s.arho[e] = make_double2(-D[e].x, -D[e].y);
+    __syncthreads();
     sm_load(T1, s.delta, n);
     sm_mm(D, R, 0, T1, 0, n);  // delta_k = rho_k delta_{k-1}
     sm_store(s.delta, D, n);

@@ -54,17 +54,17 @@ struct Work {
   int nb;
 };
 
-// Update window of the shifts s >= 1: the windowed update (n <= 16; at n = 8
+// Update window of the shifts s >= 1: the windowed update (at n = 8
 // and 16 variants -1, 4, 5) applies each shift's X and P updates once per window of
-// iterations; its length is the longest the kernel stages (4 in FP64, 8 in
-// FP32) that divides the chunk of iterations between host checks, so that
+// iterations; its length is the longest the kernel takes (4 in FP64, 8 in
+// FP32, 4 for n > 16) that divides the chunk of iterations between host checks, so that
 // every window closes at a chunk's end (where the mixed solver's reliable
 // update needs every X). Variant 6, the vector kernels and one shift: 1.
 int update_window(const bms_ctx* c, int n, int ns, int elem_bytes, int check_interval) {
   const int uv = c->update_variant;
   if (ns < 2 || !update_windowed(n)) return 1;
   if (update_mfma_supported(n) && !(uv < 0 || uv == 4 || uv == 5)) return 1;
-  int w = elem_bytes == 8 ? update_mfma_max_win<double>() : update_mfma_max_win<float>();
+  int w = elem_bytes == 8 ? update_mfma_max_win<double>(n) : update_mfma_max_win<float>(n);
   w = std::min(w, BMS_MAX_WIN);
   while (w > 1 && check_interval % w) w >>= 1;
   return w;
@@ -218,10 +218,11 @@ int enqueue_iteration(bms_ctx* c, const Work& w, const SmallParams& sp, double m
                                             (cplx<T>*)w.Wm));
   MARK(6);
   const UpdateArgs<T, T> ua = update_args<T>(w);
-  // the windowed kernels for n <= 16 (n = 8, 16: unless a vector variant is set), else the
-  // vector kernel
+  // the windowed kernels (n = 8, 16: unless a vector variant is set; n > 16: with a window),
+  // else the vector kernel
   const int uv = c->update_variant;
-  if (update_windowed(w.n) && (!update_mfma_supported(w.n) || uv < 0 || uv >= 4))
+  if (update_windowed(w.n) && (!update_mfma_supported(w.n) || uv < 0 || uv >= 4) &&
+      (w.n <= 16 || w.win > 1))
     HIP_TRY(c, launch_update_mfma<T>(c->stream, ua, uv == 5));
   else
     HIP_TRY(c, (launch_update_fast<T, T>(c->stream, ua, uv < 0 || uv >= 4 ? 2 : uv)));
@@ -486,11 +487,12 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
     double S = (double)w.blk * sizeof(cplx<T>);
     // matrix-core flops of one complex right product of a row block by an
     // n x n matrix: three real products for n > 8 (per 16-row tile 9 steps of
-    // 16 x 16 x 4 up to n = 12, then 12), one real product by the 2n x 2n form (rows (2n)^2
+    // 16 x 16 x 4 up to n = 12, then 12; 36 up to n = 24, then 48), one real product by the 2n x 2n form (rows (2n)^2
     // FMA) for n = 8
-    const double prod = n > 8 ? (n > 12 ? 1536.0 : 1152.0) * w.rows
-                              : 2.0 * w.rows * (2.0 * n) * (2.0 * n);
-    const bool mf = n >= 8 && update_windowed(n) &&
+    const double prod = n > 16  ? (n > 24 ? 6144.0 : 4608.0) * w.rows
+                        : n > 8 ? (n > 12 ? 1536.0 : 1152.0) * w.rows
+                                  : 2.0 * w.rows * (2.0 * n) * (2.0 * n);
+    const bool mf = n >= 8 && update_windowed(n) && (n <= 16 || w.win > 1) &&
                     (!update_mfma_supported(n) || c->update_variant < 0 || c->update_variant >= 4);
     for (int k = 0; k < hf.iter; ++k) {
       const double b = (units[k] & 0xffff) * S;

@@ -697,6 +697,168 @@ void k_update_close(UpdateArgs<F, F> a) {
   }
 }
 
+// The windowed update for 17 <= n <= 32 (N = 24 or 32): the products as in k_update_mfma, the
+// output columns in two halves of 16. The window's coefficients (up to 128 KiB at n = 32) pass
+// through LDS one iteration at a time, X and P family together; two work-groups share a
+// compute unit, and one computes while the other waits for its copy. Columns past n meet a
+// zero A operand, output columns past n are not used. On the matrix cores 2 x 2 x 3 N / 4
+// steps of 16 x 16 x 4 a tile, iteration and shift; X and P are moved once per window, where
+// the vector kernel for any n, which this replaces, moved them every iteration. Measured at
+// 16^4, 12 shifts, FP64, per iteration: n = 32 674 -> 205 us, n = 24 612 -> 182 (FP32 291 -> 77).
+template <typename F, int N>
+__global__ __launch_bounds__(BMS_WG) __attribute__((amdgpu_waves_per_eu(2)))
+void k_update_wide(UpdateArgs<F, F> a) {
+  using S = MfShape<N>;
+  using CF = cplx<F>;
+  using VF = typename Mf<F>::V;
+  constexpr int QREG = (N * N * 16 + 1023) / 1024 * 1024;               // an FP64 matrix
+  constexpr int SREG = (N * N * (int)sizeof(CF) + 1023) / 1024 * 1024;  // one in F
+  constexpr int TP = 64;                                                // reals of a tile's row
+  constexpr int TBYTES = sizeof(F) == 4 ? MF_WAVES * 16 * TP * 8 : 0;
+  constexpr int LBYTES = 2 * QREG + 512 > TBYTES ? 2 * QREG + 512 : TBYTES;
+  __shared__ __align__(16) unsigned char lds[LBYTES];
+  SolverFlags* fl = a.flags;
+  if (fl->halted) return;
+  const int tid = threadIdx.x;
+  const int iter = fl->iter, stop = fl->stop, slot = iter & 1;
+  const bool lead = blockIdx.y == 0;
+  if (lead && blockIdx.x == 0 && tid == 0) {
+    fl->upd_done = iter;
+    fl->upd_stop = stop;
+  }
+  if (lead && blockIdx.x == 0 && tid < 64) log_update(fl, a.upd_log, a.max_iter, a.ns);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  const int n = a.n, nn = n * n;
+  const int rows = a.rows, win = a.win, k = iter - 1;
+  const size_t blk = (size_t)rows * n;
+  const CF* Qin = a.Qring + (size_t)(k % win) * blk;
+  CF* Qout = a.Qring + (size_t)((k + 1) % win) * blk;
+  const int r0 = (blockIdx.x * MF_WAVES + wave) * 16;
+  unsigned long long late;
+  unsigned long long mask = windows_due(fl, a.ns, 0, late) &
+                            __ballot(lane % gridDim.y == blockIdx.y);
+  if (!lead && !mask) return;
+
+  lds_copy(a.rhoinv, lds, nn * 16, wave, lane);
+  lds_copy(a.arho, lds + QREG, nn * 16, wave, lane);
+  dx4 qd[2][2];  // [half][re, im]
+  {
+    double av[S::KS], wv[S::KS];
+    aload<N, true>(Qin, r0 + c, rows, n, g, av);
+    aload<N, true>(a.W, r0 + c, rows, n, g, wv);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      dx4 d3[3] = {dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}};
+      mfma3<double, N, true>(d3, av, (const double*)lds + 32 * h, n, g, c);
+      mfma3<double, N, true>(d3, wv, (const double*)(lds + QREG) + 32 * h, n, g, c);
+      qd[h][0] = mfma3_re(d3);
+      qd[h][1] = mfma3_im(d3);
+    }
+  }
+  // D layout of output half h: complex column 16 h + c of tile row Mf<>::row(g, p)
+  auto put = [&](CF* base, int r, int h, double re, double im) {
+    if (r < rows && 16 * h + c < n) {
+      CF v;
+      v.x = (F)re;
+      v.y = (F)im;
+      base[(size_t)r * n + 16 * h + c] = v;
+    }
+  };
+  if (lead) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        put(Qout, r0 + Mf<double>::row(g, p), h, qd[h][0][p], qd[h][1][p]);
+  }
+  __syncthreads();  // the Q-step LDS is reused below
+  VF qn[2][2];
+  if constexpr (sizeof(F) == 8) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      qn[h][0] = qd[h][0];
+      qn[h][1] = qd[h][1];
+    }
+  } else {
+    double* tq = (double*)lds + wave * (16 * TP);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          tq[Mf<double>::row(g, p) * TP + h * 32 + i * 16 + c] = qd[h][i][p];
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          qn[h][i][p] = (F)tq[Mf<F>::row(g, p) * TP + h * 32 + i * 16 + c];
+  }
+
+  const size_t fam = (size_t)BMS_MAX_WIN * nn;
+  for (; mask; mask &= mask - 1) {
+    const int s = __ffsll((long long)mask) - 1;
+    const int j = __builtin_amdgcn_readfirstlane(fl->win_j[slot][s]);
+    const CF* wm = a.Wm + (size_t)s * 2 * fam;
+    CF* X = a.X + (size_t)a.xidx[s] * blk;
+    CF* P = a.P + (size_t)s * blk;
+    VF dx[2][3], dp[2][3];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        dx[h][i] = VF{0, 0, 0, 0};
+        dp[h][i] = VF{0, 0, 0, 0};
+      }
+    for (int m = 0; m < j; ++m) {
+      __syncthreads();  // every wave is done with the matrices before
+      lds_copy(wm + (size_t)m * nn, lds, nn * (int)sizeof(CF), wave, lane);
+      lds_copy(wm + fam + (size_t)m * nn, lds + SREG, nn * (int)sizeof(CF), wave, lane);
+      F av[S::KS];
+      // P, then the ring buffers Q_{k-j+2} .. Q_k
+      aload<N, true>(m == 0 ? P : a.Qring + (size_t)((k - j + 1 + m) % win) * blk, r0 + c, rows, n,
+                     g, av);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        mfma3<F, N, true>(dx[h], av, (const F*)lds + 32 * h, n, g, c);
+        mfma3<F, N, true>(dp[h], av, (const F*)(lds + SREG) + 32 * h, n, g, c);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const VF xr = mfma3_re(dx[h]), xi = mfma3_im(dx[h]);
+      const VF pr = qn[h][0] + mfma3_re(dp[h]), pi = qn[h][1] + mfma3_im(dp[h]);
+      CF x[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int r = r0 + Mf<F>::row(g, p);
+        x[p] = X[(size_t)(r < rows ? r : 0) * n + (16 * h + c < n ? 16 * h + c : 0)];
+      }
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int r = r0 + Mf<F>::row(g, p);
+        if (r < rows && 16 * h + c < n) {
+          x[p].x += xr[p];
+          x[p].y += xi[p];
+          X[(size_t)r * n + 16 * h + c] = x[p];
+          CF v;
+          v.x = pr[p];
+          v.y = pi[p];
+          P[(size_t)r * n + 16 * h + c] = v;
+        }
+      }
+    }
+  }
+}
+
 // After the last iteration: every update window still open (the solve ended
 // without its update applying it) is applied to X,
 //   X += P Cx + sum_{i < j-1} Q_{k-j+2+i} Ex_i
@@ -860,6 +1022,14 @@ hipError_t launch_mf(hipStream_t st, const UpdateArgs<F, F>& a) {
 }
 
 template <typename F, int N>
+hipError_t launch_wide(hipStream_t st, const UpdateArgs<F, F>& a) {
+  const int blocks = ((a.rows + 15) / 16 + MF_WAVES - 1) / MF_WAVES;
+  const dim3 grid(blocks, shift_groups(blocks, a.ns, a.win));
+  k_update_wide<F, N><<<grid, BMS_WG, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+template <typename F, int N>
 hipError_t launch_vec(hipStream_t st, const UpdateArgs<F, F>& a) {
   constexpr int RPB = MF_WAVES * (64 / N);  // rows per work-group
   const int blocks = (a.rows + RPB - 1) / RPB;
@@ -871,11 +1041,12 @@ hipError_t launch_vec(hipStream_t st, const UpdateArgs<F, F>& a) {
 }  // namespace
 
 bool update_mfma_supported(int n) { return n == 8 || n == 16; }
-bool update_windowed(int n) { return n <= 16; }
+bool update_windowed(int n) { return n <= 32; }
 
+// (n > 16: the small step's share of a window grows with it, four iterations in FP32 too)
 template <typename F>
-int update_mfma_max_win() {
-  return MfWin<F>::MW;
+int update_mfma_max_win(int n) {
+  return n > 16 ? 4 : MfWin<F>::MW;
 }
 
 // two_tiles: two 16-row tiles per wave instead of one (n = 8 and 16)
@@ -893,7 +1064,8 @@ hipError_t launch_update_mfma(hipStream_t st, const UpdateArgs<F, F>& a, bool tw
     case 16:
       return two_tiles ? launch_mf<F, 16, 2, false>(st, a) : launch_mf<F, 16, 1, false>(st, a);
     default:
-      if (a.n > 16) return hipErrorInvalidValue;
+      if (a.n > 32) return hipErrorInvalidValue;
+      if (a.n > 16) return a.n <= 24 ? launch_wide<F, 24>(st, a) : launch_wide<F, 32>(st, a);
       return a.n <= 12 ? launch_mf<F, 12, 1, true>(st, a) : launch_mf<F, 16, 1, true>(st, a);
   }
 }
@@ -910,5 +1082,5 @@ template hipError_t launch_update_mfma<double>(hipStream_t, const UpdateArgs<dou
 template hipError_t launch_update_mfma<float>(hipStream_t, const UpdateArgs<float, float>&, bool);
 template hipError_t launch_update_drain<double>(hipStream_t, const UpdateArgs<double, double>&);
 template hipError_t launch_update_drain<float>(hipStream_t, const UpdateArgs<float, float>&);
-template int update_mfma_max_win<double>();
-template int update_mfma_max_win<float>();
+template int update_mfma_max_win<double>(int);
+template int update_mfma_max_win<float>(int);

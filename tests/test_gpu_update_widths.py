@@ -91,3 +91,23 @@ def test_closed_windows_mixed_solve(n):
     X, st = ctx.solve(0.2, r.beta, to_dev(torch, B), tol=1e-10,
                       precision=bms.BMS_PREC_MIXED)
     assert O.true_residuals(CLOSE_DIMS, BC, U, 0.2, r.beta, B, to_np(X)).max() <= 1e-10
+
+
+@pytest.mark.parametrize("interval", [8, 6, 3])
+@pytest.mark.parametrize("dims,n,k", [((4, 4, 4, 6), 17, 6), ((4, 4, 4, 6), 20, 4),
+                                      ((4, 4, 6, 6), 24, 9), ((4, 6, 4, 6), 25, 7),
+                                      ((4, 6, 4, 6), 31, 5), ((6, 6, 4, 6), 32, 9)])
+def test_wide_update_matches_oracle_iterates(dims, n, k, interval):
+    test_update_matches_oracle_iterates(dims, n, k, interval)
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("dims,n", [((4, 6, 4, 6), 18), ((4, 6, 6, 6), 24), ((6, 6, 6, 6), 29),
+                                    ((8, 8, 8, 8), 32)])
+def test_wide_update_solve(dims, n, mixed):
+    torch = torch_gpu()
+    bms, ctx, U, B = _problem(torch, dims, n, 600 + n)
+    r = configs.workload_coefficients("c2")
+    X, st = ctx.solve(0.2, r.beta, to_dev(torch, B), tol=1e-10,
+                      precision=bms.BMS_PREC_MIXED if mixed else bms.BMS_PREC_F64)
+    assert O.true_residuals(dims, BC, U, 0.2, r.beta, B, to_np(X)).max() <= 1e-10
