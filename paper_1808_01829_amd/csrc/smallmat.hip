@@ -8,12 +8,21 @@
 // (Sec. III, the paragraph after eq. convergence_bound_shifts). alpha_{k-1}^-1
 // is the previous Gram G_{k-1}, kept instead of inverting alpha again.
 //
-// One work-group of 256 threads per shift; matrices live in LDS (n <= 32). The two
+// One work-group per shift; matrices live in LDS (n <= 32). The two
 // kernels of the iteration take n > 16 here; for n <= 16 they are in smallwave.hip.
 #include "blas.h"
 
 #define NMAX BMS_MAX_RHS
 #define NN (NMAX * NMAX)
+// Every entry (i, j) of an n x n matrix over the threads of the work-group, a row of NMAX
+// threads for a row of the matrix (no division by n).
+#define SM_EACH(i, j)                                                                          \
+  for (int i = threadIdx.x / NMAX, j = threadIdx.x & (NMAX - 1); i < n && j < n; \
+       i += blockDim.x / NMAX)
+// Threads of the iteration's kernels: one for each entry at n = 32. Their steps are short
+// loops between barriers, bound by latency; with 256 threads, four entries in turn and two
+// divisions to find each, n = 24 (32) took 147 (264) us, now 129 (217).
+constexpr int SM_WG = 1024;
 
 namespace {
 
@@ -29,8 +38,8 @@ __device__ __forceinline__ double cabs2(double2 a) { return a.x * a.x + a.y * a.
 // flight (their latency, not arithmetic, sets the time of the small step);
 // the order of the additions is unchanged.
 __device__ void sm_mm(double2* C, const double2* A, int ta, const double2* B, int tb, int n) {
-  for (int e = threadIdx.x; e < n * n; e += BMS_WG) {
-    int i = e / n, j = e - (e / n) * n;
+  SM_EACH(i, j) {
+    const int e = i * n + j;
     const int a0 = ta ? i : i * n, as = ta ? n : 1;
     const int b0 = tb ? j * n : j, bs = tb ? 1 : n;
     double2 s = make_double2(0, 0);
@@ -47,22 +56,22 @@ __device__ void sm_mm(double2* C, const double2* A, int ta, const double2* B, in
 }
 
 __device__ void sm_load(double2* dst, const double2* src, int n) {
-  for (int e = threadIdx.x; e < n * n; e += BMS_WG) dst[e] = src[e];
+  for (int e = threadIdx.x; e < n * n; e += blockDim.x) dst[e] = src[e];
   __syncthreads();
 }
 
 __device__ void sm_store(double2* dst, const double2* src, int n) {
-  for (int e = threadIdx.x; e < n * n; e += BMS_WG) dst[e] = src[e];
+  for (int e = threadIdx.x; e < n * n; e += blockDim.x) dst[e] = src[e];
 }
 
 template <typename C>
 __device__ void sm_store_t(C* dst, const double2* src, int n) {
-  for (int e = threadIdx.x; e < n * n; e += BMS_WG) dst[e] = from_d<C>(src[e]);
+  for (int e = threadIdx.x; e < n * n; e += blockDim.x) dst[e] = from_d<C>(src[e]);
 }
 
 __device__ void sm_identity(double2* A, int n) {
-  for (int e = threadIdx.x; e < n * n; e += BMS_WG) {
-    int i = e / n, j = e - (e / n) * n;
+  SM_EACH(i, j) {
+    const int e = i * n + j;
     A[e] = make_double2(i == j ? 1.0 : 0.0, 0);
   }
   __syncthreads();
@@ -87,8 +96,8 @@ __device__ int sm_chol_upper(double2* R, const double2* G, int n, double tol) {
     for (int i = 0; i < n; ++i) tr += G[i * n + i].x;
     trace = tr;
   }
-  for (int e = threadIdx.x; e < n * n; e += BMS_WG) {
-    int i = e / n, l = e - (e / n) * n;
+  SM_EACH(i, l) {
+    const int e = i * n + l;
     R[e] = l >= i ? G[e] : make_double2(0, 0);
   }
   __syncthreads();
@@ -98,13 +107,13 @@ __device__ int sm_chol_upper(double2* R, const double2* G, int n, double tol) {
     if (!(d == d) || !(tr == tr) || !(fabs(tr) < 1e300)) return BMS_ENAN;
     if (!(d > tol * tr)) return BMS_EBREAKDOWN;
     const double djj = sqrt(d);
-    for (int l = j + 1 + threadIdx.x; l < n; l += BMS_WG) R[j * n + l] = cdiv_real(R[j * n + l], djj);
+    for (int l = j + 1 + threadIdx.x; l < n; l += blockDim.x)
+      R[j * n + l] = cdiv_real(R[j * n + l], djj);
     __syncthreads();
     if (threadIdx.x == 0) R[j * n + j] = make_double2(djj, 0);
-    const int m = n - j - 1;
-    for (int e = threadIdx.x; e < m * m; e += BMS_WG) {
-      const int i = j + 1 + e / m, l = j + 1 + (e - (e / m) * m);
-      if (l >= i) R[i * n + l] = csub(R[i * n + l], cmul(cconj(R[j * n + i]), R[j * n + l]));
+    SM_EACH(i, l) {
+      if (i > j && l >= i)
+        R[i * n + l] = csub(R[i * n + l], cmul(cconj(R[j * n + i]), R[j * n + l]));
     }
     __syncthreads();
   }
@@ -115,7 +124,7 @@ __device__ int sm_chol_upper(double2* R, const double2* G, int n, double tol) {
 // the columns of a row in parallel
 __device__ void sm_triinv_upper(double2* X, const double2* R, int n) {
   for (int i = n - 1; i >= 0; --i) {
-    for (int j = threadIdx.x; j < n; j += BMS_WG) {
+    for (int j = threadIdx.x; j < n; j += blockDim.x) {
       if (j < i) {
         X[i * n + j] = make_double2(0, 0);
         continue;
@@ -169,7 +178,7 @@ __device__ int sm_inv_general(double2* Ainv, double2* A, int n) {
     if (status) return status;
     int p = piv;
     if (p != c) {
-      for (int k = threadIdx.x; k < n; k += BMS_WG) {
+      for (int k = threadIdx.x; k < n; k += blockDim.x) {
         double2 t = A[p * n + k];
         A[p * n + k] = A[c * n + k];
         A[c * n + k] = t;
@@ -182,14 +191,14 @@ __device__ int sm_inv_general(double2* Ainv, double2* A, int n) {
     // the pivot itself is not written in this phase (column c of A is not
     // updated), so every thread reads it
     const double2 inv = crecip(A[c * n + c]);
-    for (int k = threadIdx.x; k < n; k += BMS_WG) {
+    for (int k = threadIdx.x; k < n; k += blockDim.x) {
       if (k > c) A[c * n + k] = cmul(A[c * n + k], inv);
       Ainv[c * n + k] = cmul(Ainv[c * n + k], inv);
     }
-    for (int r = threadIdx.x; r < n; r += BMS_WG) fac[r] = A[r * n + c];
+    for (int r = threadIdx.x; r < n; r += blockDim.x) fac[r] = A[r * n + c];
     __syncthreads();
-    for (int e = threadIdx.x; e < n * n; e += BMS_WG) {
-      int r = e / n, k = e - (e / n) * n;
+    SM_EACH(r, k) {
+      const int e = r * n + k;
       if (r == c) continue;
       double2 f = fac[r];
       if (k > c) A[e] = csub(A[e], cmul(f, A[c * n + k]));
@@ -231,7 +240,7 @@ __global__ __launch_bounds__(BMS_WG) void k_small_init(SmallParams p, SmallState
     *s.counter = 0;
   }
   if (pass == 0)
-    for (int i = threadIdx.x; i < BMS_MAX_SHIFTS; i += BMS_WG) {
+    for (int i = threadIdx.x; i < BMS_MAX_SHIFTS; i += blockDim.x) {
       fl->active[i] = i < p.ns;
       fl->conv[i] = 0;
       fl->res[i] = 1.0;
@@ -258,8 +267,8 @@ __global__ __launch_bounds__(BMS_WG) void k_small_init(SmallParams p, SmallState
   }
   // rho_0 = delta_0 in the "previous" slot of iteration 0; alpha_0 = 1 so G_0 = 1
   sm_store(s.rhob + n * n, L0, n);
-  for (int e = threadIdx.x; e < n * n; e += BMS_WG) {
-    int i = e / n, j = e - (e / n) * n;
+  SM_EACH(i, j) {
+    const int e = i * n + j;
     s.Gb[n * n + e] = make_double2(i == j ? 1.0 : 0.0, 0);
     for (int q = 0; q < p.ns; ++q) {
       // beta_0 = 1; the kernels for n <= 16 keep 1 - beta
@@ -268,7 +277,7 @@ __global__ __launch_bounds__(BMS_WG) void k_small_init(SmallParams p, SmallState
       s.alpha_s[(size_t)q * n * n + e] = make_double2(i == j ? 1.0 : 0.0, 0);
     }
   }
-  for (int i = threadIdx.x; i < n; i += BMS_WG) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
     double c = 0;
     for (int k = 0; k < n; ++k) c += cabs2(L0[k * n + i]);
     s.norm0[i] = sqrt(c);
@@ -377,8 +386,10 @@ __device__ void finish_shift(const SmallParams& p, const SmallState& s, SolverFl
 template <typename T>
 __device__ void win_mm(double2* C, const double2* C0, const double2* A, const double2* B,
                        int rows, int n, cplx<T>* Ct) {
-  for (int e = threadIdx.x; e < rows * n; e += BMS_WG) {
-    int r = e / n, j = e - (e / n) * n;
+  const int j = threadIdx.x & (NMAX - 1);
+  if (j >= n) return;
+  for (int r = threadIdx.x / NMAX; r < rows; r += blockDim.x / NMAX) {
+    const int e = r * n + j;
     double2 acc = C0 ? C0[e] : make_double2(0, 0);
 #pragma unroll 4
     for (int k = 0; k < n; ++k) acc = cfma(A[r * n + k], B[k * n + j], acc);
@@ -415,7 +426,7 @@ __device__ void win_step(const SmallParams& p, const SmallState& s, SolverFlags*
     win_mm<T>(nx, ox, op, Mx, j0 * n, n, tx);
     win_mm<T>(np, nullptr, op, Mp, j0 * n, n, tp);
   }
-  for (int e = threadIdx.x; e < nn; e += BMS_WG) {
+  for (int e = threadIdx.x; e < nn; e += blockDim.x) {
     nx[(size_t)j0 * nn + e] = Mx[e];
     tx[(size_t)j0 * nn + e] = from_d<cplx<T>>(Mx[e]);
     np[(size_t)j0 * nn + e] = Mp[e];
@@ -443,13 +454,13 @@ __device__ void rho_part(const SmallParams& p, const SmallState& s, SolverFlags*
     sm_store(s.rhob + cur * nn, R, n);
     sm_load(T1, s.alpha, n);
     sm_mm(D, T1, 0, T0, 0, n);  // alpha_k rho_k^-1
-    for (int e = threadIdx.x; e < nn; e += BMS_WG) s.arho[e] = make_double2(-D[e].x, -D[e].y);
+    for (int e = threadIdx.x; e < nn; e += blockDim.x) s.arho[e] = make_double2(-D[e].x, -D[e].y);
     __syncthreads();
     sm_load(T1, s.delta, n);
     sm_mm(D, R, 0, T1, 0, n);  // delta_k = rho_k delta_{k-1}
     sm_store(s.delta, D, n);
-    for (int e = threadIdx.x; e < nn; e += BMS_WG) {
-      int i = e / n, j = e - (e / n) * n;
+    SM_EACH(i, j) {
+      const int e = i * n + j;
       Mp[e] = from_d<cplx<T>>(cconj(R[j * n + i]));  // rho_k^dag
     }
   } else {
@@ -463,7 +474,7 @@ __device__ void rho_part(const SmallParams& p, const SmallState& s, SolverFlags*
   // relative residual estimate: max_i |delta^(s) e_i| / |b_i| (a thread per
   // column, then the maximum)
   __shared__ double colr[NMAX];
-  for (int i = threadIdx.x; i < n; i += BMS_WG) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
     double c = 0;
 #pragma unroll 4
     for (int k = 0; k < n; ++k) c += cabs2(D[k * n + i]);
@@ -489,8 +500,8 @@ __device__ void rho_part(const SmallParams& p, const SmallState& s, SolverFlags*
   }
   // the step into the shift's update window: Mx = alpha^(s)_k, Mp (FP64, T0)
   if (q == 0)
-    for (int e = threadIdx.x; e < nn; e += BMS_WG) {
-      int i = e / n, j = e - (e / n) * n;
+    SM_EACH(i, j) {
+      const int e = i * n + j;
       T0[e] = cconj(R[j * n + i]);
     }
   sm_load(T1, s.alpha_s + (size_t)q * nn, n);
@@ -504,7 +515,7 @@ __device__ void rho_part(const SmallParams& p, const SmallState& s, SolverFlags*
 // If that Cholesky loses its pivot, need_explicit is raised and the explicit
 // Gram of V plus k_small_rho_explicit finish the iteration instead.
 template <typename T>
-__global__ __launch_bounds__(BMS_WG) void k_small_iter(SmallParams p, SmallState s,
+__global__ __launch_bounds__(SM_WG) void k_small_iter(SmallParams p, SmallState s,
                                                        SolverFlags* fl, cplx<T>* Mx,
                                                        cplx<T>* Mp, cplx<T>* Wm) {
   __shared__ double2 Gk[NN], A[NN], R[NN], T0[NN], T1[NN], T2[NN], T3[NN];
@@ -550,16 +561,16 @@ __global__ __launch_bounds__(BMS_WG) void k_small_iter(SmallParams p, SmallState
     sm_load(T1, s.Gb + prev * nn, n);
     sm_mm(T0, T2, 0, T1, 0, n);  // t = alpha_k rho_{k-1} alpha_{k-1}^-1
     const double2* bold = s.beta_s + (size_t)q * nn;
-    for (int e = threadIdx.x; e < nn; e += BMS_WG) {
-      int i = e / n, j = e - (e / n) * n;
+    SM_EACH(i, j) {
+      const int e = i * n + j;
       T1[e] = csub(make_double2(i == j ? 1.0 : 0.0, 0), bold[e]);
     }
     __syncthreads();
     sm_mm(T2, T0, 0, T1, 0, n);  // t (1 - beta_{k-1})
     sm_load(T1, s.rhob + prev * nn, n);
     sm_mm(T3, T2, 0, T1, 1, n);  // ... rho_{k-1}^dag
-    for (int e = threadIdx.x; e < nn; e += BMS_WG) {
-      int i = e / n, j = e - (e / n) * n;
+    SM_EACH(i, j) {
+      const int e = i * n + j;
       double2 v = cadd(T3[e], cscale(A[e], dsig));
       if (i == j) v.x += 1.0;
       T3[e] = v;
@@ -585,8 +596,8 @@ __global__ __launch_bounds__(BMS_WG) void k_small_iter(SmallParams p, SmallState
   sm_mm(T3, T2, 0, A, 0, n);       // WW A
   sm_mm(T2, A, 1, T3, 0, n);       // A^H WW A
   const double2* QQ = s.G4 + 3 * nn;
-  for (int e = threadIdx.x; e < nn; e += BMS_WG) {
-    int i = e / n, j = e - (e / n) * n;
+  SM_EACH(i, j) {
+    const int e = i * n + j;
     // (QW A)^H = A^H QW^H
     T3[e] = cadd(csub(csub(QQ[e], T0[e]), cconj(T0[j * n + i])), T2[e]);
   }
@@ -617,7 +628,7 @@ __global__ __launch_bounds__(BMS_WG) void k_small_iter(SmallParams p, SmallState
 
 // Fallback when the expansion lost accuracy: rho_k from the explicit V^H V.
 template <typename T>
-__global__ __launch_bounds__(BMS_WG) void k_small_rho_explicit(SmallParams p, SmallState s,
+__global__ __launch_bounds__(SM_WG) void k_small_rho_explicit(SmallParams p, SmallState s,
                                                                SolverFlags* fl, cplx<T>* Mp,
                                                                cplx<T>* Wm) {
   __shared__ double2 Gk[NN], R[NN], T0[NN], T1[NN], T2[NN];
@@ -671,7 +682,7 @@ hipError_t launch_small_iter(hipStream_t st, const SmallParams& p, SmallState s,
                              int nparts) {
   if (small_wave_supported(p.n))
     return launch_small_iter_w<T>(st, p, s, fl, Mx, Mp, Wm, part, nparts);
-  k_small_iter<T><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm);
+  k_small_iter<T><<<p.ns, SM_WG, 0, st>>>(p, s, fl, Mx, Mp, Wm);
   return hipGetLastError();
 }
 
@@ -679,7 +690,7 @@ template <typename T>
 hipError_t launch_small_rho_explicit(hipStream_t st, const SmallParams& p, SmallState s,
                                      SolverFlags* fl, cplx<T>* Mp, cplx<T>* Wm) {
   if (small_wave_supported(p.n)) return launch_small_rho_explicit_w<T>(st, p, s, fl, Mp, Wm);
-  k_small_rho_explicit<T><<<p.ns, BMS_WG, 0, st>>>(p, s, fl, Mp, Wm);
+  k_small_rho_explicit<T><<<p.ns, SM_WG, 0, st>>>(p, s, fl, Mp, Wm);
   return hipGetLastError();
 }
 
