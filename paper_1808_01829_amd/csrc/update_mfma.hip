@@ -482,6 +482,13 @@ __device__ __forceinline__ void aload_b(__amdgpu_buffer_rsrc_t t, int g, int c,
 #pragma unroll
     for (int e = 0; e < (int)(16 / sizeof(F)); ++e) a[h * (int)(16 / sizeof(F)) + e] = v[e];
   }
+  if constexpr (B % 16 == 8) {  // FP32 at N = 12
+    typedef F f2 __attribute__((ext_vector_type(2)));
+    const f2 v = __builtin_bit_cast(
+        f2, __builtin_amdgcn_raw_buffer_load_b64(t, (4 * c + g) * B + B - 8, 0, 0));
+    a[MfShape<N>::KS - 2] = v[0];
+    a[MfShape<N>::KS - 1] = v[1];
+  }
 }
 template <int N, typename F>
 __device__ __forceinline__ void dload_b(__amdgpu_buffer_rsrc_t t, int g, int c,
@@ -513,7 +520,10 @@ __device__ __forceinline__ void dstore_b(__amdgpu_buffer_rsrc_t t, int g, int c,
   typedef F f2 __attribute__((ext_vector_type(2)));
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    const int o = Mf<F>::row(g, p) * 2 * N * (int)sizeof(F);
+    // (N = 12: the lanes of columns past 11 store out of range)
+    const int o = MfShape<N>::three && N < 16 && c >= N
+                      ? 1 << 30
+                      : Mf<F>::row(g, p) * 2 * N * (int)sizeof(F);
     if constexpr (MfShape<N>::three) {
       const f2 v = {d[0][p], d[1][p]};
       if constexpr (sizeof(F) == 8)
@@ -544,8 +554,11 @@ __device__ __forceinline__ void dstore_b(__amdgpu_buffer_rsrc_t t, int g, int c,
 // blocks. What bounds it then: HBM in FP64 (X and P of every shift read and written, 4.3 TB/s
 // of about 4.7), the matrix cores in FP32 (eight products a tile and window). Measured at
 // 32^4, n = 16, 20 shifts, full windows, both launches: FP64 9.8 -> 7.8 ms, FP32 8.0 -> 6.7;
-// at 16^4, n = 8, 16 shifts: FP64 268 -> 168 us, FP32 no gain (160 and 163: not taken). Slower: the window's
-// products unrolled (FP64 8.0, FP32 7.3), LDS operands read a product ahead (FP32 7.2).
+// at 16^4, n = 8, 16 shifts: FP64 268 -> 168 us, FP32 no gain (160 and 163: not taken); n = 12,
+// 15 shifts, 12 x 14 x 10 x 24 and 16^4: FP64 272 -> 196 and 398 -> 291 us, FP32 203 -> 185 and
+// 347 -> 289.
+// Slower: the window's products unrolled (FP64 8.0, FP32 7.3), LDS operands read a product
+// ahead (FP32 7.2).
 template <typename F, int N>
 __global__ __launch_bounds__(CL_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 void k_update_close(UpdateArgs<F, F> a) {
@@ -558,11 +571,15 @@ void k_update_close(UpdateArgs<F, F> a) {
   constexpr int LR = QREG ? MW - 2 : MW - 1;        // ring tiles of a wave in LDS
   constexpr int TB = 16 * N * (int)sizeof(CF);      // bytes of a tile
   constexpr int FAM = MW * N * N * (int)sizeof(CF); // bytes of one coefficient family
-  constexpr int CR = 2 * FAM / 16 / CL_THREADS;     // 16-byte pieces of a shift per thread
-  constexpr int UPR = N * (int)sizeof(CF) / 16;     // 16-byte units of a row
+  constexpr int CPS = 2 * FAM / 16;                 // 16-byte pieces of a shift, and
+  constexpr int CR = (CPS + CL_THREADS - 1) / CL_THREADS;  // of a thread
+  // 16-byte units of a row; at a power of two they lie exchanged by the row in LDS, so that
+  // the rows of a column do not meet on the same banks
+  constexpr int UPR = N * (int)sizeof(CF) / 16;
+  constexpr bool SWZ = (UPR & (UPR - 1)) == 0;
   constexpr int USH = UPR == 16 ? 0 : (UPR == 8 ? 1 : 2);
   constexpr int RB = N * (int)sizeof(CF);           // bytes of a row
-  static_assert(CR * 16 * CL_THREADS == 2 * FAM && (UPR << USH) == 16, "shape");
+  static_assert(FAM % 16 == 0 && (!SWZ || (UPR << USH) == 16) && TB % 256 == 0, "shape");
   __shared__ __align__(16) unsigned char lds[4 * FAM + CL_WAVES * LR * TB];
   const SolverFlags* fl = a.flags;
   if (fl->halted) return;
@@ -588,13 +605,17 @@ void k_update_close(UpdateArgs<F, F> a) {
     const unsigned char* wm = (const unsigned char*)(a.Wm + (size_t)s * 2 * BMS_MAX_WIN * N * N);
 #pragma unroll
     for (int u = 0; u < CR; ++u) {
-      const int q = u * CL_THREADS + tid, f = q / (FAM / 16), o = (q % (FAM / 16)) * 16;
+      int q = u * CL_THREADS + tid;
+      if (CPS % CL_THREADS && q >= CPS) q = 0;
+      const int f = q / (FAM / 16), o = (q % (FAM / 16)) * 16;
       cr[u] = *(const u4*)(wm + (size_t)f * (BMS_MAX_WIN * N * N * sizeof(CF)) + o);
     }
   };
   auto cstore = [&](int b) {
 #pragma unroll
-    for (int u = 0; u < CR; ++u) *(u4*)(lds + b * 2 * FAM + (u * CL_THREADS + tid) * 16) = cr[u];
+    for (int u = 0; u < CR; ++u)
+      if (CPS % CL_THREADS == 0 || u * CL_THREADS + tid < CPS)
+        *(u4*)(lds + b * 2 * FAM + (u * CL_THREADS + tid) * 16) = cr[u];
   };
   const int sfirst = __ffsll((long long)all) - 1;
   int buf = 0, s = sfirst, j = wj(s);
@@ -613,10 +634,11 @@ void k_update_close(UpdateArgs<F, F> a) {
     for (int m = QREG ? 1 : 0; m <= jmax - 2; ++m) {
       const unsigned char* q = (const unsigned char*)(a.Qring + (size_t)((k - m) % win) * blk);
 #pragma unroll
-      for (int i = 0; i < TB / 1024; ++i) {
-        const int x = i * 64 + lane, r = x / UPR, u = (x % UPR) ^ ((r >> USH) & (UPR - 1));
+      for (int i = 0; i < (TB + 1023) / 1024; ++i) {
+        const int x = i * 64 + lane, r = x / UPR;
+        const int u = SWZ ? (x % UPR) ^ ((r >> USH) & (UPR - 1)) : x % UPR;
         const size_t row = r0 + r < rows ? r0 + r : 0;
-        __builtin_amdgcn_global_load_lds(
+        if (TB % 1024 == 0 || x * 16 < TB) __builtin_amdgcn_global_load_lds(
             (glob_void*)(q + row * (N * sizeof(CF)) + u * 16),
             (lds_void*)(ring + (m - (QREG ? 1 : 0)) * TB + i * 1024), 16, 0, 0);
       }
@@ -657,13 +679,23 @@ void k_update_close(UpdateArgs<F, F> a) {
         }
       };
       auto rload = [&](int m, F(&av)[S::KS]) {
-        typedef F fv __attribute__((ext_vector_type(16 / sizeof(F))));
         const unsigned char* p = ring + (m - (QREG ? 1 : 0)) * TB + c * (N * sizeof(CF));
+        if constexpr (SWZ) {
+          typedef F fv __attribute__((ext_vector_type(16 / sizeof(F))));
 #pragma unroll
-        for (int h = 0; h < UPR / 4; ++h) {
-          const fv v = *(const fv*)(p + (((g * (UPR / 4) + h) ^ ((c >> USH) & (UPR - 1))) * 16));
+          for (int h = 0; h < UPR / 4; ++h) {
+            const fv v = *(const fv*)(p + (((g * (UPR / 4) + h) ^ ((c >> USH) & (UPR - 1))) * 16));
 #pragma unroll
-          for (int e = 0; e < (int)(16 / sizeof(F)); ++e) av[h * (int)(16 / sizeof(F)) + e] = v[e];
+            for (int e = 0; e < (int)(16 / sizeof(F)); ++e)
+              av[h * (int)(16 / sizeof(F)) + e] = v[e];
+          }
+        } else {
+#pragma unroll
+          for (int h = 0; h < S::KS / 2; ++h) {
+            const CF v = ((const CF*)p)[g * (S::KS / 2) + h];
+            av[2 * h] = v.x;
+            av[2 * h + 1] = v.y;
+          }
         }
       };
       const int rn = mask ? r0 : r0 + (int)gridDim.x * CL_WAVES * 16;
@@ -1010,8 +1042,8 @@ hipError_t launch_mf(hipStream_t st, const UpdateArgs<F, F>& a) {
   UpdateArgs<F, F> b = a;
   // where the rows alone fill the chip, the windows that close together go to their own
   // kernel (FP32 at n = 8: no gain)
-  constexpr bool own = !RT && (N == 16 || sizeof(F) == 8);
-  b.closing = own && a.win > 2 && grid.y == 1;
+  constexpr bool own = RT ? N == 12 : (N == 16 || sizeof(F) == 8);
+  b.closing = own && a.n == N && a.win > 2 && grid.y == 1;
   k_update_mfma<F, N, NTILE, RT><<<grid, BMS_WG, 0, st>>>(b);
   if constexpr (own)
     if (b.closing) {

@@ -68,7 +68,8 @@ def test_update_widths_solve(n, mixed):
 CLOSE_DIMS = (6, 14, 14, 10)  # 17640 rows: 1102.5 tiles of 16
 
 
-@pytest.mark.parametrize("n,k", [(8, 4), (8, 7), (16, 2), (16, 9), (16, 11)])
+@pytest.mark.parametrize("n,k", [(8, 4), (8, 7), (12, 4), (12, 11), (16, 2), (16, 9),
+                                 (16, 11)])
 def test_closed_windows_match_oracle_iterates(n, k):
     torch = torch_gpu()
     bms, ctx, U, B = _problem(torch, CLOSE_DIMS, n, 700 + n)
@@ -83,7 +84,7 @@ def test_closed_windows_match_oracle_iterates(n, k):
         assert err <= 1e-11, (s, err)
 
 
-@pytest.mark.parametrize("n", [8, 16])
+@pytest.mark.parametrize("n", [8, 12, 16])
 def test_closed_windows_mixed_solve(n):
     torch = torch_gpu()
     bms, ctx, U, B = _problem(torch, CLOSE_DIMS, n, 800 + n)
