@@ -429,7 +429,8 @@ def rhmc_measure(bms, torch, np, configs):
                 heatbath_action_residual=res["max_residual_hb"])
 
 
-KERNEL_CLASS_PREFIX = {"update": ("k_update_mfma", "k_update_n", "k_update_fast", "k_update<"),
+KERNEL_CLASS_PREFIX = {"update": ("k_update_mfma", "k_update_close", "k_update_vec",
+                                  "k_update_wide", "k_update_n", "k_update_fast", "k_update<"),
                        "hop": ("k_hop",), "gram": ("k_gram4",),
                        "force": ("k_force_fused",)}
 
@@ -472,10 +473,14 @@ def write_traffic(workload, prec, fetch_csv, write_csv, cal_fetch_csv, cal_write
         w = [v for k, v in write if pat.search(k)]
         if not f or not w or cls not in algorithmic:
             continue
-        fk, wk = sum(f) / len(f), sum(w) / len(w)
+        # an update's second kernel (the windows that close together) belongs to the launch of
+        # its first
+        nf = sum(1 for k, _ in fetch if pat.search(k) and "k_update_close" not in k)
+        nw = sum(1 for k, _ in write if pat.search(k) and "k_update_close" not in k)
+        fk, wk = sum(f) / nf, sum(w) / nw
         b = fk * 1024 * fetch_factor + wk * 1024 * write_factor
         kernels[cls] = dict(source=KERNEL_SOURCE.get(cls), source_sha256=source_sha(cls),
-                            launches=len(f), fetch_kib=round(fk, 1), write_kib=round(wk, 1),
+                            launches=nf, fetch_kib=round(fk, 1), write_kib=round(wk, 1),
                             bytes_per_launch=round(b),
                             algorithmic_bytes_per_launch=round(algorithmic[cls]),
                             ratio=round(b / algorithmic[cls], 3))

@@ -378,9 +378,10 @@ int bms_rhmc_trajectory(bms_ctx* ctx, const bms_rhmc_params* p, void* U, void* P
  * accumulators; bms_timing_read returns them (host pointers, any may be NULL).
  * bms_timing_flops returns the matrix-core work of the same launches for
  * BMS_KERNEL_UPDATE (the real products of the Q step and of the applied
- * windows, 2 flops per multiply-add: per complex product 3 rows 16^2 for
- * n = 13 .. 16, 3 rows 12 16 for n = 9 .. 12, rows (2n)^2 for n = 8), split into FP64 and FP32 arithmetic; 0 for
- * the other classes and for the vector kernels.
+ * windows, 2 flops per multiply-add: per complex product 3 rows 32 N with
+ * N = 24 or 32 for n = 17 .. 32, 3 rows 16 N with N = 12 or 16 for
+ * n = 9 .. 16, rows (2n)^2 for n = 8), split into FP64 and FP32 arithmetic; 0
+ * for the other classes and for the vector kernels.
  * bms_timing_floor returns in *seconds the least time the recorded launches
  * of a class need at the given peaks (bytes/s, FP64 and FP32 flops/s, each
  * > 0): for BMS_KERNEL_UPDATE the sum over its launches of
@@ -405,8 +406,8 @@ int bms_timing_enable(bms_ctx* ctx, int enable);
  * than the smallest are updated once per window of iterations (4 in FP64,
  * 8 in FP32: X^(s) and P^(s) of the whole window from the window's start and
  * the Q blocks it spans, 4 block vectors per shift per window instead of per
- * iteration; Algorithm 1's updates composed over the window; the other n up
- * to 16 always run such a windowed kernel);
+ * iteration; Algorithm 1's updates composed over the window; the other n
+ * always run such a windowed kernel, above 16 with windows of 4);
  * 6 = the same kernel updating every shift every iteration, one tile per
  * wave; 0..3 = the vector kernels
  * (0 = four row chunks per work-group with both coefficient columns in
@@ -418,7 +419,8 @@ int bms_timing_enable(bms_ctx* ctx, int enable);
  * 5 = the matrix-core kernel with rows staged through LDS, 1, 2 or 4 chunks
  * in flight per work-group; 0 = the vector kernel; -1 = the default (2).
  * For BMS_KERNEL_HOP: 1 = four threads per site sharing the site's links
- * (n = 4, 8, 16, 32), 0 = one thread per site and column group, 2 and 3 = 0
+ * (n = 4, 8, 16, 32, and 12, 20, 24 on lattices of at least 1.5 waves per
+ * SIMD, else as 0), 0 = one thread per site and column group, 2 and 3 = 0
  * and 1 in a tiled traversal (8 x 8 x 4 tiles in y, z, t of whole x-rows,
  * each (y, z) pencil on one XCD; lattices the tiles do not fit run in the
  * natural order), 4 = at n = 16 persistent waves that keep the next hops'
@@ -426,7 +428,7 @@ int bms_timing_enable(bms_ctx* ctx, int enable);
  * for lattices with V/2 a multiple of 128 and a ring that fits one
  * work-group's LDS, else variant 1; the hop configuration's tiles apply and
  * its cap is the ring depth, 2 or 4), -1 = the default (1 where it applies,
- * tiled in FP64 at n >= 16). For BMS_KERNEL_FORCE: 1 and 2 = the fused kernel (y = D_oe x
+ * tiled in FP64 at n >= 16 and in that form at 12). For BMS_KERNEL_FORCE: 1 and 2 = the fused kernel (y = D_oe x
  * formed on chip for all n * n_shifts columns, each link loaded once and
  * written once; links in registers, or in LDS with the loads two columns
  * ahead), 0 = D_oe hops per shift into a buffer, then one lane group per
