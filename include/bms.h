@@ -378,9 +378,10 @@ int bms_rhmc_trajectory(bms_ctx* ctx, const bms_rhmc_params* p, void* U, void* P
  * accumulators; bms_timing_read returns them (host pointers, any may be NULL).
  * bms_timing_flops returns the matrix-core work of the same launches for
  * BMS_KERNEL_UPDATE (the real products of the Q step and of the applied
- * windows, 2 flops per multiply-add: per complex product 3 rows 32 N with
- * N = 24 or 32 for n = 17 .. 32, 3 rows 16 N with N = 12 or 16 for
- * n = 9 .. 16, rows (2n)^2 for n = 8), split into FP64 and FP32 arithmetic; 0
+ * windows, 2 flops per multiply-add: per complex product rows (2n)^2 for n = 8,
+ * 4 rows 16 N with N = 12 or 16 for n = 9 .. 16 and 4 rows 32 N with N = 24 or 32
+ * for n = 17 .. 32, three quarters of that at n = 16, in the windows of
+ * n = 9 .. 15 and in FP64 windows above), split into FP64 and FP32 arithmetic; 0
  * for the other classes and for the vector kernels.
  * bms_timing_floor returns in *seconds the least time the recorded launches
  * of a class need at the given peaks (bytes/s, FP64 and FP32 flops/s, each

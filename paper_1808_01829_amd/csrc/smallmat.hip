@@ -390,9 +390,10 @@ __device__ void win_mm(double2* C, const double2* C0, const double2* A, const do
   if (j >= n) return;
   for (int r = threadIdx.x / NMAX; r < rows; r += blockDim.x / NMAX) {
     const int e = r * n + j;
-    double2 acc = C0 ? C0[e] : make_double2(0, 0);
+    double2 acc = make_double2(0, 0);
 #pragma unroll 4
     for (int k = 0; k < n; ++k) acc = cfma(A[r * n + k], B[k * n + j], acc);
+    if (C0) acc = cadd(C0[e], acc);  // last: it is the largest term
     C[e] = acc;
     Ct[e] = from_d<cplx<T>>(acc);
   }

@@ -486,12 +486,14 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     double S = (double)w.blk * sizeof(cplx<T>);
     // matrix-core flops of one complex right product of a row block by an
-    // n x n matrix: three real products for n > 8 (per 16-row tile 9 steps of
-    // 16 x 16 x 4 up to n = 12, then 12; 36 up to n = 24, then 48), one real product by the 2n x 2n form (rows (2n)^2
-    // FMA) for n = 8
-    const double prod = n > 16  ? (n > 24 ? 6144.0 : 4608.0) * w.rows
-                        : n > 8 ? (n > 12 ? 1536.0 : 1152.0) * w.rows
-                                  : 2.0 * w.rows * (2.0 * n) * (2.0 * n);
+    // n x n matrix: four real products for n > 8 (N steps of 16 x 16 x 4 per 16-row tile and
+    // 16 columns), three quarters of that as Gauss's three (at n = 16, and in the windows up
+    // to there and in FP64), one real product by the 2n x 2n form (rows (2n)^2 FMA) for n = 8
+    const int N = n > 24 ? 32 : n > 16 ? 24 : n > 12 ? 16 : 12;
+    const double four = n == 8 ? 2.0 * w.rows * (2.0 * n) * (2.0 * n)
+                               : 128.0 * N * (n > 16 ? 2 : 1) * w.rows;
+    const double prod_q = n == 16 ? 0.75 * four : four;
+    const double prod = n == 8 || (n > 16 && mixed) ? four : 0.75 * four;
     const bool mf = n >= 8 && update_windowed(n) && (n <= 16 || w.win > 1) &&
                     (!update_mfma_supported(n) || c->update_variant < 0 || c->update_variant >= 4);
     for (int k = 0; k < hf.iter; ++k) {
@@ -499,7 +501,7 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
       c->kt_bytes[BMS_KERNEL_UPDATE] += b;
       double f64 = 0, f32 = 0;
       if (mf) {
-        f64 = 2 * prod;  // the Q step, FP64
+        f64 = 2 * prod_q;  // the Q step, FP64
         (mixed ? f32 : f64) += (units[k] >> 16) * prod;
       }
       c->kt_flops64[BMS_KERNEL_UPDATE] += f64;

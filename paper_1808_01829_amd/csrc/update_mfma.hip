@@ -72,16 +72,16 @@ struct Mf<float> {
   __device__ static __forceinline__ int row(int g, int p) { return 4 * g + p; }
 };
 
-// N: block width (8 or 16), or the largest width (12 or 16) the form for a width
-// known at run time takes. Widths above 8 take the three-product form below.
 // Waves and threads of a work-group of k_update_close.
 constexpr int CL_WAVES = 8, CL_THREADS = CL_WAVES * 64;
 
+// N: block width (8 or 16), or the largest width (12, 16, 24 or 32) the form for a width
+// known at run time takes. wide: the products of mfma_wide below.
 template <int N>
 struct MfShape {
-  static constexpr bool three = N > 8;
+  static constexpr bool wide = N > 8;
   static constexpr int KS = N / 2;            // reals of a row per lane group: k-steps of 4
-  static constexpr int NT = three ? 2 : 1;    // 16-column output tiles
+  static constexpr int NT = wide ? 2 : 1;     // 16-column output tiles
   static constexpr int PITCH = NT * 16;       // reals per row of the staged output tiles
 };
 
@@ -104,21 +104,32 @@ __device__ __forceinline__ void mfma_acc_c(typename Mf<F>::V (&d)[MfShape<N>::NT
   }
 }
 
-// n > 8: the complex right product by Gauss's three real products. With
-// the A operand of a lane holding complex columns KC g .. KC g + KC - 1 of its
-// row (KC = N / 4; the same contiguous run as above), k-step ks contracts over
-// complex column kc = KC g + ks, and the three accumulators gather
-//   d0 = sum Re a Re M,  d1 = sum Im a Im M,  d2 = sum (Re a + Im a)(Re M + Im M),
-// from which Re(a M) = d0 - d1 and Im(a M) = d2 - d0 - d1 (mfma3_re/_im).
-// Output column c of every accumulator is complex column c, so the two
-// results land in the layout of the n-tiles above (tile 0 real parts, tile 1
-// imaginary parts). 3 N / 4 matrix-core steps per product and 16-row tile, against
-// N for the real form at n = 16. M: complex n x n in LDS, (re, im) pairs. For n < N the
-// columns past n meet a zero A operand and read row 0 (finite) instead; output
+// n > 8: the complex right product. With the A operand of a lane holding complex columns
+// KC g .. KC g + KC - 1 of its row (KC = N / 4; the same contiguous run as above), k-step ks
+// contracts over complex column kc = KC g + ks, and output column c of every accumulator is
+// complex column c, so the results land in the layout of the n-tiles above (tile 0 real
+// parts, tile 1 imaginary parts; wide_re, wide_im). M: complex n x n in LDS, (re, im) pairs.
+// For n < N the columns past n meet a zero A operand and read row 0 (finite) instead; output
 // columns past n are not used.
-template <typename F, int N, bool RT>
-__device__ __forceinline__ void mfma3(typename Mf<F>::V (&d)[3], const F (&a)[MfShape<N>::KS],
-                                      const F* M, int nrt, int g, int c) {
+//
+// ACC = 3: Gauss's three real products,
+//   d0 = sum Re a Re M,  d1 = sum Im a Im M,  d2 = sum (Re a + Im a)(Re M + Im M),
+//   Re(a M) = d0 - d1,  Im(a M) = d2 - d0 - d1,
+// 3 N / 4 matrix-core steps per product and 16-row tile. ACC = 2: the four products, N steps,
+// with the rounding of plain complex multiply-adds.
+//
+// The windows take three products up to n = 16, and above in FP64, where they are bound by
+// the matrix cores; the Q step of every width but 16, and FP32 windows above 16, take four,
+// which costs them little. Against the vector kernels that updated every iteration with plain
+// multiply-adds, rms error of X after 12 or 16 iterations (4 x 6 x 4 x 6, five shifts,
+// the mean over them): FP64 0.82 at n = 9, 0.84 at 12, 0.78 at 15, 0.99 to 1.01 from 17 to
+// 32; FP32 0.97, 0.96, 0.94, and 0.96 falling to 0.88. Four products in all windows: 0.78,
+// 0.81, 0.76 and FP32 0.92, 0.91, 0.91, for 10 % of the update's time (n = 12 FP64 81 -> 90
+// us at 16^4).
+template <typename F, int N, bool RT, int ACC>
+__device__ __forceinline__ void mfma_wide(typename Mf<F>::V (&d)[ACC],
+                                          const F (&a)[MfShape<N>::KS], const F* M, int nrt, int g,
+                                          int c) {
   constexpr int KC = N / 4;
   const int n = RT ? nrt : N;
 #pragma unroll
@@ -128,17 +139,31 @@ __device__ __forceinline__ void mfma3(typename Mf<F>::V (&d)[3], const F (&a)[Mf
     const F mr = M[e], mi = M[e + 1];
     const F ar = a[2 * ks], ai = a[2 * ks + 1];
     d[0] = Mf<F>::mfma(ar, mr, d[0]);
-    d[1] = Mf<F>::mfma(ai, mi, d[1]);
-    d[2] = Mf<F>::mfma(ar + ai, mr + mi, d[2]);
+    if constexpr (ACC == 3) {
+      d[1] = Mf<F>::mfma(ai, mi, d[1]);
+      d[2] = Mf<F>::mfma(ar + ai, mr + mi, d[2]);
+    } else {
+      d[1] = Mf<F>::mfma(ar, mi, d[1]);
+      d[0] = Mf<F>::mfma(-ai, mi, d[0]);
+      d[1] = Mf<F>::mfma(ai, mr, d[1]);
+    }
   }
 }
 template <typename V>
-__device__ __forceinline__ V mfma3_re(const V (&d)[3]) {
+__device__ __forceinline__ V wide_re(const V (&d)[3]) {
   return d[0] - d[1];
 }
 template <typename V>
-__device__ __forceinline__ V mfma3_im(const V (&d)[3]) {
+__device__ __forceinline__ V wide_im(const V (&d)[3]) {
   return d[2] - d[0] - d[1];
+}
+template <typename V>
+__device__ __forceinline__ V wide_re(const V (&d)[2]) {
+  return d[0];
+}
+template <typename V>
+__device__ __forceinline__ V wide_im(const V (&d)[2]) {
+  return d[1];
 }
 
 // A-operand reals of one tile row (row r, reals g*KS .. g*KS+KS-1) in the
@@ -173,7 +198,7 @@ __device__ __forceinline__ void dload(const C* base, int r0, int rows, int nrt, 
   for (int p = 0; p < 4; ++p) {
     const int r = r0 + Mf<F>::row(g, p);
     const size_t rr = r < rows ? (size_t)r : 0;
-    if constexpr (MfShape<N>::three) {
+    if constexpr (MfShape<N>::wide) {
       C v = base[rr * n + (!RT || c < n ? c : 0)];
       d[0][p] = (F)v.x;
       d[1][p] = (F)v.y;
@@ -193,7 +218,7 @@ __device__ __forceinline__ void dstore(C* base, int r0, int rows, int nrt, int g
   for (int p = 0; p < 4; ++p) {
     const int r = r0 + Mf<F>::row(g, p);
     if (!whole && r >= rows) continue;
-    if constexpr (MfShape<N>::three) {
+    if constexpr (MfShape<N>::wide) {
       C v;
       v.x = (R)d[0][p];
       v.y = (R)d[1][p];
@@ -239,16 +264,18 @@ __device__ __forceinline__ unsigned long long windows_due(const SolverFlags* fl,
 // one) is applied, with j iterations in its window:
 //   X += P Cx + sum_{i < j-1} Q_{k-j+2+i} Ex_i
 //   P  = Q_{k+1} + P Cp + sum_{i < j-1} Q_{k-j+2+i} Ep_i     (in place)
-// (sigma_0: j = 1 every iteration, the plain X += P Mx, P = Q + P Mp). A
+// (sigma_0: j = 1 every iteration, the plain X += P Mx, P = Q + P Mp). At the widths known
+// at run time the sums run from Q_k down and take P last: a shift far above sigma_0 is nearly
+// solved by its first iteration, so P Cx is as large as X and the other terms are small, and
+// taken first it had every later term rounded at its size (FP32 blocks, n = 12, a shift of
+// 10: error 1.2e-7 updated every iteration, 3.2e-7 so, 1.2e-7 from Q_k down). A
 // shift moves 4 block vectors per window instead of 4 per iteration; the
 // ring buffers it also reads are the same for every shift, so after the
 // first shift of a tile they come from L2.
 // One tile per wave: four waves per SIMD in FP32, three in FP64 (the register
 // count the compiler picks by itself leaves fewer; in FP64 four waves need
-// spills, whose scratch traffic reached HBM). Widths above 8 take the
-// three-product form for every complex product (Q step and shift windows).
-// RT: the width is a.n (9 .. 15, at most N), else N (in FP64 with N = 16 the masks cost
-// registers: two waves per SIMD instead of 24 spills). Measured at n = 12 (12.14.10.24, 15
+// spills, whose scratch traffic reached HBM).
+// RT: the width is a.n (9 .. 15, at most N), else N. Measured at n = 12 (12.14.10.24, 15
 // shifts, FP64) against the every-iteration vector kernel: 90.0 -> 35.3 us per launch.
 // gridDim.y: the shifts are dealt to that many groups of work-groups (shift s to
 // group s % gridDim.y), which all form Q_{k+1} and of which the first stores
@@ -256,12 +283,13 @@ __device__ __forceinline__ unsigned long long windows_due(const SolverFlags* fl,
 template <typename F, int N, int NTILE, bool RT>
 __global__ __launch_bounds__(BMS_WG)
 __attribute__((amdgpu_waves_per_eu(
-    NTILE == 1 ? (sizeof(F) == 4 ? 4 : (RT && N == 16 ? 2 : 3)) : 1)))
+    NTILE == 1 ? (sizeof(F) == 4 ? 4 : 3) : 1)))
 void k_update_mfma(UpdateArgs<F, F> a) {
   using S = MfShape<N>;
   using CF = cplx<F>;
   using VF = typename Mf<F>::V;
   constexpr int MW = MfWin<F>::MW;
+  constexpr bool DOWN = RT;  // the order of a window's sums, see above
   // LDS: the Q step's two coefficient matrices (FP64), then (FP32) the
   // per-wave layout change of Q, then one shift's window coefficients (F); each
   // copied region in whole KiB, and a matrix row's worth past the last one
@@ -317,12 +345,15 @@ void k_update_mfma(UpdateArgs<F, F> a) {
   dx4 qd[NTILE][S::NT];
 #pragma unroll
   for (int t = 0; t < NTILE; ++t) {
-    if constexpr (S::three) {
-      dx4 d3[3] = {dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}};
-      mfma3<double, N, RT>(d3, av[t], qb0, n, g, c);
-      mfma3<double, N, RT>(d3, wv[t], qb1, n, g, c);
-      qd[t][0] = mfma3_re(d3);
-      qd[t][1] = mfma3_im(d3);
+    if constexpr (S::wide) {
+      constexpr int QACC = RT ? 2 : 3;
+      dx4 d[QACC];
+#pragma unroll
+      for (int i = 0; i < QACC; ++i) d[i] = dx4{0.0, 0.0, 0.0, 0.0};
+      mfma_wide<double, N, RT>(d, av[t], qb0, n, g, c);
+      mfma_wide<double, N, RT>(d, wv[t], qb1, n, g, c);
+      qd[t][0] = wide_re(d);
+      qd[t][1] = wide_im(d);
     } else {
       qd[t][0] = dx4{0.0, 0.0, 0.0, 0.0};
       mfma_acc_c<N>(qd[t], av[t], qb0, g, c);
@@ -365,16 +396,17 @@ void k_update_mfma(UpdateArgs<F, F> a) {
     __syncthreads();  // the shift coefficients overwrite this LDS
   }
 
-  // the P and X tiles of a shift (the next shift's P, and for n = 8 its X,
-  // are loaded while the current one finishes; for n > 8 X is loaded after
-  // the products, which keeps the three-accumulator form at three waves per
-  // SIMD with 16 bytes of spills outside the product loop)
+  // the first A operand (P, or from Q_k down that) and X tiles of a shift (the next
+  // shift's first operand, and for n = 8 its X, are loaded while the current one finishes;
+  // for n > 8 X is loaded after the products, which keeps the three-accumulator form at
+  // three waves per SIMD with 20 bytes of spills outside the product loop)
   F pa[NTILE][S::KS];
   VF xa[NTILE][S::NT];
+  auto window = [&](int s) { return __builtin_amdgcn_readfirstlane(fl->win_j[slot][s]); };
   auto fetch = [&](int s, int t) {
     const int r0 = (tile0 + t) * 16;
-    aload<N, RT>(a.P + (size_t)s * blk, r0 + c, rows, n, g, pa[t]);
-    if constexpr (!S::three) dload<N, RT, F>(a.X + (size_t)a.xidx[s] * blk, r0, rows, n, g, c, xa[t]);
+    aload<N, RT>(DOWN && window(s) > 1 ? Qin : a.P + (size_t)s * blk, r0 + c, rows, n, g, pa[t]);
+    if constexpr (!S::wide) dload<N, RT, F>(a.X + (size_t)a.xidx[s] * blk, r0, rows, n, g, c, xa[t]);
   };
   int s = mask ? __ffsll((long long)mask) - 1 : -1;
   if (s >= 0) {
@@ -385,7 +417,7 @@ void k_update_mfma(UpdateArgs<F, F> a) {
   while (s >= 0) {
     mask &= mask - 1;
     const int s2 = mask ? __ffsll((long long)mask) - 1 : -1;
-    const int j = __builtin_amdgcn_readfirstlane(fl->win_j[slot][s]);
+    const int j = window(s);
     // the window's 2j coefficient matrices into LDS (complex n x n, the X
     // family, then the P family)
     const CF* wm = a.Wm + (size_t)s * 2 * fam;
@@ -400,42 +432,57 @@ void k_update_mfma(UpdateArgs<F, F> a) {
 #pragma unroll
     for (int t = 0; t < NTILE; ++t) {
       const int r0 = (tile0 + t) * 16;
-      constexpr int NACC = S::three ? 3 : S::NT;  // accumulators of one product family
+      constexpr int NACC = S::wide ? 3 : S::NT;  // accumulators of one product family
       VF pn[NACC], dx[NACC];
 #pragma unroll
       for (int nt = 0; nt < NACC; ++nt) {
-        pn[nt] = (S::three || nt >= S::NT) ? VF{0, 0, 0, 0} : qn[t][nt];
+        pn[nt] = (S::wide || nt >= S::NT) ? VF{0, 0, 0, 0} : qn[t][nt];
         dx[nt] = VF{0, 0, 0, 0};
       }
-      // ring buffers Q_{k-j+2} .. Q_k, two in flight
-      F qa[2][S::KS];
-      if (j >= 2) aload<N, RT>(a.Qring + (size_t)((k - j + 2) % win) * blk, r0 + c, rows, n, g, qa[0]);
       // the increment is formed on its own and added to X once, so X (large
       // next to one window's increment) is rounded once
       auto prod = [&](const F(&av)[S::KS], int m) {
-        if constexpr (S::three) {
-          mfma3<F, N, RT>(dx, av, bx + m * 2 * nn, n, g, c);
-          mfma3<F, N, RT>(pn, av, bp + m * 2 * nn, n, g, c);
+        if constexpr (S::wide) {
+          mfma_wide<F, N, RT>(dx, av, bx + m * 2 * nn, n, g, c);
+          mfma_wide<F, N, RT>(pn, av, bp + m * 2 * nn, n, g, c);
         } else {
           mfma_acc_c<N>(dx, av, bx + m * 2 * nn, g, c);
           mfma_acc_c<N>(pn, av, bp + m * 2 * nn, g, c);
         }
       };
-      prod(pa[t], 0);
+      // P and the ring buffers Q_{k-j+2} .. Q_k, two in flight
+      F qa[2][S::KS];
+      if constexpr (DOWN) {
+        // (the first, Q_k or for j = 1 P, is there)
+        auto load = [&](int m, F(&av)[S::KS]) {
+          aload<N, RT>(m ? a.Qring + (size_t)((k - j + 1 + m) % win) * blk : P, r0 + c, rows, n, g,
+                       av);
+        };
 #pragma unroll
-      for (int i = 0; i < MW - 1; ++i) {
-        if (i < j - 1) {
-          if (i + 1 < j - 1)
-            aload<N, RT>(a.Qring + (size_t)((k - j + 3 + i) % win) * blk, r0 + c, rows, n, g,
-                     qa[(i + 1) & 1]);
-          prod(qa[i & 1], i + 1);
+        for (int i = 0; i < MW; ++i) {
+          if (i < j) {
+            F(&av)[S::KS] = i & 1 ? qa[0] : pa[t];
+            if (i + 1 < j) load(j - 2 - i, i & 1 ? pa[t] : qa[0]);
+            prod(av, j - 1 - i);
+          }
+        }
+      } else {
+        auto ring = [&](int i) { return a.Qring + (size_t)((k - j + 2 + i) % win) * blk; };
+        if (j >= 2) aload<N, RT>(ring(0), r0 + c, rows, n, g, qa[0]);
+        prod(pa[t], 0);
+#pragma unroll
+        for (int i = 0; i < MW - 1; ++i) {
+          if (i < j - 1) {
+            if (i + 1 < j - 1) aload<N, RT>(ring(i + 1), r0 + c, rows, n, g, qa[(i + 1) & 1]);
+            prod(qa[i & 1], i + 1);
+          }
         }
       }
-      if constexpr (S::three) {
+      if constexpr (S::wide) {
         dload<N, RT, F>(X, r0, rows, n, g, c, xa[t]);
-        xa[t][0] += mfma3_re(dx);
-        xa[t][1] += mfma3_im(dx);
-        const VF pst[S::NT] = {qn[t][0] + mfma3_re(pn), qn[t][1] + mfma3_im(pn)};
+        xa[t][0] += wide_re(dx);
+        xa[t][1] += wide_im(dx);
+        const VF pst[S::NT] = {qn[t][0] + wide_re(pn), qn[t][1] + wide_im(pn)};
         dstore<N, RT, F>(X, r0, rows, n, g, c, xa[t]);
         dstore<N, RT, F>(P, r0, rows, n, g, c, pst);
       } else {
@@ -497,7 +544,7 @@ __device__ __forceinline__ void dload_b(__amdgpu_buffer_rsrc_t t, int g, int c,
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     const int o = Mf<F>::row(g, p) * 2 * N * (int)sizeof(F);
-    if constexpr (MfShape<N>::three) {
+    if constexpr (MfShape<N>::wide) {
       f2 v;
       if constexpr (sizeof(F) == 8)
         v = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b128(t, o + c * 16, 0, 0));
@@ -521,10 +568,10 @@ __device__ __forceinline__ void dstore_b(__amdgpu_buffer_rsrc_t t, int g, int c,
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     // (N = 12: the lanes of columns past 11 store out of range)
-    const int o = MfShape<N>::three && N < 16 && c >= N
+    const int o = MfShape<N>::wide && N < 16 && c >= N
                       ? 1 << 30
                       : Mf<F>::row(g, p) * 2 * N * (int)sizeof(F);
-    if constexpr (MfShape<N>::three) {
+    if constexpr (MfShape<N>::wide) {
       const f2 v = {d[0][p], d[1][p]};
       if constexpr (sizeof(F) == 8)
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), t, o + c * 16, 0, 0);
@@ -542,7 +589,8 @@ __device__ __forceinline__ void dstore_b(__amdgpu_buffer_rsrc_t t, int g, int c,
 }
 
 // The windows that an update closes together (usually those of every shift but sigma_0),
-// after the launch above has formed Q_{k+1}; same products, same order of sums, same bits.
+// after the launch above has formed Q_{k+1}; same products, same order of sums, same bits (at
+// n = 12 but for the rounding of adding P's terms).
 //
 // In k_update_mfma each shift reads the ring tiles again (3 or 7 loads of a wave against
 // one each of P and X), 64 rows share a copy of the coefficients, and every wave waits for
@@ -566,6 +614,7 @@ void k_update_close(UpdateArgs<F, F> a) {
   using CF = cplx<F>;
   using VF = typename Mf<F>::V;
   constexpr int MW = MfWin<F>::MW;
+  constexpr bool DOWN = N == 12;  // sums as k_update_mfma of that width adds them
   // Q_k (whose A operand costs FP32 only N / 2 registers) stays in registers in FP32
   constexpr bool QREG = sizeof(F) == 4;
   constexpr int LR = QREG ? MW - 2 : MW - 1;        // ring tiles of a wave in LDS
@@ -662,17 +711,17 @@ void k_update_close(UpdateArgs<F, F> a) {
       dload_b<N, F>(X, g, c, xa);
       const F* bx = (const F*)(lds + buf * 2 * FAM);
       const F* bp = (const F*)(lds + buf * 2 * FAM + FAM);
-      constexpr int NACC = S::three ? 3 : S::NT;
+      constexpr int NACC = S::wide ? 3 : S::NT;
       VF pn[NACC], dx[NACC];
 #pragma unroll
       for (int nt = 0; nt < NACC; ++nt) {
-        pn[nt] = (S::three || nt >= S::NT) ? VF{0, 0, 0, 0} : qn[nt];
+        pn[nt] = (S::wide || nt >= S::NT) ? VF{0, 0, 0, 0} : qn[nt];
         dx[nt] = VF{0, 0, 0, 0};
       }
       auto prod = [&](const F(&av)[S::KS], int m) {
-        if constexpr (S::three) {
-          mfma3<F, N, false>(dx, av, bx + m * 2 * N * N, N, g, c);
-          mfma3<F, N, false>(pn, av, bp + m * 2 * N * N, N, g, c);
+        if constexpr (S::wide) {
+          mfma_wide<F, N, false>(dx, av, bx + m * 2 * N * N, N, g, c);
+          mfma_wide<F, N, false>(pn, av, bp + m * 2 * N * N, N, g, c);
         } else {
           mfma_acc_c<N>(dx, av, bx + m * 2 * N * N, g, c);
           mfma_acc_c<N>(pn, av, bp + m * 2 * N * N, g, c);
@@ -699,19 +748,39 @@ void k_update_close(UpdateArgs<F, F> a) {
         }
       };
       const int rn = mask ? r0 : r0 + (int)gridDim.x * CL_WAVES * 16;
+      // the P tile of the next shift, or of the first shift of the next rows, takes this
+      // one's registers (DOWN: so P's products come first all the same, but into sums of
+      // their own that are added to the others at the end)
+      const __amdgpu_buffer_rsrc_t Pn = tile_rsrc(a.P + (size_t)s2 * blk, rn, rows, RB);
       prod(pa, 0);
-      // the P tile of the next shift, or of the first shift of the next rows
-      aload_b<N>(tile_rsrc(a.P + (size_t)s2 * blk, rn, rows, RB), g, c, pa);
-      for (int m = j - 2; m >= (QREG ? 1 : 0); --m) {
-        F qa[S::KS];
-        rload(m, qa);
-        prod(qa, j - 1 - m);
+      aload_b<N>(Pn, g, c, pa);
+      VF xp[NACC];
+      if constexpr (DOWN) {
+#pragma unroll
+        for (int i = 0; i < NACC; ++i) {
+          xp[i] = dx[i];
+          dx[i] = VF{0, 0, 0, 0};
+        }
+        if constexpr (QREG) prod(qk, j - 1);
+        for (int m = QREG ? 1 : 0; m <= j - 2; ++m) {
+          F qa[S::KS];
+          rload(m, qa);
+          prod(qa, j - 1 - m);
+        }
+#pragma unroll
+        for (int i = 0; i < NACC; ++i) dx[i] += xp[i];
+      } else {
+        for (int m = j - 2; m >= (QREG ? 1 : 0); --m) {
+          F qa[S::KS];
+          rload(m, qa);
+          prod(qa, j - 1 - m);
+        }
+        if constexpr (QREG) prod(qk, j - 1);
       }
-      if constexpr (QREG) prod(qk, j - 1);
-      if constexpr (S::three) {
-        xa[0] += mfma3_re(dx);
-        xa[1] += mfma3_im(dx);
-        const VF pst[S::NT] = {qn[0] + mfma3_re(pn), qn[1] + mfma3_im(pn)};
+      if constexpr (S::wide) {
+        xa[0] += wide_re(dx);
+        xa[1] += wide_im(dx);
+        const VF pst[S::NT] = {qn[0] + wide_re(pn), qn[1] + wide_im(pn)};
         dstore_b<N, F>(X, g, c, xa);
         dstore_b<N, F>(P, g, c, pst);
       } else {
@@ -734,7 +803,7 @@ void k_update_close(UpdateArgs<F, F> a) {
 // through LDS one iteration at a time, X and P family together; two work-groups share a
 // compute unit, and one computes while the other waits for its copy. Columns past n meet a
 // zero A operand, output columns past n are not used. On the matrix cores 2 x 2 x 3 N / 4
-// steps of 16 x 16 x 4 a tile, iteration and shift; X and P are moved once per window, where
+// steps (FP32 2 x 2 x N) of 16 x 16 x 4 a tile, iteration and shift; X and P are moved once per window, where
 // the vector kernel for any n, which this replaces, moved them every iteration. Measured at
 // 16^4, 12 shifts, FP64, per iteration: n = 32 674 -> 205 us, n = 24 612 -> 182 (FP32 291 -> 77).
 template <typename F, int N>
@@ -783,11 +852,11 @@ void k_update_wide(UpdateArgs<F, F> a) {
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      dx4 d3[3] = {dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}};
-      mfma3<double, N, true>(d3, av, (const double*)lds + 32 * h, n, g, c);
-      mfma3<double, N, true>(d3, wv, (const double*)(lds + QREG) + 32 * h, n, g, c);
-      qd[h][0] = mfma3_re(d3);
-      qd[h][1] = mfma3_im(d3);
+      dx4 d[2] = {dx4{0.0, 0.0, 0.0, 0.0}, dx4{0.0, 0.0, 0.0, 0.0}};
+      mfma_wide<double, N, true>(d, av, (const double*)lds + 32 * h, n, g, c);
+      mfma_wide<double, N, true>(d, wv, (const double*)(lds + QREG) + 32 * h, n, g, c);
+      qd[h][0] = wide_re(d);
+      qd[h][1] = wide_im(d);
     }
   }
   // D layout of output half h: complex column 16 h + c of tile row Mf<>::row(g, p)
@@ -840,34 +909,35 @@ void k_update_wide(UpdateArgs<F, F> a) {
     const CF* wm = a.Wm + (size_t)s * 2 * fam;
     CF* X = a.X + (size_t)a.xidx[s] * blk;
     CF* P = a.P + (size_t)s * blk;
-    VF dx[2][3], dp[2][3];
+    constexpr int ACC = sizeof(F) == 4 ? 2 : 3;
+    VF dx[2][ACC], dp[2][ACC];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
+      for (int i = 0; i < ACC; ++i) {
         dx[h][i] = VF{0, 0, 0, 0};
         dp[h][i] = VF{0, 0, 0, 0};
       }
-    for (int m = 0; m < j; ++m) {
+    for (int m = j - 1; m >= 0; --m) {
       __syncthreads();  // every wave is done with the matrices before
       lds_copy(wm + (size_t)m * nn, lds, nn * (int)sizeof(CF), wave, lane);
       lds_copy(wm + fam + (size_t)m * nn, lds + SREG, nn * (int)sizeof(CF), wave, lane);
       F av[S::KS];
-      // P, then the ring buffers Q_{k-j+2} .. Q_k
+      // the ring buffers Q_k .. Q_{k-j+2}, then P
       aload<N, true>(m == 0 ? P : a.Qring + (size_t)((k - j + 1 + m) % win) * blk, r0 + c, rows, n,
                      g, av);
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        mfma3<F, N, true>(dx[h], av, (const F*)lds + 32 * h, n, g, c);
-        mfma3<F, N, true>(dp[h], av, (const F*)(lds + SREG) + 32 * h, n, g, c);
+        mfma_wide<F, N, true>(dx[h], av, (const F*)lds + 32 * h, n, g, c);
+        mfma_wide<F, N, true>(dp[h], av, (const F*)(lds + SREG) + 32 * h, n, g, c);
       }
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const VF xr = mfma3_re(dx[h]), xi = mfma3_im(dx[h]);
-      const VF pr = qn[h][0] + mfma3_re(dp[h]), pi = qn[h][1] + mfma3_im(dp[h]);
+      const VF xr = wide_re(dx[h]), xi = wide_im(dx[h]);
+      const VF pr = qn[h][0] + wide_re(dp[h]), pi = qn[h][1] + wide_im(dp[h]);
       CF x[4];
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
@@ -916,12 +986,12 @@ __global__ __launch_bounds__(BMS_WG) void k_update_drain(UpdateArgs<F, F> a) {
     const double2* xf = a.wst + (size_t)(slot * ns + s) * 2 * fam;
     const CF* P = a.P + (size_t)s * blk + row * n;
     double2 acc = make_double2(0, 0);
-    for (int kk = 0; kk < n; ++kk) acc = cfma(to_d(P[kk]), xf[(size_t)kk * n + col], acc);
-    for (int i = 0; i < j - 1; ++i) {
+    for (int i = j - 2; i >= 0; --i) {
       const CF* Q = a.Qring + (size_t)((k - j + 2 + i) % win) * blk + row * n;
       const double2* ex = xf + (size_t)(i + 1) * nn;
       for (int kk = 0; kk < n; ++kk) acc = cfma(to_d(Q[kk]), ex[(size_t)kk * n + col], acc);
     }
+    for (int kk = 0; kk < n; ++kk) acc = cfma(to_d(P[kk]), xf[(size_t)kk * n + col], acc);
     CF* X = a.X + (size_t)a.xidx[s] * blk + e;
     *X = cadd(*X, from_d<CF>(acc));
   }
@@ -934,12 +1004,21 @@ __global__ __launch_bounds__(BMS_WG) void k_update_drain(UpdateArgs<F, F> a) {
 // coefficients, the shift's from LDS; the ring rows stay in registers for all shifts.
 // Memory bound on large blocks: per shift and window X and P are read and written once, as
 // in k_update_mfma. On small ones latency bound, hence the shift groups.
+// The sums run from Q_k down and take P last, as in k_update_mfma.
 // Measured per launch against the every-iteration form: n = 4 at 8^4 with 12 shifts
 // 18.0 -> 5.2 us, n = 1 at 4^4 with 8 shifts 4.5 -> 3.6 us.
+// Waves per SIMD: what the registers of the ring leave, asked for where the compiler would
+// take a few registers more (FP64 at 16^4, n = 5: 45 -> 41 us).
 template <typename F, int N>
-__global__ __launch_bounds__(BMS_WG) void k_update_vec(UpdateArgs<F, F> a) {
+__global__ __launch_bounds__(BMS_WG)
+__attribute__((amdgpu_waves_per_eu(
+    sizeof(F) == 4 ? 1 : (N == 2 ? 6 : (N == 3 ? 5 : (N == 5 ? 4 : 1))))))
+void k_update_vec(UpdateArgs<F, F> a) {
   using CF = cplx<F>;
   constexpr int MW = MfWin<F>::MW, RPW = 64 / N, NN = N * N;
+  // X loaded after the ring products: its registers are what costs a wave per SIMD (n = 3
+  // FP64 21.7 -> 19.5 us; at n = 6, where they fit, late loads cost 49 -> 61)
+  constexpr bool XLATE = sizeof(F) == 8 && (N == 3 || N == 5);
   __shared__ CF cf[2][MW * NN];  // one shift's window coefficients: X family, P family
   SolverFlags* fl = a.flags;
   if (fl->halted) return;
@@ -983,7 +1062,8 @@ __global__ __launch_bounds__(BMS_WG) void k_update_vec(UpdateArgs<F, F> a) {
     CF p[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) p[i] = P[i];
-    const CF x = *X;
+    CF x;
+    if (!XLATE) x = *X;
     const CF* wm = a.Wm + (size_t)s * 2 * fam;
     for (int e = tid; e < j * NN; e += BMS_WG) {
       cf[0][e] = wm[e];
@@ -1003,12 +1083,7 @@ __global__ __launch_bounds__(BMS_WG) void k_update_vec(UpdateArgs<F, F> a) {
     // the increment is formed on its own and added to X once
     CF dx = czero<CF>(), pn = qn;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      dx = cfma(p[i], cf[0][i * N + col], dx);
-      pn = cfma(p[i], cf[1][i * N + col], pn);
-    }
-#pragma unroll
-    for (int m = 0; m < MW - 1; ++m)
+    for (int m = MW - 2; m >= 0; --m)
       if (m < j - 1) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
@@ -1016,6 +1091,12 @@ __global__ __launch_bounds__(BMS_WG) void k_update_vec(UpdateArgs<F, F> a) {
           pn = cfma(ring[m][i], cf[1][(m + 1) * NN + i * N + col], pn);
         }
       }
+    if (XLATE) x = *X;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      dx = cfma(p[i], cf[0][i * N + col], dx);
+      pn = cfma(p[i], cf[1][i * N + col], pn);
+    }
     if (live) {
       *X = cadd(x, dx);
       P[col] = pn;
