@@ -143,10 +143,10 @@ int bms_destroy(bms_ctx* ctx);
  * With two link rows selected (bms_set_link_rows, the default) the call
  * keeps the first two rows of every link and checks that each third row is
  * what SU(3) implies, row2 = conj(row0 x row1) for the unscaled matrix, to
- * 1e-12 in every part; when all pass, the half hop and the force read two rows
- * per link and rebuild the third (a third fewer link bytes), else the call keeps
- * whole links too and all read all
- * nine entries. That check waits for the import (a host synchronisation).
+ * 1e-12 in every part; when all pass, the half hop reads two rows per link and
+ * rebuilds the third (a third fewer link bytes; the force reads the field's own
+ * third rows), else the call keeps whole links too and all read all nine
+ * entries. That check waits for the import (a host synchronisation).
  */
 int bms_set_gauge(bms_ctx* ctx, const void* U);
 

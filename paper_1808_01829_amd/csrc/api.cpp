@@ -155,7 +155,7 @@ extern "C" int bms_destroy(bms_ctx* c) {
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
   if (c->links64.p) (void)hipFree(c->links64.p);
   if (c->links32.p) (void)hipFree(c->links32.p);
-  for (DevBuf* b : {&c->links64r, &c->links32r, &c->lsign, &c->lcheck})
+  for (DevBuf* b : {&c->links64r, &c->links32r, &c->links64t, &c->lsign, &c->lcheck})
     if (b->p) (void)hipFree(b->p);
   for (auto& b : c->scratch)
     if (b.p) (void)hipFree(b.p);
@@ -181,10 +181,12 @@ extern "C" int bms_set_gauge(bms_ctx* c, const void* U) {
     const size_t nrow = (size_t)2 * c->nblk * 48 << c->sbl;
     if ((rc = ensure_buf(c, c->links64r, nrow * sizeof(double2)))) return rc;
     if ((rc = ensure_buf(c, c->links32r, nrow * sizeof(float2)))) return rc;
+    if ((rc = ensure_buf(c, c->links64t, nrow / 2 * sizeof(double2)))) return rc;
     if ((rc = ensure_buf(c, c->lsign, (size_t)2 * c->vh * sizeof(uint32_t)))) return rc;
     if ((rc = ensure_buf(c, c->lcheck, 256))) return rc;
     HIP_TRY(c, launch_fill_zero(c->stream, c->lcheck.p, 16));
-    HIP_TRY(c, launch_gauge_import(c, U, c->links64r.p, c->links32r.p, 6, c->lsign.p, c->lcheck.p));
+    HIP_TRY(c, launch_gauge_import(c, U, c->links64r.p, c->links32r.p, 6, c->links64t.p,
+                                   c->lsign.p, c->lcheck.p));
     // two rows are used only if every third row is the SU(3) one to 1e-12
     unsigned long long bits = 0;
     HIP_TRY(c, hipMemcpyAsync(&bits, c->lcheck.p, sizeof bits, hipMemcpyDeviceToHost, c->stream));
@@ -198,7 +200,7 @@ extern "C" int bms_set_gauge(bms_ctx* c, const void* U) {
     const size_t nlink = (size_t)2 * c->nblk * 72 << c->sbl;
     if ((rc = ensure_buf(c, c->links64, nlink * sizeof(double2)))) return rc;
     if ((rc = ensure_buf(c, c->links32, nlink * sizeof(float2)))) return rc;
-    HIP_TRY(c, launch_gauge_import(c, U, c->links64.p, c->links32.p, 9, nullptr, nullptr));
+    HIP_TRY(c, launch_gauge_import(c, U, c->links64.p, c->links32.p, 9, nullptr, nullptr, nullptr));
   }
   c->nlinks = 8;
   c->gauge_set = true;

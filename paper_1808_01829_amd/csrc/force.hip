@@ -22,22 +22,24 @@ struct ForceArgs {
   const double2* X;      // [ns][vh][3][n] even sites
   const double2* Y;      // [ns][vh][3][n] odd sites, Y = D_oe X
   const double2* links;  // FP64 internal links, both parities, epl entries each
-  size_t pstride;        // complex elements per parity of `links`
+  const double2* third;  // epl = 6: their third rows
+  size_t nblk;           // link blocks per parity
   int epl;               // 9, or 6 for links kept as two rows
   double2* G;            // raw gradient [mu][idx][3][3]
   double* F;             // Lie-algebra force [mu][idx][8]
   double alpha[BMS_MAX_SHIFTS];
 };
 
-// entry e of link k of checkerboard site s; with two-row links an entry of the third row
-// is conj(row0 x row1) / scale, scale = +-1/2
-__device__ __forceinline__ double2 link_entry(const double2* L, uint32_t s, int k, int e, int sbl,
-                                              int epl, double scale) {
-  if (epl == 9 || e < 6) return L[link_off(s, k, e, sbl, 8 * epl, epl)];
-  const int b = e - 6, b1 = b == 2 ? 0 : b + 1, b2 = b == 0 ? 2 : b - 1;
-  auto at = [&](int i) { return L[link_off(s, k, i, sbl, 48, 6)]; };
-  const double2 x = csub(cmul(at(b1), at(3 + b2)), cmul(at(b2), at(3 + b1)));
-  return cscale(cconj(x), 1.0 / scale);
+// Entry e of link k of checkerboard site s of parity par. All nine are the field's own: the
+// check at import accepts third rows that are off SU(3) by 1e-12, which is what rebuilding
+// them would cost a force that holds its sums to rounding.
+__device__ __forceinline__ double2 link_entry(const ForceArgs& a, int par, uint32_t s, int k,
+                                              int e) {
+  const bool t = a.epl == 6 && e >= 6;
+  const double2* L = t ? a.third : a.links;
+  const int epl = t ? 3 : a.epl;
+  return L[(par * a.nblk * (8 * epl) << a.sbl) +
+           link_off(s, k, t ? e - 6 : e, a.sbl, 8 * epl, epl)];
 }
 
 // Sum of a complex value over the LPL lanes of this lane's group (LPL a power
@@ -133,11 +135,10 @@ __global__ __launch_bounds__(BMS_WG) void k_force(ForceArgs a, int lpl) {
   }
   if (lane != 0) return;
   // U_mu(w) from the forward link of parity par: L = (1/2) eta b U
-  const double2* L = a.links + (size_t)par * a.pstride;
   double2 u[9];
   double f = 2.0 * ((esum & 1) ? -1.0 : 1.0) * ((co[mu] == g.L[mu] - 1) ? a.bc[mu] : 1);
   for (int e = 0; e < 9; ++e)
-    u[e] = cscale(link_entry(L, cb, mu, e, a.sbl, a.epl, 0.25 * f), f);
+    u[e] = cscale(link_entry(a, par, cb, mu, e), f);
   // W = U M; F^a = Im Tr[T^a W], T^a = lambda_a / 2
   double2 w[9];
   for (int i = 0; i < 3; ++i)
@@ -241,36 +242,22 @@ __global__ __launch_bounds__(BMS_WG, WAVES) void k_force_fused(ForceArgs a) {
   const double eta = (esum & 1) ? -1.0 : 1.0;
   const double bf = co[mu] == g.L[mu] - 1 ? (double)a.bc[mu] : 1.0;
   const double be = co[mu] == 0 ? (double)a.bc[mu] : 1.0;
-  const double2* L = a.links + a.pstride;  // parity 1 (odd output sites)
   __shared__ double2 lds[LDS_LINKS ? kForceSites * kLinkPitch : 1];
   double2 la[9], lb[9];
   if (LDS_LINKS) {
     // the four g-lanes of (site, q) stage the site's links mu and 4 + mu
     double2* sa = lds + sl * kLinkPitch + mu * 9;
     double2* sb_ = sa + 36;
-    for (int e = gl; e < a.epl; e += 4) {
-      sa[e] = L[link_off(z, mu, e, a.sbl, 8 * a.epl, a.epl)];
-      sb_[e] = L[link_off(z, 4 + mu, e, a.sbl, 8 * a.epl, a.epl)];
-    }
-    if (a.epl == 6) {
-      // the third rows, from the first two of the same four lanes (one wave)
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (gl < 3) {
-        const int b1 = gl == 2 ? 0 : gl + 1, b2 = gl == 0 ? 2 : gl - 1;
-        sa[6 + gl] = cscale(cconj(csub(cmul(sa[b1], sa[3 + b2]), cmul(sa[b2], sa[3 + b1]))),
-                            2.0 * eta * bf);
-        sb_[6 + gl] = cscale(cconj(csub(cmul(sb_[b1], sb_[3 + b2]), cmul(sb_[b2], sb_[3 + b1]))),
-                             -2.0 * eta * be);
-      }
+    for (int e = gl; e < 9; e += 4) {
+      sa[e] = link_entry(a, 1, z, mu, e);
+      sb_[e] = link_entry(a, 1, z, 4 + mu, e);
     }
     __syncthreads();
   } else {
 #pragma unroll
     for (int e = 0; e < 9; ++e) {
-      la[e] = link_entry(L, z, mu, e, a.sbl, a.epl, 0.5 * eta * bf);
-      lb[e] = link_entry(L, z, 4 + mu, e, a.sbl, a.epl, -0.5 * eta * be);
+      la[e] = link_entry(a, 1, z, mu, e);
+      lb[e] = link_entry(a, 1, z, 4 + mu, e);
     }
   }
   double2 ma[9], mb[9];
@@ -461,7 +448,8 @@ extern "C" int bms_force(bms_ctx* c, int n, int ns, const double* alpha, const v
   a.Y = (const double2*)Y;
   a.epl = c->links_two_rows ? 6 : 9;
   a.links = (const double2*)(c->links_two_rows ? c->links64r.p : c->links64.p);
-  a.pstride = (size_t)c->nblk * (8 * a.epl) << c->sbl;
+  a.third = (const double2*)c->links64t.p;
+  a.nblk = (size_t)c->nblk;
   a.G = (double2*)out;
   a.F = (double*)out;
   for (int s = 0; s < ns; ++s) a.alpha[s] = alpha[s];
@@ -475,7 +463,7 @@ extern "C" int bms_force(bms_ctx* c, int n, int ns, const double* alpha, const v
   if (fused) {
     // 16 lanes per odd site. Variants: 1 links in registers, loads one
     // column ahead; 2 (default) links in LDS, loads two columns ahead.
-    // Measured at 16^3 x 32, K = 128: 414 and 364 us (hops + per-link
+    // Measured at 16^3 x 32, K = 128: 414 and 366 us (hops + per-link
     // kernel, variant 0: 998 us)
     const dim3 grid((c->vh + kForceSites - 1) / kForceSites);
     const int fv = c->force_variant < 0 ? 2 : c->force_variant;

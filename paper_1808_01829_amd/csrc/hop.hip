@@ -15,7 +15,8 @@ struct Bc {
 //   k = mu     :  +1/2 eta_mu(x) bf U_mu(x)              (hop to x+mu)
 //   k = 4 + mu :  -1/2 eta_mu(x) bb U_mu(x-mu)^dag       (hop to x-mu)
 // bf / bb = bc[mu] if that hop crosses the boundary, in FP64 and FP32, EPL entries of each:
-// EPL = 9: whole links. EPL = 6: the first two rows, and bit k of sign[p][s] set when link
+// EPL = 9: whole links. EPL = 6: the first two rows, in FP64 also the third (l64t, which the
+// force reads), and bit k of sign[p][s] set when link
 // k's scale c (+-1/2) is negative, and in *dev the largest difference, over the links and
 // the parts of their entries, between a third row and the one the first two give for an
 // SU(3) matrix, row2(c V) = conj(row0 x row1) / c (+inf if not finite). A non-negative
@@ -24,12 +25,13 @@ struct Bc {
 // One thread per site, a wave over 64 consecutive ones, so that U is read as whole lines
 // (links.h) and either parity's entries are written as runs of 32 sites. Bound by that
 // traffic, the writes above all. Measured at 16^3 x 32: 206 us with both forms written,
-// an atomic per link and links read a thread each, and 60 us of fills -> 42 us.
+// an atomic per link and links read a thread each, and 60 us of fills -> 48 us (6 of
+// them the third rows).
 template <int EPL>
 __global__ __launch_bounds__(BMS_WG) void k_gauge_import(
     const double2* __restrict__ U, double2* __restrict__ l64, float2* __restrict__ l32,
-    uint32_t* __restrict__ sign, unsigned long long* __restrict__ dev, Geom g, Bc bc, int sbl,
-    int nblk, int vol) {
+    double2* __restrict__ l64t, uint32_t* __restrict__ sign, unsigned long long* __restrict__ dev,
+    Geom g, Bc bc, int sbl, int nblk, int vol) {
   __shared__ double2 stage[BMS_WG / 64][WL_ENTRIES];
   __shared__ double wdev[BMS_WG / 64];
   double2* lds = stage[threadIdx.x >> 6];
@@ -42,6 +44,7 @@ __global__ __launch_bounds__(BMS_WG) void k_gauge_import(
   const int co[4] = {c.x, c.y, c.z, c.t};
   const int par = (c.x + c.y + c.z + c.t) & 1;
   const size_t pbase = (size_t)par * nblk * (8 * EPL) << sbl;
+  const size_t tbase = (size_t)par * nblk * 24 << sbl;
   const int st[4] = {1, g.L[0], g.L[0] * g.L[1], g.L[0] * g.L[1] * g.L[2]};
   uint32_t mask = 0;
   double d = 0;
@@ -72,6 +75,9 @@ __global__ __launch_bounds__(BMS_WG) void k_gauge_import(
         l64[o] = v[e];
         l32[o] = make_float2((float)v[e].x, (float)v[e].y);
       }
+      if constexpr (EPL == 6)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) l64t[tbase + link_off(s, k, e, sbl, 24, 3)] = v[6 + e];
     }
     if constexpr (EPL == 6) {
       if (f < 0) mask |= 1u << k;
@@ -822,18 +828,18 @@ __global__ __launch_bounds__(BMS_WG) void k_hop_s(const cplx<T>* __restrict__ li
 }  // namespace
 
 hipError_t launch_gauge_import(const bms_ctx* c, const void* U, void* l64, void* l32, int entries,
-                               void* sign, void* dev) {
+                               void* l64t, void* sign, void* dev) {
   Bc bc;
   for (int i = 0; i < 4; ++i) bc.b[i] = c->bc[i];
   const unsigned nblk = (unsigned)((c->vol + BMS_WG - 1) / BMS_WG);
   if (entries == 6)
     k_gauge_import<6><<<nblk, BMS_WG, 0, c->stream>>>(
-        (const double2*)U, (double2*)l64, (float2*)l32, (uint32_t*)sign, (unsigned long long*)dev,
-        c->geom, bc, c->sbl, c->nblk, (int)c->vol);
+        (const double2*)U, (double2*)l64, (float2*)l32, (double2*)l64t, (uint32_t*)sign,
+        (unsigned long long*)dev, c->geom, bc, c->sbl, c->nblk, (int)c->vol);
   else
     k_gauge_import<9><<<nblk, BMS_WG, 0, c->stream>>>((const double2*)U, (double2*)l64,
-                                                      (float2*)l32, nullptr, nullptr, c->geom, bc,
-                                                      c->sbl, c->nblk, (int)c->vol);
+                                                      (float2*)l32, nullptr, nullptr, nullptr,
+                                                      c->geom, bc, c->sbl, c->nblk, (int)c->vol);
   return hipGetLastError();
 }
 

@@ -112,11 +112,11 @@ struct bms_ctx {
   int nlinks = 8;  // links per site and output parity: 8, or 16 with three-hop links
   // The links a half hop needs, [parity][blocked links] complex, in one of two forms
   // (links_two_rows): SU(3) links as their first two rows (links64r, links32r, six entries
-  // per link) and per site a mask of the links whose scale (+-1/2 times the phases) is
+  // per link; for the force their third rows in links64t) and per site a mask of the links whose scale (+-1/2 times the phases) is
   // negative, when link_rows is 2 and every link of the field passed the check at
   // import; else (and for the improved operator) all nine entries (links64, links32).
   DevBuf links64, links32;
-  DevBuf links64r, links32r, lsign, lcheck;
+  DevBuf links64r, links32r, links64t, lsign, lcheck;
   int link_rows = 2;            // bms_set_link_rows: 2 (when the field allows) or 3
   bool links_two_rows = false;  // the hop reads links64r / links32r
   double link_dev = -1;         // largest third-row deviation found (-1: not checked)
@@ -193,9 +193,10 @@ int link_update_dev(bms_ctx* c, double eps, const void* P, void* U);
 int kinetic_dev(bms_ctx* c, const void* P, double* K);
 
 // ---- launchers (all enqueue on c->stream) ---------------------------------
-// entries of each link: 9, or 6 with the sign masks and the check of the third rows (*dev)
+// entries of each link: 9, or 6 with the third rows (l64t), the sign masks and the check of
+// the third rows (*dev)
 hipError_t launch_gauge_import(const bms_ctx* c, const void* U, void* l64, void* l32, int entries,
-                               void* sign, void* dev);
+                               void* l64t, void* sign, void* dev);
 // the improved operator: one-hop links V and three-hop links W (16 per site)
 hipError_t launch_gauge_import_improved(const bms_ctx* c, const void* V, const void* W, void* l64,
                                         void* l32);

@@ -66,3 +66,29 @@ def test_import_and_force_in_both_link_forms(dims, field):
             Xd = to_dev(torch, X)
             assert rel(to_np(c.force(r.alpha, Xd, bms.BMS_FORCE_RAW)), Go) < 1e-12
             assert rel(to_np(c.force(r.alpha, Xd, bms.BMS_FORCE_LIE)), Fo) < 1e-12
+
+
+# Third rows off SU(3) by less than the check at import accepts: the links are read as two
+# rows, and the force follows the field all the same (rebuilt third rows: 8e-13 off and more).
+# Tolerance: sums of 24 + 8 n products of rounding 2.2e-16, a few times the largest entry.
+@pytest.mark.parametrize("dims", [(4, 4, 2, 6), (4, 4, 4, 4), (6, 4, 2, 10)])
+@pytest.mark.parametrize("n", [1, 3, 8])
+def test_force_takes_the_fields_own_third_rows(dims, n):
+    torch = torch_gpu()
+    from paper_1808_01829_amd import bms
+    r = configs.workload_coefficients("c1")
+    U = random_gauge(dims, 0.6, 21)
+    g = np.random.default_rng(5)
+    U[..., 2, :] += 9e-13 * (g.uniform(-1, 1, U[..., 2, :].shape)
+                             + 1j * g.uniform(-1, 1, U[..., 2, :].shape))
+    X = np.stack([gaussian_block(dims, n, 30 + s) for s in range(len(r.beta))])
+    Go = O.force(dims, BC, U, r.alpha, X)
+    Fo = O.lie_force(U, Go)
+    c = bms.Context(dims, BC)
+    c.set_gauge(to_dev(torch, U))
+    assert c.link_rows() == 2
+    for variant in (-1, 1):
+        c.set_variant(bms.BMS_KERNEL_FORCE, variant)
+        Xd = to_dev(torch, X)
+        assert rel(to_np(c.force(r.alpha, Xd, bms.BMS_FORCE_RAW)), Go) < 1e-13
+        assert rel(to_np(c.force(r.alpha, Xd, bms.BMS_FORCE_LIE)), Fo) < 1e-13
