@@ -181,8 +181,7 @@ UpdateArgs<T, T> update_args(const Work& w) {
 // launches only: event-record nodes of a replayed graph carry no usable
 // timestamps on this runtime, measured).
 // k: the iteration's index (Q_k is in ring buffer k % win). tail: only what follows the
-// small step of a paused iteration, the explicit Gram included (the small step's events are
-// then recorded again: that launch counts no time).
+// small step of a paused iteration (events 4 and on), the explicit Gram included.
 template <typename T>
 int enqueue_iteration(bms_ctx* c, const Work& w, const SmallParams& sp, double mass, long k,
                       hipEvent_t* ev, bool tail = false) {
@@ -205,7 +204,6 @@ int enqueue_iteration(bms_ctx* c, const Work& w, const SmallParams& sp, double m
                                     (cplx<T>*)w.Mp, (cplx<T>*)w.Wm, w.partials, nparts));
   } else {
     HIP_TRY(c, launch_resume(c->stream, w.flags));
-    MARK(3);
   }
   MARK(4);
   // explicit Cholesky-QR Gram, only when the expansion lost its pivot
@@ -425,8 +423,27 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
     c->evpool.resize(8 * K);
     for (size_t i = old; i < c->evpool.size(); ++i) HIP_TRY(c, hipEventCreate(&c->evpool[i]));
   }
+  // times and bytes of launches i0 .. i1 - 1 of the chunk's iteration k, which has ended
+  auto collect = [&](int k, int i0, int i1) -> int {
+    // links read by one half hop: nine entries, or six for two-row links
+    const int epl = c->links_two_rows && c->nlinks == 8 ? 6 : 9;
+    double G = (double)epl * c->nlinks * c->vol * sizeof(T);
+    double S = (double)w.blk * sizeof(cplx<T>);
+    // the explicit Cholesky-QR Gram (slot 4) normally exits at once: no bytes
+    const double kbytes[7] = {G + 2 * S, G + 3 * S, 3 * S, 0, 0, 0, 0};
+    for (int i = i0; i < i1; ++i) {
+      float ms = 0;
+      HIP_TRY(c, hipEventElapsedTime(&ms, c->evpool[8 * k + i], c->evpool[8 * k + i + 1]));
+      int kc = kIterKernel[i];
+      c->kt_ms[kc] += ms;
+      c->kt_launches[kc] += 1;
+      c->kt_bytes[kc] += kbytes[i];
+    }
+    return BMS_OK;
+  };
   while (true) {
     if ((rc = enqueue_chunk<T>(c, w, sp, mass, K, o.use_graph != 0))) return rc;
+    int paused = -1;  // iteration of the chunk that the host finished
     const bool rel = mixed && enqueued + K - last_rel >= o.reliable_interval;
     while (true) {
       if (rel && (rc = enqueue_reliable(c, w, sp, mass, B, Xout, xmap, R1, R2, R0, false)))
@@ -436,31 +453,20 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
       if (hf.stop != 2) break;
       // paused in iteration hf.iter of this chunk (what followed it did nothing)
       sp.inline_explicit = 1;
-      for (int k = (int)(hf.iter - enqueued); k < K; ++k)
+      paused = (int)(hf.iter - enqueued);
+      // its events up to the small step's end, before the tail records the others again
+      if (c->timing && (rc = collect(paused, 0, 4))) return rc;
+      for (int k = paused; k < K; ++k)
         if ((rc = enqueue_iteration<T>(c, w, sp, mass, k, c->timing ? &c->evpool[8 * k] : nullptr,
-                                       k == (int)(hf.iter - enqueued))))
+                                       k == paused)))
           return rc;
     }
     if (rel) last_rel = enqueued + K;
-    if (c->timing) {
-      // links read by one half hop: nine entries, or six for two-row links
-      const int epl = c->links_two_rows && c->nlinks == 8 ? 6 : 9;
-      double G = (double)epl * c->nlinks * c->vol * sizeof(T);
-      double S = (double)w.blk * sizeof(cplx<T>);
-      // the explicit Cholesky-QR Gram (slot 4) normally exits at once: no bytes
-      const double kbytes[7] = {G + 2 * S, G + 3 * S, 3 * S, 0, 0, 0, 0};
+    if (c->timing)
       for (int k = 0; k < K; ++k) {
         if (enqueued + k >= hf.iter) break;  // launches after the stop did no work
-        for (int i = 0; i < 7; ++i) {
-          float ms = 0;
-          HIP_TRY(c, hipEventElapsedTime(&ms, c->evpool[8 * k + i], c->evpool[8 * k + i + 1]));
-          int kc = kIterKernel[i];
-          c->kt_ms[kc] += ms;
-          c->kt_launches[kc] += 1;
-          c->kt_bytes[kc] += kbytes[i];
-        }
+        if ((rc = collect(k, k == paused ? 4 : 0, 7))) return rc;
       }
-    }
     enqueued += K;
     if (hf.stop) break;
     // extend_tol > 0 (the FP64 phase of the mixed solver): once the block
