@@ -31,12 +31,16 @@ def test_pause_is_no_kernels_time(n, mixed, mass):
     def per_launch(mass, **more):
         ctx.timing(False)
         ctx.solve(mass, shifts, B, **kw, **more)  # allocations and first launches
-        ctx.timing(True)
-        _, st = ctx.solve(mass, shifts, B, **kw, **more)
-        t = ctx.timing_read()
-        assert t["hop"][1] == 2 * st["iterations"] and t["gram"][1] == st["iterations"]
-        assert t["update"][1] == st["iterations"] and t["cholqr_gram"][1] == st["iterations"]
-        return {k: t[k][0] / t[k][1] for k in ("hop", "gram")}
+        best = {}
+        for _ in range(5):  # the least of five: a launch that reached an idle GPU late is longer
+            ctx.timing(True)
+            _, st = ctx.solve(mass, shifts, B, **kw, **more)
+            t = ctx.timing_read()
+            assert t["hop"][1] == 2 * st["iterations"] and t["gram"][1] == st["iterations"]
+            assert t["update"][1] == st["iterations"] and t["cholqr_gram"][1] == st["iterations"]
+            for k in ("hop", "gram"):
+                best[k] = min(best.get(k, 1e9), t[k][0] / t[k][1])
+        return best
 
     ref = per_launch(0.1, max_iter=4, max_refine=0)
     paused = per_launch(mass)
