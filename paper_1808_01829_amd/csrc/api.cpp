@@ -152,7 +152,7 @@ extern "C" int bms_destroy(bms_ctx* c) {
   // teardown: a failing release cannot be reported past this point. (hipFree waits for
   // the device, so for work on the caller's stream too; that stream may be gone by now.)
   if (c->stream) (void)hipStreamSynchronize(c->stream);
-  if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
+  c->graphs.clear([](hipGraphExec_t g) { (void)hipGraphExecDestroy(g); });
   if (c->links64.p) (void)hipFree(c->links64.p);
   if (c->links32.p) (void)hipFree(c->links32.p);
   for (DevBuf* b : {&c->links64r, &c->links32r, &c->links64t, &c->lsign, &c->lcheck})

@@ -6,6 +6,7 @@
 
 #include "../../include/bms.h"
 #include "common.h"
+#include "graph_cache.h"
 
 struct DevBuf {
   void* p = nullptr;
@@ -138,9 +139,7 @@ struct bms_ctx {
   // per update launch: algorithmic bytes, FP64 and FP32 matrix-core flops
   std::vector<double> kt_upd_launch;
   std::vector<hipEvent_t> evpool;
-  // graph cache for the iteration chunk
-  hipGraphExec_t graph_exec = nullptr;
-  std::string graph_key;
+  GraphCache<hipGraphExec_t> graphs;  // captured chunks of iterations
   // work done by the current bms_solve (reset at its start, reported in bms_stats)
   long it_f64 = 0, it_f32 = 0, hop_work = 0, rel_work = 0;
 };

@@ -335,13 +335,14 @@ int enqueue_chunk(bms_ctx* c, const Work& w, const SmallParams& sp, double mass,
     return BMS_OK;
   }
   std::string key = chunk_key<T>(c, w, sp, mass, K);
-  if (!c->graph_exec || c->graph_key != key) {
-    if (c->graph_exec) {
+  hipGraphExec_t exec = c->graphs.find(key);
+  if (!exec) {
+    auto& slot = c->graphs.place();
+    if (slot.graph) {
       HIP_TRY(c, hipStreamSynchronize(c->stream));  // an earlier replay may still run
-      HIP_TRY(c, hipGraphExecDestroy(c->graph_exec));
-      c->graph_exec = nullptr;
+      HIP_TRY(c, hipGraphExecDestroy(slot.graph));
+      slot.graph = nullptr;
     }
-    c->graph_key.clear();
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     int rc = BMS_OK;
     for (int k = 0; k < K && rc == BMS_OK; ++k)
@@ -353,15 +354,13 @@ int enqueue_chunk(bms_ctx* c, const Work& w, const SmallParams& sp, double mass,
       return rc;
     }
     if (e != hipSuccess) return set_err(c, BMS_EHIP, "stream capture: %s", hipGetErrorString(e));
-    e = hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0);
+    e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
     hipGraphDestroy(g);
-    if (e != hipSuccess) {
-      c->graph_exec = nullptr;
-      return set_err(c, BMS_EHIP, "graph instantiate: %s", hipGetErrorString(e));
-    }
-    c->graph_key = key;
+    if (e != hipSuccess) return set_err(c, BMS_EHIP, "graph instantiate: %s", hipGetErrorString(e));
+    slot.graph = exec;
+    slot.key = key;
   }
-  HIP_TRY(c, hipGraphLaunch(c->graph_exec, c->stream));
+  HIP_TRY(c, hipGraphLaunch(exec, c->stream));
   return BMS_OK;
 }
 
