@@ -213,6 +213,13 @@ int bms_apply_mdagm(bms_ctx* ctx, double mass, double sigma, int n, const void* 
  * <= tol; BMS_ENOCONV when max_iter block iterations were not enough (X holds
  * the last iterate, stats the residuals); BMS_EBREAKDOWN when the block lost
  * rank (e.g. linearly dependent columns in B); BMS_ENAN on non-finite values.
+ * Workspace kept in the context, in FP64 blocks the size of B: 2 n_shifts + 4,
+ * and the residual blocks of an update window, 4 (FP64; 8 FP32 blocks, the same,
+ * in BMS_PREC_MIXED up to n = 16, else 4; 1 with one shift or an odd
+ * check_interval), 2 more where shifts are refined and n_shifts + 5 more for
+ * the FP32 phase. If the device has not that much, the solve does without
+ * windows (1 residual block, every shift updated every iteration, the same X to
+ * rounding); BMS_ENOMEM if it has not that either.
  */
 int bms_solve(bms_ctx* ctx, double mass, int n, int n_shifts, const double* shifts, double tol,
               int max_iter, const bms_opts* opts, const void* B, void* X, bms_stats* stats);

@@ -132,7 +132,12 @@ int ensure_buf(bms_ctx* c, DevBuf& b, size_t bytes) {
     b.p = nullptr;
     b.bytes = 0;
   }
-  HIP_TRY(c, hipMalloc(&b.p, bytes));
+  hipError_t e = hipMalloc(&b.p, bytes);
+  if (e != hipSuccess) {
+    b.p = nullptr;
+    (void)hipGetLastError();  // reported here, not by the next launch's check
+    HIP_TRY(c, e);
+  }
   b.bytes = bytes;
   // fresh device memory may hold stale data; counters and flags rely on zero
   HIP_TRY(c, hipMemsetAsync(b.p, 0, bytes, c->stream));

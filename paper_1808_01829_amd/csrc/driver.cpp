@@ -270,10 +270,26 @@ extern "C" int bms_solve_batch(int nprob, bms_ctx* const* ctxs, const double* ma
   // All workspace first, one context after another: a solve that grew a
   // buffer inside a thread would free and allocate device memory while a
   // sibling thread captures its iteration chunk into a hipGraph.
+  auto windows_again = [&] {
+    for (int j = 0; j < nprob; ++j) ctxs[j]->win_limit = BMS_MAX_WIN;
+  };
+  bool lean = false;
   for (int i = 0; i < nprob; ++i) {
     int rc = solve_reserve(ctxs[i], mass[i], n[i], n_shifts[i], shifts[i], tol[i], max_iter[i],
                            opts ? &opts[i] : nullptr, B[i], X[i]);
+    if (rc == BMS_ENOMEM && !lean) {
+      // what is missing may be in the other problems' update windows
+      lean = true;
+      for (int j = 0; j < nprob; ++j) {
+        bms_opts o;
+        bms_default_opts(&o);
+        (void)drop_windows(ctxs[j], n[j], n_shifts[j], (opts ? opts[j] : o).check_interval);
+      }
+      i = -1;
+      continue;
+    }
     if (rc) {
+      windows_again();
       for (int j = 0; j < nprob; ++j) status[j] = j == i ? rc : BMS_OK;
       return rc;
     }
@@ -286,6 +302,7 @@ extern "C" int bms_solve_batch(int nprob, bms_ctx* const* ctxs, const double* ma
                             opts ? &opts[i] : nullptr, B[i], X[i], stats ? &stats[i] : nullptr);
     });
   for (auto& t : th) t.join();
+  windows_again();
   for (int i = 0; i < nprob; ++i)
     if (status[i] != BMS_OK) return status[i];
   return BMS_OK;

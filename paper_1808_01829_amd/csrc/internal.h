@@ -140,6 +140,7 @@ struct bms_ctx {
   std::vector<double> kt_upd_launch;
   std::vector<hipEvent_t> evpool;
   GraphCache<hipGraphExec_t> graphs;  // captured chunks of iterations
+  int win_limit = BMS_MAX_WIN;  // of the update windows; 1 for a solve short of memory
   // work done by the current bms_solve (reset at its start, reported in bms_stats)
   long it_f64 = 0, it_f32 = 0, hop_work = 0, rel_work = 0;
 };
@@ -165,6 +166,7 @@ int solve_validate(bms_ctx* c, double mass, int n, int ns, const double* shifts,
 // size every workspace slot a solve of this shape may use (see solver.cpp)
 int solve_reserve(bms_ctx* c, double mass, int n, int ns, const double* shifts, double tol,
                   int max_iter, const bms_opts* opts, const void* B, const void* X);
+bool drop_windows(bms_ctx* c, int n, int ns, int check_interval);
 int stream_end(bms_ctx* c);
 
 // The calls other than the solves enqueue their work on the caller's stream itself: while

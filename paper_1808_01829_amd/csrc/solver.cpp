@@ -65,7 +65,7 @@ int update_window(const bms_ctx* c, int n, int ns, int elem_bytes, int check_int
   if (ns < 2 || !update_windowed(n)) return 1;
   if (update_mfma_supported(n) && !(uv < 0 || uv == 4 || uv == 5)) return 1;
   int w = elem_bytes == 8 ? update_mfma_max_win<double>(n) : update_mfma_max_win<float>(n);
-  w = std::min(w, BMS_MAX_WIN);
+  w = std::min(w, c->win_limit);
   while (w > 1 && check_interval % w) w >>= 1;
   return w;
 }
@@ -547,6 +547,24 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
 
 }  // namespace
 
+// A solve of this shape found no memory: give back the ring of residual blocks that its
+// windows need (3 blocks more in FP64, 7 FP32 ones in mixed precision than an update
+// of every iteration) and do without windows until win_limit is reset. Returns whether that
+// leaves anything to try.
+bool drop_windows(bms_ctx* c, int n, int ns, int check_interval) {
+  if (update_window(c, n, ns, 8, check_interval) < 2 &&
+      update_window(c, n, ns, 4, check_interval) < 2)
+    return false;
+  c->win_limit = 1;
+  c->last_error.clear();
+  if ((int)c->scratch.size() > S_Q && c->scratch[S_Q].p) {
+    DevBuf& q = c->scratch[S_Q];
+    if (hipStreamSynchronize(c->stream) != hipSuccess || hipFree(q.p) != hipSuccess) return false;
+    q = DevBuf();
+  }
+  return true;
+}
+
 // Size every workspace slot that a solve of n columns, ns shifts and max_iter
 // iterations can touch, in any phase and precision (FP64 blocks are the
 // larger), and the event pool of per-kernel timing. Called serially for each
@@ -572,10 +590,11 @@ int solve_reserve(bms_ctx* c, double mass, int n, int ns, const double* shifts, 
   if ((rc = ensure_device(c))) return rc;
   const size_t rows = (size_t)3 * c->vh, blk = rows * n, nn = (size_t)n * n, e = sizeof(double2);
   void* p;
-  const struct {
+  struct Need {
     int slot;
     size_t bytes;
-  } need[] = {
+  };
+  const Need need[] = {
       {S_W1, blk * e},
       {S_W, blk * e},
       {S_Q, blk * std::max(e * update_window(c, n, ns, 8, check_interval),
@@ -600,8 +619,13 @@ int solve_reserve(bms_ctx* c, double mass, int n, int ns, const double* shifts, 
       {S_E2, (size_t)ns * blk * e},
       {S_CMAT, nn * e + 64},
   };
-  for (const auto& q : need)
-    if ((rc = scratch_buf(c, q.slot, q.bytes, &p))) return rc;
+  for (const Need& q : need) {
+    if ((rc = scratch_buf(c, q.slot, q.bytes, &p)) == BMS_OK) continue;
+    // without windows the rest may fit (bms_solve keeps to that)
+    if (rc == BMS_ENOMEM && drop_windows(c, n, ns, check_interval))
+      return solve_reserve(c, mass, n, ns, shifts, tol, max_iter, opts, B, X);
+    return rc;
+  }
   if (c->timing && (int)c->evpool.size() < 8 * check_interval) {
     size_t old = c->evpool.size();
     c->evpool.resize(8 * check_interval);
@@ -1069,10 +1093,13 @@ extern "C" int bms_solve(bms_ctx* c, double mass, int n, int ns, const double* s
   bms_default_opts(&o);
   if (opts) o = *opts;
   if ((rc = stream_begin(c))) return rc;
-  if (o.precision == BMS_PREC_F64)
-    rc = solve_precision<double>(c, mass, n, ns, shifts, tol, max_iter, o, B, X, st);
-  else
-    rc = solve_precision<float>(c, mass, n, ns, shifts, tol, max_iter, o, B, X, st);
+  do {
+    if (o.precision == BMS_PREC_F64)
+      rc = solve_precision<double>(c, mass, n, ns, shifts, tol, max_iter, o, B, X, st);
+    else
+      rc = solve_precision<float>(c, mass, n, ns, shifts, tol, max_iter, o, B, X, st);
+  } while (rc == BMS_ENOMEM && drop_windows(c, n, ns, o.check_interval));
+  c->win_limit = BMS_MAX_WIN;
   int rc2 = stream_end(c);
   return rc ? rc : rc2;
 }
