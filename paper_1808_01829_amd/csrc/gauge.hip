@@ -328,6 +328,9 @@ __device__ __forceinline__ M3 exp_i(const M3& X) {
   return E;
 }
 
+// two momenta of a link; a caller's P has the alignment of double
+typedef double d2a8 __attribute__((ext_vector_type(2), aligned(8)));
+
 // U_mu(x) <- exp(i eps P^a T^a) U_mu(x), one thread per link; bound by reading U and P and
 // writing U once, the links as whole lines (links.h). Measured at 16^3 x 32: 56 -> 28 us
 // (184 MB, most of it in the Infinity Cache).
@@ -347,7 +350,7 @@ __global__ __launch_bounds__(BMS_WG) void k_link_update(double2* __restrict__ U,
   double p[8];
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    const double2 v = ((const double2*)P)[(size_t)t * 4 + a];
+    const d2a8 v = ((const d2a8*)P)[(size_t)t * 4 + a];
     p[2 * a] = v.x;
     p[2 * a + 1] = v.y;
   }

@@ -92,3 +92,24 @@ def test_force_takes_the_fields_own_third_rows(dims, n):
         Xd = to_dev(torch, X)
         assert rel(to_np(c.force(r.alpha, Xd, bms.BMS_FORCE_RAW)), Go) < 1e-13
         assert rel(to_np(c.force(r.alpha, Xd, bms.BMS_FORCE_LIE)), Fo) < 1e-13
+
+
+# momenta at an odd multiple of 8 bytes, the alignment of their type
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 4, 2, 6)])
+def test_momenta_aligned_to_8_bytes(dims):
+    torch = torch_gpu()
+    from paper_1808_01829_amd import bms
+    U = random_gauge(dims, 0.7, 11)
+    P = np.random.default_rng(12).standard_normal((4, int(np.prod(dims)), 8))
+    buf = torch.zeros(P.size + 2, dtype=torch.float64, device="cuda")
+    Pd = buf[1:-1].view(P.shape)
+    assert Pd.data_ptr() % 16 == 8
+    Pd.copy_(to_dev(torch, P))
+    c = bms.Context(dims, BC)
+    Ud = to_dev(torch, U)
+    c.gauge_update(0.05, Pd, Ud)
+    assert rel(to_np(Ud), R.link_update(U, P, 0.05)) < 1e-13
+    assert abs(c.kinetic_energy(Pd) - 0.5 * (P ** 2).sum()) < 1e-12 * (P ** 2).sum()
+    c.gauge_force(5.6, to_dev(torch, U), Pd, -0.3)
+    assert rel(to_np(Pd), P - 0.3 * R.gauge_force(dims, U, 5.6)) < 1e-13
+    assert buf[0] == 0 and buf[-1] == 0
