@@ -1,0 +1,68 @@
+"""Calls on the caller's stream and solves on the library's, in turn, on one context.
+
+Every call other than a solve is enqueued on the caller's stream itself and a solve runs on the
+library's own, ordered behind and before the caller's. Here the caller's stream is a torch
+stream that is not the default one, its inputs are written on it by work that takes a while, each
+call takes the output of another, and nothing waits in between. A call that did not wait
+for its input would read the zeros, or an earlier round's block, that the buffer held before.
+
+Tolerances: as in the tests of the single calls.
+"""
+import numpy as np
+import pytest
+
+from gpu_common import rel, to_dev, to_np, torch_gpu
+from oracle import oracle as O
+from paper_1808_01829_amd.inputs import configs, gaussian_block, random_gauge
+
+pytestmark = pytest.mark.gpu
+DIMS, BC, M = (4, 4, 4, 6), (1, 1, 1, -1), 0.1
+
+
+@pytest.mark.parametrize("n", [3, 8])
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("default", [False, True])
+def test_calls_and_solves_in_turn(n, mixed, default):
+    torch = torch_gpu()
+    from paper_1808_01829_amd import bms
+    r = configs.workload_coefficients("c1")
+    st = torch.cuda.default_stream() if default else torch.cuda.Stream()
+    big = torch.rand(64 << 20, device="cuda")
+    Us = [random_gauge(DIMS, 0.5, 700 + k) for k in range(2)]
+    Bs = [gaussian_block(DIMS, n, 710 + k) for k in range(2)]
+    src = [(to_dev(torch, U), to_dev(torch, B)) for U, B in zip(Us, Bs)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        ctx = bms.Context(DIMS, BC)  # on the current stream
+        U, B = torch.zeros_like(src[0][0]), torch.zeros_like(src[0][1])
+        outs = []
+        for Ud, Bd in src + src:
+            for _ in range(20):
+                big.mul_(1.0000001)
+            U.copy_(Ud)
+            B.copy_(Bd)
+            ctx.set_gauge(U)
+            for _ in range(20):
+                big.mul_(1.0000001)
+            B.mul_(2.0)
+            v = ctx.apply_mdagm(M, 0.2, B)               # caller's stream
+            X, _ = ctx.solve(M, r.beta, v, tol=1e-11,    # the library's
+                             precision=bms.BMS_PREC_MIXED if mixed else bms.BMS_PREC_F64)
+            w = ctx.apply_hop(1, X[0].contiguous())      # caller's again
+            F = ctx.force(r.alpha, X, bms.BMS_FORCE_LIE)
+            S = ctx.action(r.a0, r.alpha, v, X)
+            outs.append((v, X, w, F, S))
+            B.zero_()                                    # behind all of it
+    torch.cuda.synchronize()
+    for k, (v, X, w, F, S) in enumerate(outs):
+        U0, B0 = Us[k % 2], 2 * Bs[k % 2]
+        vo = O.mdagm(DIMS, BC, U0, M, 0.2, B0)
+        assert rel(to_np(v), vo) < 1e-13
+        Xn = to_np(X)
+        assert O.true_residuals(DIMS, BC, U0, M, r.beta, vo, Xn).max() <= 1.01e-11
+        wo = np.stack([O.dslash_half(DIMS, BC, U0, 1, np.ascontiguousarray(Xn[0][..., j]))
+                       for j in range(n)], axis=-1)
+        assert rel(to_np(w), wo) < 1e-13
+        assert rel(to_np(F), O.lie_force(U0, O.force(DIMS, BC, U0, r.alpha, Xn))) < 1e-12
+        So = O.action(vo, Xn, r.a0, r.alpha)
+        assert np.abs(np.array(S) - So).max() < 1e-12 * np.abs(So).max()
