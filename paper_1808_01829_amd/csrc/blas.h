@@ -26,6 +26,7 @@ struct UpdateArgs {
   SolverFlags* flags;         // read; the matrix-core update also sets upd_done, upd_stop
   int* upd_log;               // [max_iter] traffic and work of each iteration's update
   int max_iter;
+  int num_cu;                 // compute units of the device
   int closing;                // k_update_close follows and takes the windows closed together
   int xidx[BMS_MAX_SHIFTS];
 };

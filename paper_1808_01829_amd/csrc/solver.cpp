@@ -152,8 +152,9 @@ const int kIterKernel[7] = {BMS_KERNEL_HOP,   BMS_KERNEL_HOP,   BMS_KERNEL_GRAM,
                             BMS_KERNEL_CHOLQR, BMS_KERNEL_SMALL, BMS_KERNEL_UPDATE};
 
 template <typename T>
-UpdateArgs<T, T> update_args(const Work& w) {
+UpdateArgs<T, T> update_args(const bms_ctx* c, const Work& w) {
   UpdateArgs<T, T> ua;
+  ua.num_cu = c->num_cu;
   ua.rows = w.rows;
   ua.n = w.n;
   ua.ns = w.ns;
@@ -215,7 +216,7 @@ int enqueue_iteration(bms_ctx* c, const Work& w, const SmallParams& sp, double m
     HIP_TRY(c, launch_small_rho_explicit<T>(c->stream, sp, w.sm, w.flags, (cplx<T>*)w.Mp,
                                             (cplx<T>*)w.Wm));
   MARK(6);
-  const UpdateArgs<T, T> ua = update_args<T>(w);
+  const UpdateArgs<T, T> ua = update_args<T>(c, w);
   // the windowed kernels (n = 8, 16: unless a vector variant is set; n > 16: with a window),
   // else the vector kernel
   const int uv = c->update_variant;
@@ -481,9 +482,8 @@ int solve_core(bms_ctx* c, double mass, int n, int ns, const double* sigma, cons
     if (enqueued > (long)max_iter + 2L * K)  // the device stops itself at max_iter
       return set_err(c, BMS_EHIP, "device iteration control did not stop (iter %d)", hf.iter);
   }
-  // increments the two-iteration update still holds back
   // windows the solve ended with still open
-  if (w.win > 1) HIP_TRY(c, launch_update_drain<T>(c->stream, update_args<T>(w)));
+  if (w.win > 1) HIP_TRY(c, launch_update_drain<T>(c->stream, update_args<T>(c, w)));
   if (c->timing && hf.iter > 0) {
     std::vector<int> units(hf.iter);
     HIP_TRY(c, hipMemcpyAsync(units.data(), w.upd_log, hf.iter * sizeof(int),

@@ -1104,14 +1104,16 @@ void k_update_vec(UpdateArgs<F, F> a) {
     __syncthreads();  // every wave is done with this shift's coefficients
   }
 }
+
 // Groups the shifts of an update are dealt to: as many as bring the launch to about
 // two work-groups per compute unit, so that a small lattice, whose rows alone leave most of
 // the chip idle while each work-group walks its shifts one after the other, spreads the
 // shifts too. Measured at 8^4, FP64, 16 shifts, full windows, one group and with this rule:
 // n = 4 23.3 and 12.8 us, n = 8 49.9 and 20.2, n = 16 114 and 40.
-int shift_groups(int blocks, int ns, int win) {
-  if (win < 2) return 1;  // Q is updated in place
-  return std::min(ns, std::max(1, 512 / blocks));
+template <typename F>
+int shift_groups(const UpdateArgs<F, F>& a, int blocks) {
+  if (a.win < 2) return 1;  // Q is updated in place
+  return std::min(a.ns, std::max(1, 2 * a.num_cu / blocks));
 }
 
 template <typename F, int N, int NTILE, bool RT>
@@ -1119,7 +1121,7 @@ hipError_t launch_mf(hipStream_t st, const UpdateArgs<F, F>& a) {
   int tiles = (a.rows + 15) / 16;
   int waves = (tiles + NTILE - 1) / NTILE;
   int blocks = (waves + MF_WAVES - 1) / MF_WAVES;
-  const dim3 grid(blocks, shift_groups(blocks, a.ns, a.win));
+  const dim3 grid(blocks, shift_groups(a, blocks));
   UpdateArgs<F, F> b = a;
   // where the rows alone fill the chip, the windows that close together go to their own
   // kernel (FP32 at n = 8: no gain)
@@ -1128,8 +1130,9 @@ hipError_t launch_mf(hipStream_t st, const UpdateArgs<F, F>& a) {
   k_update_mfma<F, N, NTILE, RT><<<grid, BMS_WG, 0, st>>>(b);
   if constexpr (own)
     if (b.closing) {
+      // one work-group per compute unit (its LDS holds one at n = 16)
       const int nblk = (a.rows + 16 * CL_WAVES - 1) / (16 * CL_WAVES);
-      k_update_close<F, N><<<std::min(nblk, 256), CL_THREADS, 0, st>>>(b);
+      k_update_close<F, N><<<std::min(nblk, a.num_cu), CL_THREADS, 0, st>>>(b);
     }
   return hipGetLastError();
 }
@@ -1137,7 +1140,7 @@ hipError_t launch_mf(hipStream_t st, const UpdateArgs<F, F>& a) {
 template <typename F, int N>
 hipError_t launch_wide(hipStream_t st, const UpdateArgs<F, F>& a) {
   const int blocks = ((a.rows + 15) / 16 + MF_WAVES - 1) / MF_WAVES;
-  const dim3 grid(blocks, shift_groups(blocks, a.ns, a.win));
+  const dim3 grid(blocks, shift_groups(a, blocks));
   k_update_wide<F, N><<<grid, BMS_WG, 0, st>>>(a);
   return hipGetLastError();
 }
@@ -1146,7 +1149,7 @@ template <typename F, int N>
 hipError_t launch_vec(hipStream_t st, const UpdateArgs<F, F>& a) {
   constexpr int RPB = MF_WAVES * (64 / N);  // rows per work-group
   const int blocks = (a.rows + RPB - 1) / RPB;
-  const dim3 grid(blocks, shift_groups(blocks, a.ns, a.win));
+  const dim3 grid(blocks, shift_groups(a, blocks));
   k_update_vec<F, N><<<grid, BMS_WG, 0, st>>>(a);
   return hipGetLastError();
 }
