@@ -30,17 +30,23 @@ struct ForceArgs {
   double alpha[BMS_MAX_SHIFTS];
 };
 
-// Entry e of link k of checkerboard site s of parity par. All nine are the field's own: the
-// check at import accepts third rows that are off SU(3) by 1e-12, which is what rebuilding
-// them would cost a force that holds its sums to rounding.
-__device__ __forceinline__ double2 link_entry(const ForceArgs& a, int par, uint32_t s, int k,
-                                              int e) {
-  const bool t = a.epl == 6 && e >= 6;
-  const double2* L = t ? a.third : a.links;
-  const int epl = t ? 3 : a.epl;
-  return L[(par * a.nblk * (8 * epl) << a.sbl) +
-           link_off(s, k, t ? e - 6 : e, a.sbl, 8 * epl, epl)];
-}
+// The links of checkerboard site s of parity par, entry e of link k. All nine are the field's
+// own: the check at import accepts third rows that are off SU(3) by 1e-12, which is what
+// rebuilding them would cost a force that holds its sums to rounding.
+struct SiteLinks {
+  const double2 *a, *third;
+  int epl, sbl;
+  __device__ __forceinline__ SiteLinks(const ForceArgs& f, int par, uint32_t s)
+      : epl(f.epl), sbl(f.sbl) {
+    const size_t blk = par * f.nblk + (s >> sbl);
+    const uint32_t in = s & ((1u << sbl) - 1);
+    a = f.links + (blk * (8 * epl) << sbl) + in;
+    third = f.third + (blk * 24 << sbl) + in;
+  }
+  __device__ __forceinline__ double2 operator()(int k, int e) const {
+    return epl == 6 && e >= 6 ? third[(k * 3 + e - 6) << sbl] : a[(k * epl + e) << sbl];
+  }
+};
 
 // Sum of a complex value over the LPL lanes of this lane's group (LPL a power
 // of two dividing the wave): every lane of the group ends with the total.
@@ -135,10 +141,11 @@ __global__ __launch_bounds__(BMS_WG) void k_force(ForceArgs a, int lpl) {
   }
   if (lane != 0) return;
   // U_mu(w) from the forward link of parity par: L = (1/2) eta b U
+  const SiteLinks L(a, par, cb);
   double2 u[9];
   double f = 2.0 * ((esum & 1) ? -1.0 : 1.0) * ((co[mu] == g.L[mu] - 1) ? a.bc[mu] : 1);
   for (int e = 0; e < 9; ++e)
-    u[e] = cscale(link_entry(a, par, cb, mu, e), f);
+    u[e] = cscale(L(mu, e), f);
   // W = U M; F^a = Im Tr[T^a W], T^a = lambda_a / 2
   double2 w[9];
   for (int i = 0; i < 3; ++i)
@@ -243,21 +250,22 @@ __global__ __launch_bounds__(BMS_WG, WAVES) void k_force_fused(ForceArgs a) {
   const double bf = co[mu] == g.L[mu] - 1 ? (double)a.bc[mu] : 1.0;
   const double be = co[mu] == 0 ? (double)a.bc[mu] : 1.0;
   __shared__ double2 lds[LDS_LINKS ? kForceSites * kLinkPitch : 1];
+  const SiteLinks L(a, 1, z);
   double2 la[9], lb[9];
   if (LDS_LINKS) {
     // the four g-lanes of (site, q) stage the site's links mu and 4 + mu
     double2* sa = lds + sl * kLinkPitch + mu * 9;
     double2* sb_ = sa + 36;
     for (int e = gl; e < 9; e += 4) {
-      sa[e] = link_entry(a, 1, z, mu, e);
-      sb_[e] = link_entry(a, 1, z, 4 + mu, e);
+      sa[e] = L(mu, e);
+      sb_[e] = L(4 + mu, e);
     }
     __syncthreads();
   } else {
 #pragma unroll
     for (int e = 0; e < 9; ++e) {
-      la[e] = link_entry(a, 1, z, mu, e);
-      lb[e] = link_entry(a, 1, z, 4 + mu, e);
+      la[e] = L(mu, e);
+      lb[e] = L(4 + mu, e);
     }
   }
   double2 ma[9], mb[9];
