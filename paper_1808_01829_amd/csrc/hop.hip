@@ -25,8 +25,8 @@ struct Bc {
 // One thread per site, a wave over 64 consecutive ones, so that U is read as whole lines
 // (links.h) and either parity's entries are written as runs of 32 sites. Bound by that
 // traffic, the writes above all. Measured at 16^3 x 32: 206 us with both forms written,
-// an atomic per link and links read a thread each, and 60 us of fills -> 48 us (6 of
-// them the third rows).
+// an atomic per link and links read a thread each, and 60 us of fills -> 53 us (11
+// of them the third rows).
 template <int EPL>
 __global__ __launch_bounds__(BMS_WG) void k_gauge_import(
     const double2* __restrict__ U, double2* __restrict__ l64, float2* __restrict__ l32,
@@ -918,8 +918,8 @@ HopSmall hop_small(const bms_ctx* c, int n, bool quad, bool fp64) {
 }  // namespace
 
 // Whether the half hop takes four threads per site: the widths 4, 8, 16 and 32 always; 12, 20
-// and 24, where the threads of k_hop hold four columns and each load every link, from 1.5
-// waves per SIMD on. Measured k_hop / four threads, FP64 (FP32) us: n = 12 32^4 369 / 278
+// and 24, where the threads of k_hop hold two (n = 12) or four columns and each load every link,
+// from 1.5 waves per SIMD on. Measured k_hop / four threads, FP64 (FP32) us: n = 12 32^4 369 / 278
 // (222 / 169), 16^4 24.1 / 16.4 (15.0 / 11.9), 16^3 x 12 17.3 / 13.4; n = 20 and 24 at 16^4
 // 38 / 26 and 41 / 29. Below that k_hop has more waves, or its batch of hops in flight: n = 12
 // at 14^4 13.2 / 15.2, n = 24 at 12^4 15.1 / 16.8. (28 gains at 16^4 and loses at 20^4.)
@@ -1016,8 +1016,8 @@ hipError_t launch_hop(const bms_ctx* c, int par, int n, const void* in, void* ou
   const cplx<T>* links = (const cplx<T>*)lb.p + (size_t)par * pstride;
   const uint32_t* sgn = two ? (const uint32_t*)c->lsign.p + (size_t)par * c->vh : nullptr;
   // Variants: 0 one thread per (site, column group), 1 four threads per site
-  // sharing the links (n = 4, 8, 16, 32), 2 and 3 the same in the tiled
-  // traversal; the default is 1, tiled in FP64 at n >= 16. The traversal's
+  // sharing the links (where hop_quad allows, else as 0), 2 and 3 the same in the
+  // tiled traversal; the default is 1, tiled as hop_plan has it. The traversal's
   // tile extents, resident cap and link-load hint come from the context's
   // hop configuration (bms_set_hop_config, bms_autotune).
   const HopPlan hp = hop_plan(c, n, sizeof(T) == 8);

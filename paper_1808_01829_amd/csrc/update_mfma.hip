@@ -275,8 +275,9 @@ __device__ __forceinline__ unsigned long long windows_due(const SolverFlags* fl,
 // One tile per wave: four waves per SIMD in FP32, three in FP64 (the register
 // count the compiler picks by itself leaves fewer; in FP64 four waves need
 // spills, whose scratch traffic reached HBM).
-// RT: the width is a.n (9 .. 15, at most N), else N. Measured at n = 12 (12.14.10.24, 15
-// shifts, FP64) against the every-iteration vector kernel: 90.0 -> 35.3 us per launch.
+// RT: the width is a.n (9 .. 15, at most N), else N. Measured at 16^4 with
+// 12 shifts, FP64, k_update_close included, against the every-iteration vector kernel, us per
+// iteration: n = 9 265 -> 87, n = 12 354 -> 77 to 84, n = 14 501 -> 115.
 // gridDim.y: the shifts are dealt to that many groups of work-groups (shift s to
 // group s % gridDim.y), which all form Q_{k+1} and of which the first stores
 // it; more than one only with a ring (win > 1), where nothing is overwritten.
@@ -805,7 +806,8 @@ void k_update_close(UpdateArgs<F, F> a) {
 // zero A operand, output columns past n are not used. On the matrix cores 2 x 2 x 3 N / 4
 // steps (FP32 2 x 2 x N) of 16 x 16 x 4 a tile, iteration and shift; X and P are moved once per window, where
 // the vector kernel for any n, which this replaces, moved them every iteration. Measured at
-// 16^4, 12 shifts, FP64, per iteration: n = 32 674 -> 205 us, n = 24 612 -> 182 (FP32 291 -> 77).
+// 16^4, 12 shifts none of which converges, FP64, per iteration: n = 32 1484 -> 403 us, n = 24
+// 1028 -> 287 (FP32 897 -> 175).
 template <typename F, int N>
 __global__ __launch_bounds__(BMS_WG) __attribute__((amdgpu_waves_per_eu(2)))
 void k_update_wide(UpdateArgs<F, F> a) {
