@@ -122,8 +122,8 @@ __device__ __forceinline__ void mfma_acc_c(typename Mf<F>::V (&d)[MfShape<N>::NT
 // the matrix cores; the Q step of every width but 16, and FP32 windows above 16, take four,
 // which costs them little. Against the vector kernels that updated every iteration with plain
 // multiply-adds, rms error of X after 12 or 16 iterations (4 x 6 x 4 x 6, five shifts,
-// the mean over them): FP64 0.82 at n = 9, 0.84 at 12, 0.78 at 15, 0.99 to 1.01 from 17 to
-// 32; FP32 0.97, 0.96, 0.94, and 0.96 falling to 0.88. Four products in all windows: 0.78,
+// the mean over them): FP64 0.82 at n = 9, 0.84 at 12, 0.78 at 15, 0.99 to 1.02 from 17 to
+// 32; FP32 0.97, 0.96, 0.94, and 0.93 falling to 0.87. Four products in all windows: 0.78,
 // 0.81, 0.76 and FP32 0.92, 0.91, 0.91, for 10 % of the update's time (n = 12 FP64 81 -> 90
 // us at 16^4).
 template <typename F, int N, bool RT, int ACC>

@@ -2,7 +2,7 @@
 iteration, so the sum of its window is one large term, P Cx, and small ones. Added
 to last, the large term costs the rounding of one product of n columns; added to first,
 every later term of the window is rounded at its size too (eight iterations in FP32 blocks:
-up to 2.9 times the error).
+up to 2.7 times the error).
 
 FP32 blocks from the start (mixed_switch 0), k iterations, X against the FP64 oracle's
 iterate k. Tolerance, for a sum of 2 n products per real part with rms unit rounding
