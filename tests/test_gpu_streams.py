@@ -4,7 +4,7 @@ Every call other than a solve is enqueued on the caller's stream itself and a so
 library's own, ordered behind and before the caller's. Here the caller's stream is a torch
 stream that is not the default one, its inputs are written on it by work that takes a while, each
 call takes the output of another, and nothing waits in between. A call that did not wait
-for its input would read the zeros, or an earlier round's block, that the buffer held before.
+for its input would read the zeros, or an earlier pass's block, that the buffer held before.
 
 Tolerances: as in the tests of the single calls.
 """
